@@ -15,10 +15,13 @@ namespace csgv {
 constexpr uint32_t kMaxWaves = 16;       // work-groups of up to 1024 threads
 constexpr uint32_t kFullSlots = 4688;    // full grids of levels 0..4 at 0, 8, 16, 80, 592
 constexpr uint32_t kEWords = 148;        // expansion bitmaps of levels 0..4: 1+1+2+16+128 words
-constexpr uint32_t kUBytes = 8192;       // parent list of the level being decoded | staged palette
+constexpr uint32_t kUBytesMin = 2048;    // parent list / palette area of the smallest slot area
 constexpr uint32_t kMinCap16 = 8192;     // 16 KiB: the rANS table
 constexpr uint32_t kMaxCap16 = 32760;    // largest LDS slot share accepted
 constexpr uint32_t kDefaultCap16 = 10240;
+// parent list of level 5 (one 16-bit entry per 8 slots) | staged palette
+__host__ __device__ constexpr uint32_t list_bytes(uint32_t cap16) { return (cap16 / 4u + 15u) & ~15u; }
+static_assert(list_bytes(kMinCap16) >= kUBytesMin, "palette area");
 
 // ---- per work-group global scratch (byte offsets).  Big-path level storage
 // (32-bit slots: full grids of levels 0..4, level 5 by rank), the level-5

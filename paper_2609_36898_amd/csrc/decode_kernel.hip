@@ -75,30 +75,29 @@ constexpr uint32_t kHdrWords = 2 + 7 + 4;
 
 struct TaskHdr {
     uint32_t hw[kHdrWords];  // the record's first words (parse_task)
-    uint32_t task, status, write_ok, coder, L, t, log2W, pc, big, c5g, pal_lds, nsym;
+    uint32_t task, status, write_ok, coder, L, t, log2W, pc, nsym;
     uint32_t sym_end[7];
     uint32_t gw[4], gstart[4];
     uint64_t out_off, pal_off, pay_off, states_off;
 };
 
+// Fixed part of a work-group's LDS; the parent list / palette area (u_bytes) and
+// the slot area follow it.
 struct Shared {
     TaskHdr h;   // the task being decoded
     TaskHdr hn;  // the work-group's next task, parsed ahead
     uint32_t err;
-    uint32_t tab_ok;                     // the rANS table is in LDS from an earlier task
-    uint32_t prog[4];                    // per rANS lane group: symbols out so far (release/acquire)
-    uint32_t nexp;                       // expanding nodes of the parent level of the next level
-    uint32_t adv;                        // PALETTE_ADV operations decoded so far (handed between phases)
-    uint32_t pub[2][kMaxWaves][4];       // per pass and wave: run summary (f, n, a)
-    uint32_t E[kEWords];                 // expansion bitmaps of levels 0..4
-    uint16_t wpre[kEWords];              // exclusive popcount prefix of each bitmap word
-    alignas(16) uint16_t G[kFullSlots];  // full grids of levels 0..4 (fast path)
-    alignas(16) uint8_t U[kUBytes];      // parent list of the level being decoded | staged palette
+    uint32_t tab_ok;                // the rANS table is in LDS from an earlier task
+    uint32_t prog[4];               // per rANS lane group: symbols out so far (release/acquire)
+    uint32_t nexp;                  // expanding nodes of the parent level of the next level
+    uint32_t adv;                   // PALETTE_ADV operations decoded so far (handed between phases)
+    alignas(16) uint4 pub[2][kMaxWaves];  // per pass and wave: run summary (exit states, counts)
+    alignas(16) uint2 EP[kEWords];        // expansion bitmaps of levels 0..4: bits, prefix
+    alignas(16) uint16_t G[kFullSlots];   // full grids of levels 0..4
 };
-static_assert(sizeof(Shared) % 16 == 0, "the slot area follows Shared 16-byte aligned");
+static_assert(sizeof(Shared) % 16 == 0, "the areas behind Shared are 16-byte aligned");
 static_assert(sizeof(TaskHdr) % 4 == 0 && sizeof(TaskHdr) / 4 <= 128, "a header is copied one word per thread");
-static_assert(offsetof(Shared, U) == offsetof(Shared, G) + sizeof(Shared::G) &&
-                  offsetof(Shared, U) + sizeof(Shared::U) == sizeof(Shared),
+static_assert(offsetof(Shared, G) + sizeof(Shared::G) == sizeof(Shared),
               "grids, parent list and slot area form one range (rANS staging)");
 
 // ------------------------------------------------------ wave/block helpers
@@ -135,24 +134,6 @@ __device__ __forceinline__ void lsync() {
     } else {
         __syncthreads();
     }
-}
-
-// 2-state transfer function of one symbol, or of a run of symbols:
-// bit e = state after the run when it was entered in state e
-// (state 0: the next symbol is an operation; state 1: it is a delta entry).
-__host__ __device__ constexpr uint32_t fn_then_ref(uint32_t first, uint32_t second) {
-    return ((second >> (first & 1)) & 1) | (((second >> ((first >> 1) & 1)) & 1) << 1);
-}
-// all 16 compositions, 2 bits each at bit 2 * (4 * first + second)
-__host__ __device__ constexpr uint32_t fn_then_table() {
-    uint32_t t = 0;
-    for (uint32_t a = 0; a < 4; ++a)
-        for (uint32_t b = 0; b < 4; ++b) t |= fn_then_ref(a, b) << (2 * (4 * a + b));
-    return t;
-}
-constexpr uint32_t kFnThen = fn_then_table();
-__device__ __forceinline__ uint32_t fn_then(uint32_t first, uint32_t second) {
-    return (kFnThen >> (2u * (4u * first + second))) & 3u;
 }
 
 // DPP moves (GFX9 controls).  A lane whose source lane does not exist, or
@@ -197,7 +178,6 @@ __device__ __forceinline__ void parse_task(const Params& P, uint32_t task, TaskH
     h.task = task;
     h.status = kTaskOk;
     h.write_ok = 0;
-    h.big = 0;
     const uint32_t id = P.ids[task];
     const uint32_t lod = P.lods[task];
     const uint64_t out_off = P.out_offs ? P.out_offs[task] : P.dense_offs[task];
@@ -269,13 +249,6 @@ __device__ __forceinline__ void parse_task(const Params& P, uint32_t task, TaskH
     h.pal_off = a + pal_rel;
     h.pay_off = a + pay_rel;
     h.nsym = h.sym_end[t];
-    // explicit nodes of level 5: at most one per symbol of its segment
-    const uint32_t need5 = t >= 5 ? h.sym_end[5] - h.sym_end[4] : 0u;
-    // a 32^3 cube at full resolution whose level 5 outgrows the LDS slot area
-    // keeps levels 0..4 in LDS and only its level-5 slots in scratch (c5g)
-    h.big = pc > 32768u || (need5 > P.cap16 && t != 5);
-    h.c5g = !h.big && need5 > P.cap16;
-    h.pal_lds = (uint64_t)pc * lb <= kUBytes;
     // cache-paletted output: a palette beyond 2^I entries, or a 64^3 cube, has no packed form
     if (P.pal_bits && (t == 6 || (uint64_t)pc > (1ull << P.pal_bits))) {
         h.status = kTaskInvalid;
@@ -442,558 +415,6 @@ __device__ __forceinline__ void rans_rounds(const Params& P, Shared& sh, const u
     }
 }
 
-// The decode with the record's words staged in LDS (`stage`, the level grids
-// and slot area, idle until the levels start) and the symbols in LDS at `nl`;
-// with `nib` set, the symbols then reach it in one coalesced copy.  The caller
-// checks that words and symbols fit.
-template <int NT>
-__device__ __forceinline__ void rans_decode_lds(const Params& P, Shared& sh, const uint32_t* tab, uint8_t* stage,
-                                                uint8_t* nl, uint8_t* nib) {
-    const uint32_t x0 = rans_stage_words<NT>(P, sh.h, (uint16_t*)stage);
-    __syncthreads();
-    rans_rounds<NT>(P, sh, tab, (const uint16_t*)stage, nl, x0, 0u);
-    if (nib) {
-        __syncthreads();
-        const uint32_t nw = ((sh.h.nsym + 1u) / 2u + 3u) / 4u;
-        for (uint32_t q = threadIdx.x; q < nw; q += NT) ((uint32_t*)nib)[q] = ((const uint32_t*)nl)[q];
-    }
-}
-
-// ------------------------------------------------------------ level store
-template <typename V>
-struct Slot {
-    static constexpr V kFinal = (V)(V(1) << (sizeof(V) * 8 - 1));
-    static constexpr V kIdx = (V)(kFinal - 1);
-    static constexpr V kNotYet = kIdx;  // explicit node whose operation is not decoded yet (full levels)
-};
-
-// Where the levels of one task live.  V: slot type (u16 fast path, u32 big
-// path).  Full grids of levels 0..4 and the compact level 5 are LDS (fast) or
-// scratch (big); level-6 slots are u32 at the voxel position in the output.
-template <typename V>
-struct Store {
-    V* full;          // levels 0..4 at fbase(i)
-    V* c5;            // level-5 explicit nodes by operation rank
-    uint32_t* out6;   // level-6 slot of voxel v: out6[v * lb4]
-    uint32_t lb4;     // label_bytes / 4
-    uint32_t* E;      // bitmaps of levels 0..4 (LDS)
-    uint16_t* wpre;
-    uint32_t* E5;     // bitmap of level 5 (scratch; 64^3 bricks at full resolution)
-    uint16_t* wpre5;
-    uint16_t* list_l;  // parents of the level being decoded, LDS (levels 1..5 on the fast path)
-    uint16_t* list_g;  // the same in scratch (level 6, big path)
-    uint32_t* pval_g;  // values of level-6 parents (scratch)
-
-    // expansion bit / rank among the expanding nodes of a level: levels 0..4 in LDS ...
-    __device__ __forceinline__ bool ebit(uint32_t lvl, uint32_t q) const {
-        return (E[ebase(lvl) + (q >> 5)] >> (q & 31)) & 1u;
-    }
-    __device__ __forceinline__ uint32_t rank(uint32_t lvl, uint32_t q) const {
-        const uint32_t w = E[ebase(lvl) + (q >> 5)];
-        return wpre[ebase(lvl) + (q >> 5)] + (uint32_t)__popc(w & ((1u << (q & 31)) - 1u));
-    }
-    // ... and level 5 in scratch
-    __device__ __forceinline__ bool ebit5(uint32_t q) const { return (E5[q >> 5] >> (q & 31)) & 1u; }
-    __device__ __forceinline__ uint32_t rank5(uint32_t q) const {
-        return wpre5[q >> 5] + (uint32_t)__popc(E5[q >> 5] & ((1u << (q & 31)) - 1u));
-    }
-    // value of a level-5 node (levels 0..5 final)
-    __device__ __forceinline__ uint32_t value5(uint32_t node) const {
-        const uint32_t q = node >> 3;
-        if (ebit(4, q)) return c5[8 * rank(4, q) + (node & 7)];
-        return full[fbase(4) + q];
-    }
-};
-
-// voxel index (z*64 + y)*64 + x of a level-6 Morton index
-__device__ __forceinline__ uint32_t vox6(uint32_t p) {
-    return (compact3(p >> 2) << 12) | (compact3(p >> 1) << 6) | compact3(p);
-}
-
-// ------------------------------------------------------------ level set-up
-// Expanding parents of level i (the nodes of level pl = i - 1 whose bit is set
-// in its bitmap), in two steps.  level_prefix (wavefront 0): exclusive
-// popcount prefix of the bitmap's words, each lane summing a run of
-// consecutive words, and the number of expanding parents in sh.nexp.
-// level_fill (all threads of the level): the list of their node indices by
-// rank and, for a full level i, the children's initial slots; the bitmap of
-// level i is cleared when level i has children.
-template <typename V, bool PL5>
-__device__ __forceinline__ void level_prefix(Shared& sh, const Store<V>& st, uint32_t pl) {
-    const uint32_t lane = lane_id(), pn = 1u << (3 * pl), pw = ewords(pl);
-    const uint32_t mask = pn < 32 ? (1u << pn) - 1u : 0xFFFFFFFFu;
-    const uint32_t* const Ep = PL5 ? st.E5 : st.E + ebase(pl);
-    uint16_t* const Wp = PL5 ? st.wpre5 : st.wpre + ebase(pl);
-    const uint32_t per = (pw + 63u) / 64u, w0 = lane * per;
-    uint32_t sum = 0;
-    for (uint32_t q = 0; q < per; ++q)
-        if (w0 + q < pw) sum += (uint32_t)__popc(Ep[w0 + q] & mask);
-    const uint32_t incl = wave_incl_sum(sum);
-    uint32_t run = incl - sum;
-    for (uint32_t q = 0; q < per; ++q)
-        if (w0 + q < pw) {
-            Wp[w0 + q] = (uint16_t)run;
-            run += (uint32_t)__popc(Ep[w0 + q] & mask);
-        }
-    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-    if (lane == 0) sh.nexp = total;
-}
-
-template <int NT, typename V, bool BIG, bool LIST_LDS, bool PL5>
-__device__ __forceinline__ void level_fill(Shared& sh, const Store<V>& st, uint32_t i, uint32_t t) {
-    const uint32_t tid = threadIdx.x & (NT - 1);  // (NT = 64: the calling wavefront's lane)
-    const uint32_t pl = i - 1, pn = 1u << (3 * pl);
-    const uint32_t* const Ep = PL5 ? st.E5 : st.E + ebase(pl);
-    const uint16_t* const Wp = PL5 ? st.wpre5 : st.wpre + ebase(pl);
-    constexpr V NOTYET = Slot<V>::kNotYet;
-    for (uint32_t q = tid; q < pn; q += NT) {
-        const uint32_t bits = Ep[q >> 5] & (pn < 32 ? (1u << pn) - 1u : 0xFFFFFFFFu);
-        const bool ex = (bits >> (q & 31)) & 1u;
-        if (ex) {
-            const uint32_t r = Wp[q >> 5] + (uint32_t)__popc(bits & ((1u << (q & 31)) - 1u));
-            if (LIST_LDS) {
-                st.list_l[r] = (uint16_t)q;
-            } else {
-                st.list_g[r] = (uint16_t)q;
-                if (PL5) st.pval_g[r] = st.value5(q);
-            }
-        }
-        if (!PL5 && i <= 4) {
-            const V v = ex ? NOTYET : st.full[fbase(pl) + q];
-            V* d = st.full + fbase(i) + 8 * q;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) d[c] = v;
-        }
-    }
-    if (i < t) {
-        if (i <= 4) {
-            for (uint32_t w = tid; w < ewords(i); w += NT) st.E[ebase(i) + w] = 0;
-        } else {
-            for (uint32_t w = tid; w < ewords(5); w += NT) st.E5[w] = 0;
-        }
-    }
-    lsync<NT>();
-}
-
-// ------------------------------------------------------------ level passes
-// 2-state automaton summary of a run of symbols for both entry states: f (bit
-// e = exit state when entered in state e), and per entry state e the number of
-// operations | the number of PALETTE_ADV operations << 16 (p0, p1).  A pass
-// holds at most 8 symbols per thread, so both counts stay below 2^16.
-struct RunSum {
-    uint32_t f, p0, p1;
-};
-constexpr uint32_t kHalf = 0xFFFFu;
-
-// the run `y` after the run `x`
-__device__ __forceinline__ RunSum run_then(const RunSum& x, const RunSum& y) {
-    RunSum r;
-    r.f = fn_then(x.f, y.f);
-    r.p0 = x.p0 + ((x.f & 1u) ? y.p1 : y.p0);
-    r.p1 = x.p1 + ((x.f & 2u) ? y.p1 : y.p0);
-    return r;
-}
-
-template <int CTRL, int ROWS = 0xF>
-__device__ __forceinline__ RunSum dpp_run(const RunSum& x) {
-    return RunSum{dpp<CTRL, ROWS>(kFnId, x.f), dpp<CTRL, ROWS>(0u, x.p0), dpp<CTRL, ROWS>(0u, x.p1)};
-}
-
-// bit 4q set where nibble q of lo3 (nibbles of 3 bits) equals c (c given in every nibble)
-__device__ __forceinline__ uint32_t nib_eq(uint32_t lo3, uint32_t c) {
-    const uint32_t t = lo3 ^ c;
-    return ~(t | (t >> 1) | (t >> 2)) & 0x11111111u;
-}
-
-// inclusive scan of run summaries over the wavefront (lane 0 first)
-__device__ __forceinline__ RunSum wave_scan_run(RunSum x) {
-    x = run_then(dpp_run<kDppRowShr + 1>(x), x);
-    x = run_then(dpp_run<kDppRowShr + 2>(x), x);
-    x = run_then(dpp_run<kDppRowShr + 4>(x), x);
-    x = run_then(dpp_run<kDppRowShr + 8>(x), x);
-    x = run_then(dpp_run<kDppBcast15, 0xA>(x), x);
-    x = run_then(dpp_run<kDppBcast31, 0xC>(x), x);
-    return x;
-}
-
-// KIND 0: full level (i <= 4), 1: compact level 5, 2: level 6 in the output.
-//
-// A pass gives every thread R consecutive symbols (R = 1, 2, 4 or 8 per level:
-// the fewest that still fill one pass, so small levels do not serialise).
-// Each thread summarises its R symbols for both automaton entry states; a
-// wavefront scan and a scan of the waves' totals give each thread its entry
-// state, its first operation rank and its first palette (ADV) rank; then each
-// thread decodes its own operations in order.  References to nodes decoded in
-// the same pass are resolved after it.
-template <int NT, int KIND, typename V, bool BIG, bool LIST_LDS>
-__device__ __forceinline__ void level_passes(const Params& P, Shared& sh, const Store<V>& st, const uint8_t* nib, uint32_t i,
-                             uint32_t expected, uint32_t& adv_done, uint32_t& pbuf) {
-    constexpr uint32_t NW = NT / 64;
-    const uint32_t tid = threadIdx.x & (NT - 1), lane = lane_id(), wave = tid >> 6;
-    const uint32_t t = sh.h.t, pc = sh.h.pc;
-    const uint32_t nodes = 1u << (3 * i);
-    // final flag of this level's slots (level 6 slots are always u32)
-    constexpr uint32_t FIN = KIND == 2 ? 0x80000000u : (uint32_t)Slot<V>::kFinal;
-    constexpr uint32_t IDX = FIN - 1u;
-    constexpr uint32_t VIDX = (uint32_t)Slot<V>::kIdx;
-    V* const full_i = st.full + (KIND == 0 ? fbase(i) : 0u);
-    const V* const full_p = st.full + (i ? fbase(i <= 5 ? i - 1 : 4) : 0u);
-    // expansion bits of this level (needed when t > i): LDS for full levels, scratch for level 5
-    uint32_t* const Ei_l = KIND == 0 && i < t ? st.E + ebase(i) : nullptr;
-    uint32_t* const Ei_g = KIND == 1 && i < t ? st.E5 : nullptr;
-    const uint32_t mx = 0x09249249u & (nodes - 1u), my = mx << 1, mz = mx << 2;
-    const uint32_t s0 = i ? sh.h.sym_end[i - 1] : 0u, s1 = sh.h.sym_end[i];
-    const uint32_t* const nib32 = (const uint32_t*)nib;
-    const uint32_t n_sym = s1 - s0;
-    const uint32_t lr = n_sym <= NT ? 0u : n_sym <= 2u * NT ? 1u : n_sym <= 4u * NT ? 2u : 3u;  // log2 R
-    const uint32_t g_first = s0 >> lr, g_last = n_sym ? (s1 - 1u) >> lr : 0u;
-    const uint32_t n_groups = n_sym ? g_last - g_first + 1u : 0u;
-    const uint32_t w_last = n_sym ? (s1 - 1u) >> 3 : 0u;  // last word holding a symbol of the level
-    // slot of the operation of rank k whose node is p
-    auto slot_of = [&](uint32_t k, uint32_t p) -> uint32_t { return KIND == 0 ? p : KIND == 1 ? k : vox6(p); };
-    auto parent_of = [&](uint32_t k) -> uint32_t {
-        return i ? (LIST_LDS ? (uint32_t)st.list_l[k >> 3] : (uint32_t)st.list_g[k >> 3]) : 0u;
-    };
-    auto read_slot = [&](uint32_t x) -> uint32_t {
-        return KIND == 0 ? (uint32_t)full_i[x] : KIND == 1 ? (uint32_t)st.c5[x] : st.out6[(uint64_t)x * st.lb4];
-    };
-    auto write_slot = [&](uint32_t x, uint32_t v) {
-        if (KIND == 0) full_i[x] = (V)v;
-        else if (KIND == 1) st.c5[x] = (V)v;
-        else st.out6[(uint64_t)x * st.lb4] = v;
-    };
-    uint32_t carry = 0, k_done = 0;
-    bool bad = false;
-    // each thread reads the two words holding its group of R symbols and what
-    // follows it (delta entries), one pass ahead, at clamped indices: no branch
-    // around the loads, so nothing waits for them before their use
-    uint32_t nlo = 0, nhi = 0;
-    if (n_groups) {
-        const uint32_t w = ((g_first + tid) << lr) >> 3;
-        nlo = nib32[min(w, w_last)];
-        nhi = nib32[min(w + 1u, w_last)];
-    }
-    for (uint32_t pg = 0; pg < n_groups; pg += NT) {
-        const uint32_t g = g_first + pg + tid, j0 = g << lr, pb = pbuf;
-        // symbols j0, j0 + 1, ... from bit 0 on (16 - (j0 & 7) of them)
-        const uint64_t win = ((((uint64_t)nhi) << 32) | nlo) >> (4u * (j0 & 7u));
-        const uint32_t word = (uint32_t)win, avail = 16u - (j0 & 7u);
-        {
-            const uint32_t w = ((g + NT) << lr) >> 3;
-            nlo = nib32[min(w, w_last)];
-            nhi = nib32[min(w + 1u, w_last)];
-        }
-        // Masks over the thread's symbols, bit 4q for symbol j0 + q ("nibble
-        // masks"): V4 the symbols of this group that belong to the level
-        uint32_t V4 = 0;
-        if (g <= g_last) {
-            const uint32_t lo = s0 > j0 ? s0 - j0 : 0u, hi = min(s1 - j0, 1u << lr);
-            V4 = (hi >= 8u ? 0xFFFFFFFFu : (1u << (4u * hi)) - 1u) & ~((1u << (4u * lo)) - 1u) & 0x11111111u;
-        }
-        const uint32_t lo3 = word & 0x77777777u, C4 = (word >> 3) & 0x11111111u;
-        // the automaton state before each symbol for entry state 0 (S0) and 1 (S1):
-        // state 1 = inside a delta chain (the symbol is a delta entry)
-        uint32_t S0 = 0, S1 = 0;
-        // a wave holding no symbol of the level skips its summary, scan and decode
-        // (it still takes part in the barriers and the waves' scan)
-        const bool wave_on = g_first + pg + 64u * wave <= g_last;
-        RunSum incl{kFnId, 0u, 0u}, excl{kFnId, 0u, 0u};
-        if (wave_on) {
-            // a symbol outside the level keeps the state: DELTA code off, continuation on
-            const uint32_t Dv = nib_eq(lo3, 0x66666666u) & V4, Cv = C4 | (~V4 & 0x11111111u);
-            uint32_t e0 = 0, e1 = 1;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const uint32_t d = (Dv >> (4 * q)) & 1u, c = (Cv >> (4 * q)) & 1u;
-                S0 |= e0 << (4 * q);
-                S1 |= e1 << (4 * q);
-                e0 = e0 ? c : d;
-                e1 = e1 ? c : d;
-            }
-            const uint32_t A4 = nib_eq(lo3, 0x44444444u), O0 = V4 & ~S0, O1 = V4 & ~S1;
-            const RunSum x{e0 | (e1 << 1), (uint32_t)__popc(O0) | ((uint32_t)__popc(O0 & A4) << 16),
-                           (uint32_t)__popc(O1) | ((uint32_t)__popc(O1 & A4) << 16)};
-            incl = wave_scan_run(x);
-            excl = dpp_run<kDppWaveShr1>(incl);
-        }
-        // this wave's entry state and packed operation / ADV bases for both entry
-        // states (wf, wp0, wp1), and the pass totals (tf, tp0, tp1): one wavefront
-        // has them from its own scan
-        uint32_t wf = kFnId, wp0 = 0, wp1 = 0, tf, tp0, tp1;
-        if (NW == 1) {
-            tf = (uint32_t)__builtin_amdgcn_readlane((int)incl.f, 63);
-            tp0 = (uint32_t)__builtin_amdgcn_readlane((int)incl.p0, 63);
-            tp1 = (uint32_t)__builtin_amdgcn_readlane((int)incl.p1, 63);
-        } else {
-            if (lane == 63) {
-                uint32_t* pub = sh.pub[pb][wave];
-                pub[0] = incl.f;
-                pub[1] = incl.p0;
-                pub[2] = incl.p1;
-            }
-            lsync<NT>();
-            // the waves' totals, scanned over the first NW lanes (one row of 16)
-            RunSum wt{kFnId, 0u, 0u};
-            if (lane < NW) wt = RunSum{sh.pub[pb][lane][0], sh.pub[pb][lane][1], sh.pub[pb][lane][2]};
-            wt = run_then(dpp_run<kDppRowShr + 1>(wt), wt);
-            wt = run_then(dpp_run<kDppRowShr + 2>(wt), wt);
-            wt = run_then(dpp_run<kDppRowShr + 4>(wt), wt);
-            wt = run_then(dpp_run<kDppRowShr + 8>(wt), wt);
-            const RunSum we = dpp_run<kDppRowShr + 1>(wt);
-            wf = (uint32_t)__builtin_amdgcn_readlane((int)we.f, (int)wave);
-            wp0 = (uint32_t)__builtin_amdgcn_readlane((int)we.p0, (int)wave);
-            wp1 = (uint32_t)__builtin_amdgcn_readlane((int)we.p1, (int)wave);
-            tf = (uint32_t)__builtin_amdgcn_readlane((int)wt.f, (int)(NW - 1));
-            tp0 = (uint32_t)__builtin_amdgcn_readlane((int)wt.p0, (int)(NW - 1));
-            tp1 = (uint32_t)__builtin_amdgcn_readlane((int)wt.p1, (int)(NW - 1));
-        }
-        const uint32_t my_e = (wf >> carry) & 1u;
-        const uint32_t wp = carry ? wp1 : wp0, tp = carry ? tp1 : tp0;
-        const uint32_t my_kb = k_done + (wp & kHalf);
-        const uint32_t my_ab = adv_done + (wp >> 16);
-        const uint32_t k0 = k_done;
-        k_done += tp & kHalf;
-        adv_done += tp >> 16;
-        carry = (tf >> carry) & 1u;
-        pbuf ^= 1u;
-        const uint32_t ls = (excl.f >> my_e) & 1u;
-        // this thread's first operation rank and first ADV rank
-        const uint32_t lp = my_e ? excl.p1 : excl.p0;
-        const uint32_t k_first = my_kb + (lp & kHalf);
-        const uint32_t a_first = my_ab + (lp >> 16);
-        uint32_t opm = 0, refm = 0;
-        if (wave_on) {
-            // classify the thread's symbols from its entry state (nibble masks):
-            // operations, and among them ADVs, palette (ADV, LAST, DELTA, invalid code:
-            // bit 2 of the code), parent and neighbour operations, and stop bits; each
-            // kind is then decoded in a loop of its own, so a wavefront runs one kind's
-            // code at a time
-            opm = V4 & ~(ls ? S1 : S0);
-            const uint32_t advm = opm & nib_eq(lo3, 0x44444444u);
-            uint32_t palm = opm & (word >> 2) & 0x11111111u;
-            uint32_t parm = opm & nib_eq(lo3, 0u);
-            uint32_t nbm = opm & ~palm & ~parm;
-            uint32_t stopm = opm & C4;
-            // operations past the level's node count are an error and write nothing
-            if (k_first + (uint32_t)__popc(opm) > expected) {
-                bad = true;
-                uint32_t keep = expected > k_first ? expected - k_first : 0u, km = 0;
-                for (uint32_t m = opm; m && keep; m &= m - 1u, --keep) km |= m & (0u - m);
-                palm &= km;
-                parm &= km;
-                nbm &= km;
-                stopm |= ~km;
-            }
-            // rank of the operation at bit position b = 4q, its ADV rank, and its node
-            auto k_at = [&](uint32_t b) -> uint32_t { return k_first + (uint32_t)__popc(opm & ((1u << b) - 1u)); };
-            auto a_at = [&](uint32_t b) -> uint32_t { return a_first + (uint32_t)__popc(advm & ((1u << b) - 1u)); };
-            auto node_of = [&](uint32_t kq) -> uint32_t { return i ? ((parent_of(kq) << 3) | (kq & 7u)) : 0u; };
-            // palette: ADV -> a, LAST -> a - 1, DELTA -> a - delta, the entries following in the window
-            for (uint32_t m = palm; m; m &= m - 1u) {
-                const uint32_t b = (uint32_t)__builtin_ctz(m), q = b >> 2, kq = k_at(b), aq = a_at(b);
-                const uint32_t op = (word >> b) & 7u;
-                uint32_t v = FIN;
-                bool err = false;
-                if (op == kAdv) {
-                    if (aq >= pc) err = true;
-                    else v = FIN | aq;
-                } else if (op == kLast) {
-                    if (aq == 0) err = true;
-                    else v = FIN | (aq - 1u);
-                } else if (op == kDelta) {
-                    uint32_t d = 0, mm = q + 1u, en = 8;
-                    while (en & 8u) {
-                        const uint32_t jj = j0 + mm;
-                        if (jj >= s1) {
-                            err = true;
-                            break;
-                        }
-                        en = mm < avail ? (uint32_t)(win >> (4 * mm)) & 15u : (nib[jj >> 1] >> (4 * (jj & 1))) & 15u;
-                        d = d >= (1u << 29) ? 0xFFFFFFFFu : ((d << 3) | (en & 7u));
-                        ++mm;
-                    }
-                    if (!err) {
-                        if (d == 0 || d > aq) err = true;
-                        else v = FIN | (aq - d);
-                    }
-                } else {
-                    err = true;
-                }
-                if (err) {
-                    bad = true;
-                    v = FIN;
-                }
-                // written even after an error, so that a later lookup never meets an unset slot
-                write_slot(slot_of(kq, KIND == 1 ? 0u : node_of(kq)), v);
-            }
-            // parent copies
-            for (uint32_t m = parm; m; m &= m - 1u) {
-                const uint32_t kq = k_at((uint32_t)__builtin_ctz(m));
-                const uint32_t pn = parent_of(kq);
-                uint32_t v = FIN;
-                if (i == 0) bad = true;
-                else if (KIND == 2) v = (st.pval_g[kq >> 3] & VIDX) | FIN;
-                else v = full_p[pn];
-                write_slot(slot_of(kq, i ? ((pn << 3) | (kq & 7u)) : 0u), v);
-            }
-            // neighbour copies: an implied target holds its parent's value, an explicit one of
-            // an earlier pass its final value, one of this pass becomes a reference
-            for (uint32_t m = nbm; m; m &= m - 1u) {
-                const uint32_t b = (uint32_t)__builtin_ctz(m), kq = k_at(b);
-                const uint32_t op = (word >> b) & 7u;
-                const uint32_t p = node_of(kq);
-                const uint32_t am = mx << ((op - 1u) & 3u);  // NX, NY, NZ: the x, y or z bits
-                uint32_t v = FIN;
-                if (KIND == 1) {
-                    // level 5 without branches: the target's implied value (its level-4
-                    // parent's) and its explicit slot are both read, then selected; a
-                    // node at coordinate 0 (no neighbour) reads in-range garbage
-                    const uint32_t pa = p & am;
-                    const uint32_t tn = ((pa - 1u) & am) | (p & ~am), tq = tn >> 3;
-                    const uint32_t ew = st.E[ebase(4) + (tq >> 5)];
-                    const uint32_t kt = 8u * (st.wpre[ebase(4) + (tq >> 5)] +
-                                              (uint32_t)__popc(ew & ((1u << (tq & 31)) - 1u))) + (tn & 7u);
-                    const uint32_t implied = full_p[tq], got = st.c5[kt < k0 ? kt : 0u];
-                    v = !pa ? FIN : !((ew >> (tq & 31)) & 1u) ? implied : kt < k0 ? got : kt;
-                    bad = bad || !pa;
-                    refm |= (v & FIN) ? 0u : (1u << b);
-                } else if (!(p & am)) {
-                    bad = true;
-                } else {
-                    const uint32_t tn = (((p & am) - 1u) & am) | (p & ~am);
-                    if (KIND == 0) {
-                        v = full_i[tn];
-                        if (v == (uint32_t)Slot<V>::kNotYet) v = tn;
-                    } else {
-                        const uint32_t tq = tn >> 3;
-                        if (KIND == 1 ? !st.ebit(4, tq) : !st.ebit5(tq)) {
-                            v = KIND == 1 ? (uint32_t)full_p[tq] : ((st.value5(tq) & VIDX) | FIN);
-                        } else {
-                            const uint32_t kt = 8 * (KIND == 1 ? st.rank(4, tq) : st.rank5(tq)) + (tn & 7u);
-                            const uint32_t ti = KIND == 1 ? kt : vox6(tn);
-                            v = kt < k0 ? read_slot(ti) : ti;
-                        }
-                    }
-                    refm |= (v & FIN) ? 0u : (1u << b);
-                }
-                write_slot(slot_of(kq, p), v);
-            }
-            // expansion bits of this level's operations without a stop bit
-            if (Ei_l || Ei_g) {
-                for (uint32_t m = opm & ~stopm; m; m &= m - 1u) {
-                    const uint32_t p = node_of(k_at((uint32_t)__builtin_ctz(m)));
-                    if (Ei_l) atomicOr(Ei_l + (p >> 5), 1u << (p & 31));
-                    if (Ei_g) atomicOr(Ei_g + (p >> 5), 1u << (p & 31));
-                }
-            }
-        }
-        lsync<NT>();
-        // references within the pass: chase to a final value (targets precede
-        // their sources, so every chain ends within the pass's operations)
-        for (uint32_t m = refm; m; m &= m - 1u) {
-            const uint32_t b = (uint32_t)__builtin_ctz(m);
-            const uint32_t kq = k_first + (uint32_t)__popc(opm & ((1u << b) - 1u));
-            const uint32_t pq = i ? ((parent_of(kq) << 3) | (kq & 7u)) : 0u;
-            const uint32_t me = slot_of(kq, pq);
-            const uint32_t lim = KIND == 0 ? nodes : KIND == 1 ? k_done : (1u << 18);
-            uint32_t v = read_slot(me), it = 0;
-            while (!(v & FIN)) {
-                if ((v & IDX) >= lim || ++it > 8 * NT) {
-                    bad = true;
-                    v = FIN;
-                    break;
-                }
-                v = read_slot(v & IDX);
-            }
-            write_slot(me, v);
-        }
-    }
-    if (bad) atomicOr(&sh.err, 1u);
-    if ((k_done != expected || carry != 0) && tid == 0) sh.err = 1u;
-}
-
-// Levels 0..min(t, last) (last = 2: at most 73 nodes; 3: 585) decoded by the
-// calling wavefront alone, with wave barriers; then the parent prefix of the
-// next level when the cube has one, and the ADV count in sh.adv.
-template <typename V, bool BIG, bool LIST_LDS>
-__device__ __forceinline__ void small_levels(const Params& P, Shared& sh, const Store<V>& st, const uint8_t* nib,
-                                             uint32_t last) {
-    const uint32_t t = sh.h.t, tw = t < last ? t : last, lane = lane_id();
-    uint32_t adv_done = 0, pbuf = 0;
-    for (uint32_t i = 0; i <= tw; ++i) {
-        uint32_t expected = 1;
-        if (i == 0) {
-            // Level 0 is one node whose only valid operation is PALETTE_ADV (entry
-            // 0), with or without a stop bit: take that case directly; anything
-            // else goes through the general pass, which reports the error.
-            const uint32_t s0 = nib[0] & 15u;
-            if (sh.h.sym_end[0] == 1u && (s0 & 7u) == kAdv && sh.h.pc > 0u) {
-                if (lane == 0) {
-                    st.full[fbase(0)] = (V)Slot<V>::kFinal;
-                    if (t > 0) st.E[ebase(0)] = (s0 & 8u) ? 0u : 1u;
-                }
-                adv_done = 1;
-                lsync<64>();
-                continue;
-            }
-            if (t > 0 && lane == 0) st.E[ebase(0)] = 0;
-            lsync<64>();
-        } else {
-            level_prefix<V, false>(sh, st, i - 1);
-            lsync<64>();
-            expected = 8 * sh.nexp;
-            level_fill<64, V, BIG, LIST_LDS, false>(sh, st, i, t);
-        }
-        level_passes<64, 0, V, BIG, LIST_LDS>(P, sh, st, nib, i, expected, adv_done, pbuf);
-        lsync<64>();
-        if (sh.err) break;
-    }
-    if (!sh.err && t > tw) level_prefix<V, false>(sh, st, tw);
-    if (lane == 0) sh.adv = adv_done;
-}
-
-// Decode levels 0..t; on return all slots of level t are final unless sh.err.
-// Levels 0..2 are decoded by one wavefront (wavefront 0 here; with `small_upto`
-// >= 0, levels 0..min(t, small_upto) were decoded during the rANS decode), the
-// other wavefronts wait at the work-group barrier that follows.  From then on,
-// all threads decode; wavefront 0 computes the next level's parent prefix after
-// a level's last pass, before the barrier that ends it.
-template <int NT, typename V, bool BIG, bool LIST_LDS>
-__device__ __forceinline__ void decode_levels(const Params& P, Shared& sh, const Store<V>& st, const uint8_t* nib,
-                                              Ahead& ah, int small_upto) {
-    const uint32_t t = sh.h.t, wave = threadIdx.x >> 6;
-    const uint32_t last = small_upto < 0 ? 2u : (uint32_t)small_upto;
-    const uint32_t tw = t < last ? t : last;  // last level of the single wavefront
-    if (small_upto < 0) {
-        if (wave == 0) {
-            small_levels<V, BIG, LIST_LDS>(P, sh, st, nib, 2u);
-        } else if (threadIdx.x == NT - 64 && !ah.done) {
-            parse_ahead(P, sh.hn, ah.jt);
-            ah.done = true;
-        }
-        __syncthreads();
-    }
-    if (sh.err) return;
-    uint32_t adv_done = sh.adv, pbuf = 0;
-    for (uint32_t i = tw + 1; i <= t; ++i) {
-        const uint32_t expected = 8 * sh.nexp;
-        if (i <= 5) level_fill<NT, V, BIG, LIST_LDS, false>(sh, st, i, t);
-        else level_fill<NT, V, BIG, false, true>(sh, st, i, t);
-        if (i <= 4) level_passes<NT, 0, V, BIG, LIST_LDS>(P, sh, st, nib, i, expected, adv_done, pbuf);
-        else if (i == 5) level_passes<NT, 1, V, BIG, LIST_LDS>(P, sh, st, nib, i, expected, adv_done, pbuf);
-        else level_passes<NT, 2, V, BIG, false>(P, sh, st, nib, i, expected, adv_done, pbuf);
-        // the level's bitmap is final after its last pass: the next level's parent prefix
-        if (i < t && wave == 0) {
-            if (i == 5) level_prefix<V, true>(sh, st, i);
-            else level_prefix<V, false>(sh, st, i);
-        }
-        __syncthreads();
-        if (sh.err) return;
-    }
-    if (t == sh.h.L && adv_done != sh.h.pc && threadIdx.x == 0) sh.err = 1u;
-    __syncthreads();
-}
-
 // ------------------------------------------------------------------ output
 // Decoded labels are written once and not read again by the kernel: vector
 // stores carry the non-temporal hint, so they do not displace the records and
@@ -1004,26 +425,38 @@ __device__ __forceinline__ void st16_nt(void* p, uint4 v) {
     __builtin_nontemporal_store(w, (u32x4*)p);
 }
 
-template <typename LT>
+template <typename LT, bool NT_HINT = true>
 __device__ __forceinline__ void store4(LT* o, LT a, LT b, LT c, LT d, bool vec) {
+    if (!vec) {
+        o[0] = a;
+        o[1] = b;
+        o[2] = c;
+        o[3] = d;
+        return;
+    }
+    uint4 w[sizeof(LT) / 4];
     if (sizeof(LT) == 4) {
-        if (vec) st16_nt(o, make_uint4((uint32_t)a, (uint32_t)b, (uint32_t)c, (uint32_t)d));
-        else {
-            o[0] = a;
-            o[1] = b;
-            o[2] = c;
-            o[3] = d;
-        }
+        w[0] = make_uint4((uint32_t)a, (uint32_t)b, (uint32_t)c, (uint32_t)d);
     } else {
-        if (vec) {
-            st16_nt((uint4*)o, make_uint4((uint32_t)a, (uint32_t)((uint64_t)a >> 32), (uint32_t)b, (uint32_t)((uint64_t)b >> 32)));
-            st16_nt((uint4*)o + 1, make_uint4((uint32_t)c, (uint32_t)((uint64_t)c >> 32), (uint32_t)d, (uint32_t)((uint64_t)d >> 32)));
-        } else {
-            o[0] = a;
-            o[1] = b;
-            o[2] = c;
-            o[3] = d;
-        }
+        w[0] = make_uint4((uint32_t)a, (uint32_t)((uint64_t)a >> 32), (uint32_t)b, (uint32_t)((uint64_t)b >> 32));
+        w[sizeof(LT) / 4 - 1] = make_uint4((uint32_t)c, (uint32_t)((uint64_t)c >> 32), (uint32_t)d, (uint32_t)((uint64_t)d >> 32));
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(LT) / 4; ++k) {
+        if (NT_HINT) st16_nt((uint4*)o + k, w[k]);
+        else ((uint4*)o)[k] = w[k];
+    }
+}
+
+template <typename LT>
+__device__ __forceinline__ void store2(LT* o, LT a, LT b, bool vec) {
+    if (!vec) {
+        o[0] = a;
+        o[1] = b;
+    } else if (sizeof(LT) == 4) {
+        *(uint2*)o = make_uint2((uint32_t)a, (uint32_t)b);
+    } else {
+        *(uint4*)o = make_uint4((uint32_t)a, (uint32_t)((uint64_t)a >> 32), (uint32_t)b, (uint32_t)((uint64_t)b >> 32));
     }
 }
 
@@ -1040,25 +473,733 @@ __device__ __forceinline__ void zero_output(const Params& P, const TaskHdr& h) {
     }
 }
 
-// Labels of level t (all slots final) as an S^3 x-fastest cube.  Full levels
-// voxel by voxel (4 per thread); levels 5 and 6 by pairs of 2x2x2 blocks
-// along x under two level-(t-1) nodes: a node that does not expand gives its
-// value to its 8 children, an expanding one has 8 explicit children.
-template <int NT, typename V, typename LT, bool PAL_LDS>
-__device__ __forceinline__ void write_labels(const Params& P, Shared& sh, const Store<V>& st) {
+// ------------------------------------------------------------ level bitmaps
+// Expansion bits of levels 0..4, one entry per 32 nodes: x the bits, y the
+// number of expanding nodes before the word (level_prefix).  A 64^3 brick keeps
+// level 5 the same way in the slot area.
+__device__ __forceinline__ bool ep_bit(uint2 e, uint32_t q) { return (e.x >> (q & 31)) & 1u; }
+__device__ __forceinline__ uint32_t ep_rank(uint2 e, uint32_t q) {
+    return e.y + (uint32_t)__popc(e.x & ((1u << (q & 31)) - 1u));
+}
+
+// Exclusive popcount prefix of the words of one level's bitmap (one wavefront;
+// each lane takes a run of words); returns the number of expanding nodes.
+__device__ __forceinline__ uint32_t level_prefix(uint2* ep, uint32_t words) {
+    const uint32_t lane = lane_id(), per = (words + 63u) / 64u, w0 = lane * per;
+    uint32_t sum = 0;
+    for (uint32_t q = 0; q < per; ++q)
+        if (w0 + q < words) sum += (uint32_t)__popc(ep[w0 + q].x);
+    const uint32_t incl = wave_incl_sum(sum);
+    uint32_t run = incl - sum;
+    for (uint32_t q = 0; q < per; ++q)
+        if (w0 + q < words) {
+            const uint32_t bits = ep[w0 + q].x;
+            ep[w0 + q].y = run;
+            run += (uint32_t)__popc(bits);
+        }
+    return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+}
+
+// ------------------------------------------------------ symbols to operations
+// A symbol is an operation or a 4-bit entry of the delta chain before it: a
+// 2-state automaton (state 1 = the symbol is an entry).  A symbol's effect on
+// the state depends on its code and bit 3 alone:
+//   DELTA code, bit 3 set      -> 1         DELTA code, bit 3 clear -> inverted
+//   other code, bit 3 clear    -> 0         other code, bit 3 set   -> kept
+// With the inversions taken out by a parity prefix, what is left is a carry
+// chain (generate, kill, propagate), so one addition gives the state before
+// each of a word's 8 symbols: nibble q of A is 15 where the symbol generates
+// or propagates, bit 4q of B is 1 where it generates, and the carry into nibble
+// q is the state before symbol q (up to the parity).
+constexpr uint32_t kNib = 0x11111111u;  // bit 4q <-> symbol q of a word ("nibble mask")
+
+// nibble mask of the symbols whose low 3 bits equal c (c given in every nibble)
+__device__ __forceinline__ uint32_t nib_eq(uint32_t lo3, uint32_t c) {
+    const uint32_t t = lo3 ^ c;
+    return ~(t | (t >> 1) | (t >> 2)) & kNib;
+}
+
+struct WordRun {
+    uint32_t A, B, par;  // carry chain; inclusive parity of the inversions
+    // nibble mask of the symbols that are delta entries when the word is entered in state e
+    __device__ __forceinline__ uint32_t entries(uint32_t e) const { return (((A + B + e) ^ A ^ B) & kNib) ^ (par << 4); }
+    __device__ __forceinline__ uint32_t exit(uint32_t e) const { return ((A & ~(A + B + e)) >> 31) ^ (par >> 28); }
+};
+
+// V: the symbols of the word that belong to the level; the others keep the state
+__device__ __forceinline__ WordRun word_run(uint32_t word, uint32_t V) {
+    const uint32_t D = nib_eq(word & 0x77777777u, 0x66666666u), C = word >> 3;
+    const uint32_t set = D & C & V, rst = ~(D | C) & V;
+    uint32_t p = D & ~C & V;
+    p ^= p << 4;
+    p ^= p << 8;
+    p ^= p << 16;
+    const uint32_t pg = kNib & ~((set & p) | (rst & ~p));
+    return WordRun{(pg << 4) - pg, (set & ~p) | (rst & p), p};
+}
+
+// nibble mask of the symbols of word w inside [s0, s1)
+__device__ __forceinline__ uint32_t word_valid(uint32_t w, uint32_t s0, uint32_t s1) {
+    const uint32_t j = 8u * w;
+    const uint32_t hi = s1 > j ? min(s1 - j, 8u) : 0u, lo = s0 > j ? min(s0 - j, 8u) : 0u;
+    const uint32_t mh = hi >= 8u ? kNib : ((1u << (4u * hi)) - 1u) & kNib;
+    return lo >= 8u ? 0u : mh & ~((1u << (4u * lo)) - 1u);
+}
+
+__device__ __forceinline__ uint32_t lane_bit(uint64_t m) {
+    const uint32_t l = lane_id();
+    return ((l & 32u ? (uint32_t)(m >> 32) : (uint32_t)m) >> (l & 31u)) & 1u;
+}
+
+// where a level's symbols have been read to
+struct RunState {
+    uint32_t state;  // automaton state
+    uint32_t k;      // operations so far
+    uint32_t adv;    // PALETTE_ADV operations so far, all levels
+};
+
+// slot values: a final palette index, or an operation that copies (its code, 0..3)
+template <bool W32>
+struct SlotBits {
+    static constexpr uint32_t kFinal = W32 ? 0x80000000u : 0x8000u;
+    static constexpr uint32_t kStop = W32 ? 0x40000000u : 0x4000u;
+};
+
+// One pass over words [w_at, w_at + nw) of a level with symbols [s0, s1): every
+// thread takes 1 << lr (at most 4) consecutive words, summarises them for both
+// entry states (operations | ADVs << 16), a wavefront scan and one barrier give
+// it its entry state, its first operation rank k and its ADV count, and it then
+// writes the slot of each of its operations, slot[k - kbase]: palette
+// operations as final indices (ADV -> a, LAST -> a - 1, DELTA -> a - delta),
+// copies as their code; with STOP the stop bit goes along.  False (to every
+// thread, nothing written) when the operations exceed `expected`.  Needs at
+// least one ADV before the pass (level 0 is decoded apart).
+template <int NT, bool W32, bool STOP, typename SLOT>
+__device__ __forceinline__ bool ops_pass(Shared& sh, const uint32_t* sym, uint32_t s0, uint32_t s1, uint32_t w_at,
+                                         uint32_t nw, uint32_t lr, uint32_t expected, uint32_t kbase, SLOT* slot,
+                                         RunState& rs, uint32_t& pbuf, bool& bad) {
+    constexpr uint32_t NW = NT / 64;
+    constexpr uint32_t FIN = SlotBits<W32>::kFinal, STP = SlotBits<W32>::kStop;
+    const uint32_t tid = threadIdx.x & (NT - 1), wave = tid >> 6;
+    const uint32_t w_last = (s1 - 1u) >> 3, w_end = w_at + nw, w0 = w_at + (tid << lr), R = 1u << lr;
+    // the thread's words and the one after them (delta entries), at clamped indices
+    uint32_t W[5];
+    W[0] = sym[min(w0, w_last)];
+    W[1] = sym[min(w0 + 1u, w_last)];
+    if (lr >= 1u) W[2] = sym[min(w0 + 2u, w_last)];
+    if (lr >= 2u) {
+        W[3] = sym[min(w0 + 3u, w_last)];
+        W[4] = sym[min(w0 + 4u, w_last)];
+    }
+    auto valid = [&](uint32_t r) -> uint32_t { return w0 + r < w_end ? word_valid(w0 + r, s0, s1) : 0u; };
+    const bool wave_on = w_at + ((64u * wave) << lr) < w_end;
+    uint32_t n0 = 0, n1 = 0, i0 = 0, i1 = 0, x0 = 0, x1 = 1;  // counts, their scans, the wave's exit states
+    uint64_t m0 = 0, m1 = 0;                                   // the lanes' entry states
+    if (wave_on) {
+        uint32_t e0 = 0, e1 = 1;
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            if (r < R) {
+                const uint32_t V = valid(r), advm = nib_eq(W[r] & 0x77777777u, 0x44444444u);
+                const WordRun wr = word_run(W[r], V);
+                const uint32_t o0 = V & ~wr.entries(e0), o1 = V & ~wr.entries(e1);
+                n0 += (uint32_t)__popc(o0) | ((uint32_t)__popc(o0 & advm) << 16);
+                n1 += (uint32_t)__popc(o1) | ((uint32_t)__popc(o1 & advm) << 16);
+                e0 = wr.exit(e0);
+                e1 = wr.exit(e1);
+            }
+        }
+        // the same carry chain over the lanes, in scalar registers
+        const uint64_t b0 = __ballot(e0 != 0u), b1 = __ballot(e1 != 0u);
+        uint64_t p = b0 & ~b1;  // lanes that invert
+        if (p) {
+            p ^= p << 1;
+            p ^= p << 2;
+            p ^= p << 4;
+            p ^= p << 8;
+            p ^= p << 16;
+            p ^= p << 32;
+        }
+        const uint64_t set = b0 & b1, rst = ~(b0 | b1);
+        const uint64_t B = (set & ~p) | (rst & p), A = (b0 ^ b1) | B;
+        const uint64_t a0 = A + B, a1 = a0 + 1u;
+        m0 = a0 ^ A ^ B ^ (p << 1);
+        m1 = a1 ^ A ^ B ^ (p << 1);
+        x0 = (uint32_t)(((B | (A & ~a0)) ^ p) >> 63);
+        x1 = (uint32_t)(((B | (A & ~a1)) ^ p) >> 63);
+        i0 = wave_incl_sum(lane_bit(m0) ? n1 : n0);
+        i1 = wave_incl_sum(lane_bit(m1) ? n1 : n0);
+    }
+    uint32_t st = rs.state, k = rs.k, adv = rs.adv, my_st = st, my_k = k, my_adv = adv;
+    auto add_run = [&](uint32_t xs, uint32_t t0, uint32_t t1) {
+        const uint32_t tot = st ? t1 : t0;
+        k += tot & 0xFFFFu;
+        adv += tot >> 16;
+        st = (xs >> st) & 1u;
+    };
+    const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)i0, 63);
+    const uint32_t t1 = (uint32_t)__builtin_amdgcn_readlane((int)i1, 63);
+    if (NW == 1) {
+        add_run(x0 | (x1 << 1), t0, t1);
+    } else {
+        if (lane_id() == 0) sh.pub[pbuf][wave] = make_uint4(x0 | (x1 << 1), t0, t1, 0u);
+        __syncthreads();
+#pragma unroll
+        for (uint32_t w = 0; w < NW; ++w) {
+            const uint4 pw = sh.pub[pbuf][w];
+            if (w == wave) {
+                my_st = st;
+                my_k = k;
+                my_adv = adv;
+            }
+            add_run((uint32_t)__builtin_amdgcn_readfirstlane((int)pw.x), (uint32_t)__builtin_amdgcn_readfirstlane((int)pw.y),
+                    (uint32_t)__builtin_amdgcn_readfirstlane((int)pw.z));
+        }
+        pbuf ^= 1u;
+    }
+    rs = RunState{st, k, adv};
+    if (k > expected) return false;
+    if (!wave_on) return true;
+    uint32_t e = lane_bit(my_st ? m1 : m0);
+    const uint32_t excl = (my_st ? i1 : i0) - (e ? n1 : n0);
+    uint32_t kk = my_k - kbase + (excl & 0xFFFFu), aa = my_adv + (excl >> 16);
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint32_t word = W[0], V = valid(r), lo3 = word & 0x77777777u;
+        const WordRun wr = word_run(word, V);
+        const uint32_t opm = V & ~wr.entries(e), advm = opm & nib_eq(lo3, 0x44444444u);
+        e = wr.exit(e);
+        bad = bad || (opm & nib_eq(lo3, 0x77777777u));
+        uint32_t kq = kk, aq = aa;
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) {
+            if ((opm >> (4 * q)) & 1u) {
+                const uint32_t op = (word >> (4 * q)) & 7u;
+                uint32_t v = op < 4u ? op : FIN | (aq - min(op - 4u, 1u));  // (back references: below)
+                if (STOP) v |= ((word >> (4 * q + 3)) & 1u) ? STP : 0u;
+                slot[kq] = (SLOT)v;
+                kq += 1u;
+                aq += (advm >> (4 * q)) & 1u;
+            }
+        }
+        // back references: the entries that follow, in the word, the next word, or (rarely) beyond
+        for (uint32_t m = opm & nib_eq(lo3, 0x66666666u); m; m &= m - 1u) {
+            const uint32_t b = (uint32_t)__builtin_ctz(m), below = (1u << b) - 1u;
+            const uint32_t a = aa + (uint32_t)__popc(advm & below);
+            uint64_t win = ((((uint64_t)W[1]) << 32) | word) >> b;
+            uint32_t d = 0, left = 15u - (b >> 2), j = 8u * (w0 + r) + (b >> 2), en;
+            do {
+                ++j;
+                if (left) {
+                    win >>= 4;
+                    en = (uint32_t)win & 15u;
+                    --left;
+                } else {
+                    en = j < s1 ? (sym[j >> 3] >> (4u * (j & 7u))) & 15u : 0u;
+                }
+                d = d >= (1u << 29) ? 0xFFFFFFFFu : ((d << 3) | (en & 7u));
+            } while ((en & 8u) && j < s1);
+            if (d == 0u || d > a) {
+                bad = true;
+                d = a;
+            }
+            uint32_t v = FIN | (a - d);
+            if (STOP) v |= ((word >> (b + 3u)) & 1u) ? STP : 0u;
+            slot[kk + (uint32_t)__popc(opm & below)] = (SLOT)v;
+        }
+        kk += (uint32_t)__popc(opm);
+        aa += (uint32_t)__popc(advm);
+        W[0] = W[1];
+        W[1] = W[2];
+        W[2] = W[3];
+        W[3] = W[4];
+    }
+    return true;
+}
+
+// All passes of a level whose slots are slot[0 .. expected); true when the
+// symbols are exactly its operations (and the ADVs stay inside the palette).
+template <int NT, bool STOP>
+__device__ __forceinline__ bool ops_level(Shared& sh, const uint32_t* sym, uint32_t s0, uint32_t s1, uint32_t expected,
+                                          uint16_t* slot, uint32_t& adv, uint32_t& pbuf, bool& bad) {
+    RunState rs{0u, 0u, adv};
+    if (s1 > s0) {
+        const uint32_t w_first = s0 >> 3, n_words = ((s1 - 1u) >> 3) - w_first + 1u;
+        const uint32_t lr = n_words <= NT ? 0u : n_words <= 2u * NT ? 1u : 2u;
+        for (uint32_t w = 0; w < n_words; w += NT << lr)
+            if (!ops_pass<NT, false, STOP>(sh, sym, s0, s1, w_first + w, min(n_words - w, (uint32_t)NT << lr), lr, expected, 0u,
+                                           slot, rs, pbuf, bad))
+                return false;
+    }
+    adv = rs.adv;
+    return rs.k == expected && rs.state == 0u && adv <= sh.h.pc;
+}
+
+// -------------------------------------------------------- operations to values
+// The 8 children of one expanding parent: op(c) is child c's slot as ops_pass
+// left it (without its stop bit), pv the parent's value, ext(axis, c) the value
+// of (or a reference to) the node beside child c across the parent's lower
+// face; inv[axis]: there is no such node.  A copy from a sibling takes the
+// sibling's value, which may be a reference itself.
+template <uint32_t FIN, typename OP, typename EXT>
+__device__ __forceinline__ void resolve8(uint32_t v[8], OP op, uint32_t pv, EXT ext, const bool inv[3], bool& bad) {
+#pragma unroll
+    for (uint32_t c = 0; c < 8; ++c) {
+        const uint32_t o = op(c);
+        uint32_t r = pv;
+#pragma unroll
+        for (uint32_t a = 0; a < 3; ++a) {
+            const bool is = o == a + 1u;
+            if (c & (1u << a)) {
+                r = is ? v[c ^ (1u << a)] : r;
+            } else {
+                r = is ? ext(a, c) : r;
+                bad = bad || (is && inv[a]);
+            }
+        }
+        v[c] = (o & FIN) ? o : r;
+    }
+}
+
+__device__ __forceinline__ uint4 pack8(const uint32_t v[8]) {
+    return make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
+}
+__device__ __forceinline__ uint32_t half_of(const uint4& w, uint32_t c) {
+    const uint32_t x = c < 2 ? w.x : c < 4 ? w.y : c < 6 ? w.z : w.w;
+    return c & 1u ? x >> 16 : x & 0xFFFFu;
+}
+
+// node below q along `axis` (Morton; mask am = the axis's bits): q itself when there is none
+__device__ __forceinline__ uint32_t node_below(uint32_t q, uint32_t am) {
+    const uint32_t x = q & am;
+    return (x ? (x - 1u) & am : 0u) | (q & ~am);
+}
+
+// Replace the references among 8 slots by the values at the ends of their
+// chains.  A reference points to an explicit node of the same level before its
+// source in Morton order, so chains end.
+__device__ __forceinline__ void chase8(const uint16_t* base, uint4* at) {
+    const uint4 w = *at;
+    if ((w.x & w.y & w.z & w.w & 0x80008000u) == 0x80008000u) return;
+    uint32_t v[8];
+#pragma unroll
+    for (uint32_t c = 0; c < 8; ++c) v[c] = half_of(w, c);
+    uint32_t all;
+    do {
+        all = 0x8000u;
+#pragma unroll
+        for (uint32_t c = 0; c < 8; ++c) {
+            if (!(v[c] & 0x8000u)) v[c] = base[v[c]];
+            all &= v[c];
+        }
+    } while (!all);
+    *at = pack8(v);
+}
+
+// ------------------------------------------------------------- full levels
+// Level i <= 4 into its full grid: NT threads (64: the calling wavefront alone).
+// The operations are written compactly into the grid's own space, read back by
+// the parents they belong to, and then every node of level i - 1 writes its 8
+// children and their expansion bits: an expanding parent what its operations
+// say, any other its own value.
+template <int NT>
+__device__ __forceinline__ bool full_level(Shared& sh, const uint32_t* sym, uint32_t i, uint32_t nexp, uint32_t& adv,
+                                           uint32_t& pbuf) {
+    constexpr uint32_t PP = NT >= 512 ? 1u : NT == 64 ? 1u : 512u / NT;  // parents per thread (level 4; NT = 64: levels 1..3)
+    constexpr uint32_t FIN = SlotBits<false>::kFinal, STP = SlotBits<false>::kStop;
+    const uint32_t tid = threadIdx.x & (NT - 1);
+    uint16_t* const grid = sh.G + fbase(i);
+    const uint16_t* const par = sh.G + fbase(i - 1);
+    const uint2* const ep = sh.EP + ebase(i - 1);
+    const uint32_t np = 1u << (3 * (i - 1));
+    bool bad = false;
+    if (!ops_level<NT, true>(sh, sym, sh.h.sym_end[i - 1], sh.h.sym_end[i], 8u * nexp, grid, adv, pbuf, bad)) return false;
+    lsync<NT>();
+    uint4 raw[PP];
+    bool ex[PP];
+#pragma unroll
+    for (uint32_t p = 0; p < PP; ++p) {
+        const uint32_t q = tid + p * NT;
+        ex[p] = false;
+        if (q < np) {
+            const uint2 e = ep[q >> 5];
+            ex[p] = ep_bit(e, q);
+            if (ex[p]) raw[p] = *(const uint4*)(grid + 8u * ep_rank(e, q));
+        }
+    }
+    lsync<NT>();
+    const uint32_t mx = 0x09249249u & (np - 1u);
+#pragma unroll
+    for (uint32_t p = 0; p < PP; ++p) {
+        const uint32_t q = tid + p * NT;
+        if (q < np) {
+            const uint32_t pv = par[q];
+            uint32_t v[8], bits = 0;
+            if (ex[p]) {
+                uint32_t eb[3], ea[3];
+                bool inv[3];
+#pragma unroll
+                for (uint32_t a = 0; a < 3; ++a) {
+                    const uint32_t am = mx << a, tq = node_below(q, am);
+                    inv[a] = !(q & am);
+                    const bool te = !inv[a] && ep_bit(ep[tq >> 5], tq);
+                    eb[a] = te ? 8u * tq : par[tq];
+                    ea[a] = te ? 7u : 0u;
+                }
+                resolve8<FIN>(v, [&](uint32_t c) { return half_of(raw[p], c) & ~STP; }, pv,
+                              [&](uint32_t a, uint32_t c) { return eb[a] + ((c | (1u << a)) & ea[a]); }, inv, bad);
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c) bits |= (half_of(raw[p], c) & STP) ? 0u : 1u << c;
+            } else {
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c) v[c] = pv;
+            }
+            ((uint4*)grid)[q] = pack8(v);
+            uint2* const eo = sh.EP + ebase(i) + (q >> 2);
+            if (i == 1) eo->x = bits;
+            else ((uint8_t*)&eo->x)[q & 3u] = (uint8_t)bits;
+        }
+    }
+    if (bad) sh.err = 1u;
+    lsync<NT>();
+#pragma unroll
+    for (uint32_t p = 0; p < PP; ++p)
+        if (ex[p]) chase8(grid, (uint4*)grid + (tid + p * NT));
+    return true;
+}
+
+// Levels 0..last (at most 3) by the calling wavefront alone; then the parent
+// prefix of the next level, the number of its expanding nodes in sh.nexp and
+// the ADV count in sh.adv.  Level 0 is one node whose only valid operation is
+// PALETTE_ADV (entry 0), with or without a stop bit.
+__device__ __forceinline__ void small_levels(Shared& sh, const uint32_t* sym, uint32_t last) {
+    const uint32_t s0 = sym[0] & 15u;
+    if (sh.h.sym_end[0] != 1u || (s0 & 7u) != kAdv || sh.h.pc == 0u) {
+        sh.err = 1u;
+        return;
+    }
+    if (lane_id() == 0) {
+        sh.G[fbase(0)] = 0x8000u;
+        sh.EP[ebase(0)] = make_uint2(s0 & 8u ? 0u : 1u, 0u);
+    }
+    lsync<64>();
+    uint32_t adv = 1, pbuf = 0, nexp = s0 & 8u ? 0u : 1u;
+    for (uint32_t i = 1; i <= last; ++i) {
+        if (!full_level<64>(sh, sym, i, nexp, adv, pbuf)) {
+            sh.err = 1u;
+            return;
+        }
+        lsync<64>();
+        nexp = level_prefix(sh.EP + ebase(i), ewords(i));
+        lsync<64>();
+    }
+    if (lane_id() == 0) {
+        sh.nexp = nexp;
+        sh.adv = adv;
+    }
+}
+
+// ------------------------------------------------------- level 5 in LDS
+// Level 5 of a 32^3 cube at full resolution: its explicit nodes by operation
+// rank in the slot area (child c of the r-th expanding parent at 8r + c).
+template <int NT>
+__device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t* c5, uint16_t* list, uint32_t nexp,
+                                       uint32_t& adv, uint32_t& pbuf) {
+    constexpr uint32_t FIN = SlotBits<false>::kFinal;
+    const uint2* const ep = sh.EP + ebase(4);
+    const uint16_t* const par = sh.G + fbase(4);
+    // the expanding parents by rank: each thread lists those of some bytes of the bitmap
+    for (uint32_t b = threadIdx.x; b < 512u; b += NT) {
+        const uint2 e = ep[b >> 2];
+        uint32_t r = ep_rank(e, 8u * b), bits = (e.x >> (8u * (b & 3u))) & 0xFFu;
+#pragma unroll
+        for (uint32_t c = 0; c < 8; ++c)
+            if ((bits >> c) & 1u) list[r++] = (uint16_t)(8u * b + c);
+    }
+    bool bad = false;
+    if (!ops_level<NT, false>(sh, sym, sh.h.sym_end[4], sh.h.sym_end[5], 8u * nexp, c5, adv, pbuf, bad)) return false;
+    __syncthreads();
+    for (uint32_t r = threadIdx.x; r < nexp; r += NT) {
+        const uint32_t q = list[r], pv = par[q];
+        const uint4 raw = ((const uint4*)c5)[r];
+        uint32_t eb[3], ea[3], v[8];
+        bool inv[3];
+#pragma unroll
+        for (uint32_t a = 0; a < 3; ++a) {
+            const uint32_t am = 0x249u << a, tq = node_below(q, am);
+            const uint2 e = ep[tq >> 5];
+            inv[a] = !(q & am);
+            const bool te = !inv[a] && ep_bit(e, tq);
+            eb[a] = te ? 8u * ep_rank(e, tq) : par[tq];
+            ea[a] = te ? 7u : 0u;
+        }
+        resolve8<FIN>(v, [&](uint32_t c) { return half_of(raw, c); }, pv,
+                      [&](uint32_t a, uint32_t c) { return eb[a] + ((c | (1u << a)) & ea[a]); }, inv, bad);
+        ((uint4*)c5)[r] = pack8(v);
+    }
+    if (bad) sh.err = 1u;
+    __syncthreads();
+    for (uint32_t r = threadIdx.x; r < nexp; r += NT) chase8(c5, (uint4*)c5 + r);
+    return true;
+}
+
+// ------------------------------------------------ levels 5 and 6 in chunks
+// A level whose explicit nodes do not fit in LDS: level 6, level 5 of a 64^3
+// cube, and level 5 of a 32^3 cube that outgrows the slot area or whose palette
+// indices need more than 15 bits.  The symbols are read in passes; the
+// operations of a pass go to a buffer of 32-bit slots in LDS, and the parents
+// whose 8 operations are there are finished before the next pass.  References
+// point into the buffer; a node finished earlier is read where its result went:
+//   LABELS  the task's output, which holds the labels of all nodes before the
+//           chunk and of all implied nodes (fill_implied);
+//   else    the work-group's scratch (c5: the palette index by operation rank).
+constexpr uint32_t kChunkDone = 0x20000000u;  // slot: the result is where the low bits say (c5 rank, output voxel)
+
+struct ChunkMem {
+    uint2* ep5;      // level-5 bitmap (64^3 cubes), 1024 entries at the start of the slot area
+    uint32_t* buf;   // operation buffer behind it
+    uint32_t cap;    // its 32-bit slots
+    uint16_t* c5;    // scratch: level-5 palette indices by operation rank
+    uint16_t* list;  // scratch: expanding parents by rank
+    const void* pal; // palette: staged in LDS, or the record's
+};
+
+// palette index of a level-5 node (64^3 cubes; levels 4 and 5 final)
+__device__ __forceinline__ uint32_t value5(const Shared& sh, const ChunkMem& cm, uint32_t node) {
+    const uint32_t q = node >> 3;
+    const uint2 e = sh.EP[ebase(4) + (q >> 5)];
+    return ep_bit(e, q) ? (uint32_t)cm.c5[8u * ep_rank(e, q) + (node & 7u)] : (uint32_t)sh.G[fbase(4) + q] & 0x7FFFu;
+}
+
+template <int NT, bool LABELS, typename LT>
+__device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const ChunkMem& cm, const uint32_t* sym, uint32_t i,
+                                            uint32_t nexp, uint32_t& adv, uint32_t& pbuf) {
+    constexpr uint32_t FIN = SlotBits<true>::kFinal, STP = SlotBits<true>::kStop;
+    const uint32_t tid = threadIdx.x, S = 1u << i, pc = sh.h.pc;
+    const LT* const pal = (const LT*)cm.pal;
+    const uint2* const ep = i == 5 ? sh.EP + ebase(4) : cm.ep5;
+    const uint16_t* const par4 = sh.G + fbase(4);
+    const bool with_bits = i == 5 && sh.h.t == 6;
+    LT* const out = (LT*)(P.out + sh.h.out_off * sizeof(LT));
+    const bool vec = ((uintptr_t)out & (2 * sizeof(LT) - 1)) == 0;
+    // expanding parents by rank
+    const uint32_t nb = 1u << (3 * (i - 1) - 3);
+    for (uint32_t b = tid; b < nb; b += NT) {
+        const uint2 e = ep[b >> 2];
+        uint32_t r = ep_rank(e, 8u * b), bits = (e.x >> (8u * (b & 3u))) & 0xFFu;
+        for (; bits; bits &= bits - 1u) cm.list[r++] = (uint16_t)(8u * b + (uint32_t)__builtin_ctz(bits));
+    }
+    if (with_bits)
+        for (uint32_t w = tid; w < 1024u; w += NT) cm.ep5[w].x = 0;
+    __syncthreads();
+    const uint32_t s0 = sh.h.sym_end[i - 1], s1 = sh.h.sym_end[i], expected = 8u * nexp;
+    const uint32_t mx = 0x09249249u & ((1u << (3 * (i - 1))) - 1u);
+    RunState rs{0u, 0u, adv};
+    uint32_t r_next = 0;
+    bool bad = false;
+    const uint32_t w_first = s0 >> 3, n_words = s1 > s0 ? ((s1 - 1u) >> 3) - w_first + 1u : 0u;
+    const uint32_t step = min((uint32_t)NT, (cm.cap - 8u) / 8u);  // words of a pass: their operations fit
+    for (uint32_t w = 0; w < n_words; w += step) {
+        const uint32_t kbase = 8u * r_next;
+        if (!ops_pass<NT, true, true>(sh, sym, s0, s1, w_first + w, min(n_words - w, step), 0u, expected, kbase, cm.buf, rs,
+                                      pbuf, bad))
+            return false;
+        __syncthreads();
+        const uint32_t n_par = (rs.k >> 3) - r_next;
+        for (uint32_t x = tid; x < n_par; x += NT) {
+            const uint32_t q = cm.list[r_next + x];
+            uint32_t raw[8], v[8], eb[3];
+            bool inv[3], in[3], te[3];
+#pragma unroll
+            for (uint32_t c = 0; c < 8; ++c) raw[c] = cm.buf[8u * x + c];
+            const uint32_t pv = FIN | (i == 5 ? (uint32_t)par4[q] & 0x7FFFu : value5(sh, cm, q));
+            const uint32_t vox = (compact3(q >> 2) * 2u * S + compact3(q >> 1) * 2u) * S + compact3(q) * 2u;  // child 0's
+#pragma unroll
+            for (uint32_t a = 0; a < 3; ++a) {
+                const uint32_t am = mx << a, tq = node_below(q, am);
+                const uint2 e = ep[tq >> 5];
+                inv[a] = !(q & am);
+                te[a] = !inv[a] && ep_bit(e, tq);
+                const uint32_t kt = 8u * ep_rank(e, tq);
+                in[a] = te[a] && kt >= kbase;
+                eb[a] = in[a] ? kt - kbase : kt;
+                if (!te[a] && i == 5) eb[a] = FIN | ((uint32_t)par4[tq] & 0x7FFFu);
+            }
+            auto ext = [&](uint32_t a, uint32_t c) -> uint32_t {
+                const uint32_t ct = c | (1u << a);
+                if (!te[a] && i == 5) return eb[a];
+                if (!LABELS) return in[a] ? eb[a] + ct : FIN | kChunkDone | (eb[a] + ct);
+                const uint32_t at = vox + ((c >> 2) * S + ((c >> 1) & 1u)) * S + (c & 1u) - (a == 0 ? 1u : a == 1 ? S : S * S);
+                return in[a] ? eb[a] + ct : inv[a] ? FIN : FIN | kChunkDone | at;
+            };
+            resolve8<FIN>(v, [&](uint32_t c) { return raw[c] & ~STP; }, pv, ext, inv, bad);
+            if (with_bits) {
+                uint32_t bits = 0;
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c) bits |= (raw[c] & STP) ? 0u : 1u << c;
+                ((uint8_t*)&cm.ep5[q >> 2].x)[q & 3u] = (uint8_t)bits;
+            }
+#pragma unroll
+            for (uint32_t c = 0; c < 8; ++c) cm.buf[8u * x + c] = v[c];
+        }
+        // operations of a parent that the next pass completes move to the front
+        const uint32_t rest = rs.k & 7u, keep = tid < rest ? cm.buf[8u * n_par + tid] : 0u;
+        __syncthreads();
+        for (uint32_t x = tid; x < n_par; x += NT) {
+            const uint32_t q = cm.list[r_next + x];
+            uint32_t v[8], all;
+#pragma unroll
+            for (uint32_t c = 0; c < 8; ++c) v[c] = cm.buf[8u * x + c];
+            do {
+                all = FIN;
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c) {
+                    if (!(v[c] & FIN)) v[c] = cm.buf[v[c]];
+                    all &= v[c];
+                }
+            } while (!all);
+            // (both candidates are loaded, at clamped places: no branch around the loads)
+            if (!LABELS) {
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c) {
+                    const bool done = v[c] & kChunkDone;
+                    const uint32_t at = v[c] & (kChunkDone - 1u), got = cm.c5[done ? at : 0u];
+                    v[c] = done ? got : at & 0xFFFFu;
+                }
+                ((uint4*)cm.c5)[r_next + x] = pack8(v);
+            } else {
+                LT l[8];
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c) {
+                    const bool done = v[c] & kChunkDone;
+                    const uint32_t at = v[c] & (kChunkDone - 1u);
+                    const LT got = out[done ? at : 0u], own = pal[min(done ? 0u : at, pc - 1u)];
+                    l[c] = done ? got : own;
+                }
+                LT* const o = out + (compact3(q >> 2) * 2u * S + compact3(q >> 1) * 2u) * S + compact3(q) * 2u;
+#pragma unroll
+                for (uint32_t zy = 0; zy < 4; ++zy) {
+                    store2<LT>(o + ((zy >> 1) * S + (zy & 1u)) * S, l[2 * zy], l[2 * zy + 1], vec);
+                }
+            }
+        }
+        __syncthreads();
+        if (tid < rest) cm.buf[tid] = keep;
+        r_next += n_par;
+    }
+    if (bad) sh.err = 1u;
+    adv = rs.adv;
+    return rs.k == expected && rs.state == 0u && adv <= pc;
+}
+
+// Labels of the implied nodes of level t = 5 or 6 (children of the level t - 1
+// nodes that do not expand), by pairs of such nodes along x.
+template <int NT, typename LT>
+__device__ __forceinline__ void fill_implied(const Params& P, Shared& sh, const ChunkMem& cm) {
+    const uint32_t t = sh.h.t, S = 1u << t, hb = t - 1, H = 1u << hb, pc = sh.h.pc;
+    const LT* const pal = (const LT*)cm.pal;
+    LT* const out = (LT*)(P.out + sh.h.out_off * sizeof(LT));
+    const bool vec = ((uintptr_t)out & (4 * sizeof(LT) - 1)) == 0;
+    const uint2* const ep = t == 5 ? sh.EP + ebase(4) : cm.ep5;
+    for (uint32_t u = threadIdx.x; u < (H >> 1) * H * H; u += NT) {
+        const uint32_t px = u & ((H >> 1) - 1), qy = (u >> (hb - 1)) & (H - 1), qz = u >> (2 * hb - 1);
+        const uint32_t q = spread3(2 * px) | (spread3(qy) << 1) | (spread3(qz) << 2);
+        const uint32_t ex = (ep[q >> 5].x >> (q & 31)) & 3u;  // the x neighbour differs in bit 0
+        if (ex == 3u) continue;
+        LT l[2];
+#pragma unroll
+        for (uint32_t hx = 0; hx < 2; ++hx) {
+            const uint32_t idx = t == 5 ? (uint32_t)sh.G[fbase(4) + q + hx] & 0x7FFFu : value5(sh, cm, q + hx);
+            l[hx] = pal[min(idx, pc - 1u)];
+        }
+        LT* const o = out + ((2 * qz) * S + 2 * qy) * S + 4 * px;
+#pragma unroll
+        for (uint32_t zy = 0; zy < 4; ++zy) {
+            LT* const d = o + ((zy >> 1) * S + (zy & 1u)) * S;
+            if (ex == 0u) store4<LT, false>(d, l[0], l[0], l[1], l[1], vec);
+            else store2<LT>(d + (ex == 1u ? 2 : 0), l[ex & 1u], l[ex & 1u], vec);
+        }
+    }
+}
+
+// Levels 4..t (0..3 are decoded); wavefront 0 computes a level's parent prefix
+// before the barrier that ends it.  False (to every thread) on an error; labels:
+// the output pass is left to do, from c5g (scratch) when it is set.
+template <int NT>
+__device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8_t* u_area, uint16_t* slots, uint8_t* scratch,
+                                              const uint32_t* sym, uint16_t*& c5g, bool& labels) {
+    const uint32_t t = sh.h.t, wave = threadIdx.x >> 6;
+    uint32_t adv = sh.adv, pbuf = 0;
+    bool ok = true;
+    labels = true;
+    if (t >= 4) {
+        ok = full_level<NT>(sh, sym, 4, sh.nexp, adv, pbuf);
+        if (ok && t >= 5) {
+            if (wave == 0) {
+                const uint32_t n = level_prefix(sh.EP + ebase(4), ewords(4));
+                if (threadIdx.x == 0) sh.nexp = n;
+            }
+            __syncthreads();
+            const uint32_t nexp = sh.nexp;
+            if (t == 5 && 8u * nexp <= P.cap16 && sh.h.pc <= 32768u) {
+                ok = level5<NT>(sh, sym, slots, (uint16_t*)u_area, nexp, adv, pbuf);
+            } else {
+                ChunkMem cm;
+                cm.ep5 = (uint2*)slots;
+                cm.buf = (uint32_t*)(cm.ep5 + 1024);
+                cm.cap = P.cap16 / 2u - 2048u;
+                cm.c5 = (uint16_t*)(scratch + kScrComp);
+                cm.list = (uint16_t*)(scratch + kScrList);
+                cm.pal = P.vol + sh.h.pal_off;
+                const uint32_t pb = sh.h.pc * P.label_bytes;
+                if (sh.h.pc <= kUBytesMin / P.label_bytes && !P.pal_bits) {  // (staged behind the next barrier)
+                    for (uint32_t w = threadIdx.x; w < pb / 4u; w += NT) ((uint32_t*)u_area)[w] = ((const uint32_t*)cm.pal)[w];
+                    cm.pal = u_area;
+                }
+                c5g = cm.c5;
+                if (t == 6 || P.pal_bits) {
+                    ok = chunk_level<NT, false, uint32_t>(P, sh, cm, sym, 5, nexp, adv, pbuf);
+                    if (ok && t == 6) {
+                        if (wave == 0) {
+                            const uint32_t n = level_prefix(cm.ep5, 1024u);
+                            if (threadIdx.x == 0) sh.nexp = n;
+                        }
+                    }
+                }
+                __syncthreads();
+                if (ok && !P.pal_bits) {
+                    labels = false;
+                    if (P.label_bytes == 4) {
+                        fill_implied<NT, uint32_t>(P, sh, cm);
+                        ok = chunk_level<NT, true, uint32_t>(P, sh, cm, sym, t, sh.nexp, adv, pbuf);
+                    } else {
+                        fill_implied<NT, uint64_t>(P, sh, cm);
+                        ok = chunk_level<NT, true, uint64_t>(P, sh, cm, sym, t, sh.nexp, adv, pbuf);
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    return ok && !(t == sh.h.L && adv != sh.h.pc) && !sh.err;
+}
+// Labels of level t <= 5 (all slots final) as an S^3 x-fastest cube.  Full
+// levels voxel by voxel (4 per thread); level 5 by pairs of 2x2x2 blocks along
+// x under two level-4 nodes: a node that does not expand gives its value to its
+// 8 children, an expanding one has 8 explicit children.
+template <int NT, typename LT, bool PAL_LDS>
+__device__ __forceinline__ void write_labels(const Params& P, Shared& sh, const uint8_t* u_area, const uint16_t* c5) {
     const TaskHdr& h = sh.h;
     const uint32_t t = h.t, S = 1u << t, pc = h.pc;
-    constexpr uint32_t VIDX = (uint32_t)Slot<V>::kIdx;
     LT* out = (LT*)(P.out + h.out_off * sizeof(LT));
-    const LT* pal = PAL_LDS ? (const LT*)sh.U : (const LT*)(P.vol + h.pal_off);
+    const LT* pal = PAL_LDS ? (const LT*)u_area : (const LT*)(P.vol + h.pal_off);
     const bool vec = ((uintptr_t)out & (4 * sizeof(LT) - 1)) == 0;
     if (t <= 4) {
-        const V* g = st.full + fbase(t);
+        const uint16_t* g = sh.G + fbase(t);
         if (S < 4) {
             const uint32_t n = S * S * S;
             for (uint32_t v = threadIdx.x; v < n; v += NT) {
                 const uint32_t x = v & (S - 1), y = (v >> t) & (S - 1), z = v >> (2 * t);
-                const LT l = pal_get<LT, PAL_LDS>(pal, g[spread3(x) | (spread3(y) << 1) | (spread3(z) << 2)] & VIDX, pc);
+                const LT l = pal_get<LT, PAL_LDS>(pal, g[spread3(x) | (spread3(y) << 1) | (spread3(z) << 2)] & 0x7FFFu, pc);
                 __builtin_nontemporal_store(l, out + v);
             }
             return;
@@ -1068,61 +1209,48 @@ __device__ __forceinline__ void write_labels(const Params& P, Shared& sh, const 
             const uint32_t lin = u << 2;
             const uint32_t x = lin & (S - 1), y = (lin >> t) & (S - 1), z = lin >> (2 * t);
             const uint32_t m = spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
-            store4<LT>(out + lin, pal_get<LT, PAL_LDS>(pal, g[m] & VIDX, pc), pal_get<LT, PAL_LDS>(pal, g[m + 1] & VIDX, pc),
-                       pal_get<LT, PAL_LDS>(pal, g[m + 8] & VIDX, pc), pal_get<LT, PAL_LDS>(pal, g[m + 9] & VIDX, pc), vec);
+            store4<LT>(out + lin, pal_get<LT, PAL_LDS>(pal, g[m] & 0x7FFFu, pc), pal_get<LT, PAL_LDS>(pal, g[m + 1] & 0x7FFFu, pc),
+                       pal_get<LT, PAL_LDS>(pal, g[m + 8] & 0x7FFFu, pc), pal_get<LT, PAL_LDS>(pal, g[m + 9] & 0x7FFFu, pc), vec);
         }
         return;
     }
-    const uint32_t hb = t - 1, H = 1u << hb;  // parents per axis
-    const uint32_t units = (H >> 1) * H * H;   // pairs of parents along x
-    for (uint32_t u = threadIdx.x; u < units; u += NT) {
-        const uint32_t px = u & ((H >> 1) - 1), qy = (u >> (hb - 1)) & (H - 1), qz = u >> (2 * hb - 1);
-        const uint64_t e0 = ((uint64_t)(2 * qz) * S + 2 * qy) * S + 4 * px;
+    for (uint32_t u = threadIdx.x; u < 2048u; u += NT) {
+        const uint32_t px = u & 7u, qy = (u >> 3) & 15u, qz = u >> 7;
+        LT* const o = out + ((2 * qz) * S + 2 * qy) * S + 4 * px;
+        const uint32_t q = spread3(2 * px) | (spread3(qy) << 1) | (spread3(qz) << 2);
+        const uint2 e = sh.EP[ebase(4) + (q >> 5)];
+        const uint32_t r = ep_rank(e, q), ex = (e.x >> (q & 31)) & 3u;  // the x neighbour differs in bit 0
+        const uint32_t f2 = *(const uint32_t*)(sh.G + fbase(4) + q);
         // palette indices of the 8 children of each of the two nodes (child c = x | y << 1 | z << 2)
-        uint32_t ix[2][8];
-        const uint32_t q0 = spread3(2 * px) | (spread3(qy) << 1) | (spread3(qz) << 2);
+        LT l[2][8];
 #pragma unroll
-        for (int hx = 0; hx < 2; ++hx) {
-            const uint32_t q = q0 | (uint32_t)hx;  // the x neighbour differs in bit 0
-            if (t == 5) {
-                if (st.ebit(4, q)) {
-                    const V* c = st.c5 + 8 * st.rank(4, q);
+        for (uint32_t hx = 0; hx < 2; ++hx) {
+            const uint32_t f = (hx ? f2 >> 16 : f2) & 0x7FFFu;
+            if ((ex >> hx) & 1u) {
+                const uint4 w = ((const uint4*)c5)[r + (hx & ex)];
 #pragma unroll
-                    for (int ch = 0; ch < 8; ++ch) ix[hx][ch] = c[ch] & VIDX;
-                } else {
-                    const uint32_t v = st.full[fbase(4) + q] & VIDX;
-#pragma unroll
-                    for (int ch = 0; ch < 8; ++ch) ix[hx][ch] = v;
-                }
-            } else if (st.ebit5(q)) {
-                const uint32_t* o6 = st.out6 + (e0 + 2 * hx) * st.lb4;
-#pragma unroll
-                for (int ch = 0; ch < 8; ++ch)
-                    ix[hx][ch] = o6[((((ch >> 2) & 1) * S + ((ch >> 1) & 1)) * S + (ch & 1)) * st.lb4] & 0x7FFFFFFFu;
+                for (uint32_t c = 0; c < 8; ++c) l[hx][c] = pal_get<LT, PAL_LDS>(pal, half_of(w, c) & 0x7FFFu, pc);
             } else {
-                const uint32_t v = st.value5(q) & VIDX;
+                const LT v = pal_get<LT, PAL_LDS>(pal, f, pc);
 #pragma unroll
-                for (int ch = 0; ch < 8; ++ch) ix[hx][ch] = v;
+                for (uint32_t c = 0; c < 8; ++c) l[hx][c] = v;
             }
         }
 #pragma unroll
-        for (int zy = 0; zy < 4; ++zy) {
-            store4<LT>(out + e0 + ((uint64_t)(zy >> 1) * S + (zy & 1)) * S,
-                       pal_get<LT, PAL_LDS>(pal, ix[0][2 * zy], pc), pal_get<LT, PAL_LDS>(pal, ix[0][2 * zy + 1], pc),
-                       pal_get<LT, PAL_LDS>(pal, ix[1][2 * zy], pc), pal_get<LT, PAL_LDS>(pal, ix[1][2 * zy + 1], pc), vec);
-        }
+        for (uint32_t zy = 0; zy < 4; ++zy)
+            store4<LT>(o + ((zy >> 1) * S + (zy & 1u)) * S, l[0][2 * zy], l[0][2 * zy + 1], l[1][2 * zy], l[1][2 * zy + 1], vec);
     }
 }
 
 // Cache-paletted output: the cube's palette indices, I bits each, floor(32/I)
 // to a 32-bit word (voxel k, x fastest, in word k / e at bit (k mod e) * I).
-// One thread per word; level 5 reaches a voxel's slot through its level-4
-// parent, looked up once per pair of voxels along x.
-template <int NT, typename V>
-__device__ __forceinline__ void write_indices(const Params& P, Shared& sh, const Store<V>& st) {
+// One thread per word; level 5 (c5: slots, or with C5G plain indices in
+// scratch) reaches a voxel through its level-4 parent, looked up once per pair
+// of voxels along x.
+template <int NT, bool C5G>
+__device__ __forceinline__ void write_indices(const Params& P, Shared& sh, const uint16_t* c5) {
     const TaskHdr& h = sh.h;
     const uint32_t t = h.t, S = 1u << t, bits = P.pal_bits, e = 32u / bits;
-    constexpr uint32_t VIDX = (uint32_t)Slot<V>::kIdx;
     const uint32_t n = S * S * S, words = (n + e - 1u) / e;
     uint32_t* const out = (uint32_t*)P.out + h.out_off;
     for (uint32_t w = threadIdx.x; w < words; w += NT) {
@@ -1135,15 +1263,16 @@ __device__ __forceinline__ void write_indices(const Params& P, Shared& sh, const
             const uint32_t m = spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
             uint32_t idx;
             if (t <= 4) {
-                idx = st.full[fbase(t) + m] & VIDX;
+                idx = sh.G[fbase(t) + m] & 0x7FFFu;
             } else {
                 const uint32_t pq = m >> 3;
                 if (pq != last_q) {
                     last_q = pq;
-                    expands = st.ebit(4, pq);
-                    base = expands ? 8u * st.rank(4, pq) : (uint32_t)st.full[fbase(4) + pq];
+                    const uint2 ep = sh.EP[ebase(4) + (pq >> 5)];
+                    expands = ep_bit(ep, pq);
+                    base = expands ? 8u * ep_rank(ep, pq) : (uint32_t)sh.G[fbase(4) + pq] & 0x7FFFu;
                 }
-                idx = (expands ? (uint32_t)st.c5[base + (m & 7u)] : base) & VIDX;
+                idx = expands ? (uint32_t)c5[base + (m & 7u)] & (C5G ? 0xFFFFu : 0x7FFFu) : base;
             }
             acc |= idx << (q * bits);
         }
@@ -1151,165 +1280,129 @@ __device__ __forceinline__ void write_indices(const Params& P, Shared& sh, const
     }
 }
 
-template <int NT, typename V>
-__device__ __forceinline__ void write_output(const Params& P, Shared& sh, const Store<V>& st) {
+// Output pass; c5g: the level-5 palette indices in scratch (null: slots in LDS).
+template <int NT>
+__device__ __forceinline__ void write_output(const Params& P, Shared& sh, uint8_t* u_area, uint32_t u_bytes,
+                                             const uint16_t* slots, const uint16_t* c5g) {
+    const TaskHdr& h = sh.h;
     if (P.pal_bits) {
-        write_indices<NT, V>(P, sh, st);
-    } else if (P.label_bytes == 4) {
-        if (sh.h.pal_lds && sh.h.t > 3) write_labels<NT, V, uint32_t, true>(P, sh, st);
-        else write_labels<NT, V, uint32_t, false>(P, sh, st);
+        if (c5g) write_indices<NT, true>(P, sh, c5g);
+        else write_indices<NT, false>(P, sh, slots);
+        return;
+    }
+    // the palette is staged in LDS over the parent list when it fits there (a
+    // cube of side <= 8 reads its few labels straight from the record)
+    const bool lds = h.t > 3 && (uint64_t)h.pc * P.label_bytes <= u_bytes;
+    if (lds) {
+        const uint32_t words = h.pc * P.label_bytes / 4u;
+        const uint32_t* src = (const uint32_t*)(P.vol + h.pal_off);
+        for (uint32_t w = threadIdx.x; w < words; w += NT) ((uint32_t*)u_area)[w] = src[w];
+        __syncthreads();
+    }
+    if (P.label_bytes == 4) {
+        if (lds) write_labels<NT, uint32_t, true>(P, sh, u_area, slots);
+        else write_labels<NT, uint32_t, false>(P, sh, u_area, slots);
     } else {
-        if (sh.h.pal_lds && sh.h.t > 3) write_labels<NT, V, uint64_t, true>(P, sh, st);
-        else write_labels<NT, V, uint64_t, false>(P, sh, st);
+        if (lds) write_labels<NT, uint64_t, true>(P, sh, u_area, slots);
+        else write_labels<NT, uint64_t, false>(P, sh, u_area, slots);
     }
 }
 
 // ------------------------------------------------------------------ a task
-template <typename V, bool BIG, bool C5G>
-__device__ __forceinline__ Store<V> make_store(const Params& P, Shared& sh, uint16_t* slots_lds, uint8_t* scratch) {
-    const TaskHdr& h = sh.h;
-    Store<V> st;
-    st.E = sh.E;
-    st.wpre = sh.wpre;
-    st.E5 = (uint32_t*)(scratch + kScrE5);
-    st.wpre5 = (uint16_t*)(scratch + kScrWpre5);
-    st.list_l = (uint16_t*)sh.U;
-    st.list_g = (uint16_t*)(scratch + kScrList);
-    st.pval_g = (uint32_t*)(scratch + kScrPval);
-    st.lb4 = P.label_bytes / 4;
-    st.out6 = (uint32_t*)(P.out + h.out_off * P.label_bytes);
-    if (BIG) {
-        st.full = (V*)(scratch + kScrFull);
-        st.c5 = (V*)(scratch + kScrComp);
-    } else {
-        st.full = (V*)sh.G;
-        st.c5 = C5G ? (V*)(scratch + kScrComp) : (V*)slots_lds;
-    }
-    return st;
-}
-
-template <int NT, typename V, bool BIG, bool C5G>
-__device__ __forceinline__ void run_levels(const Params& P, Shared& sh, uint16_t* slots_lds, uint8_t* scratch, const uint8_t* nib,
-                                           Ahead& ah, int small_upto) {
-    const TaskHdr& h = sh.h;
-    const Store<V> st = make_store<V, BIG, C5G>(P, sh, slots_lds, scratch);
-    if (!BIG && h.t <= 5) decode_levels<NT, V, BIG, true>(P, sh, st, nib, ah, small_upto);
-    else decode_levels<NT, V, BIG, false>(P, sh, st, nib, ah, small_upto);
-    if (sh.err) return;
-    // palette staging for the output pass (the parent list is no longer needed);
-    // a cube of side <= 8 reads its few labels straight from the record
-    if (h.pal_lds && !P.pal_bits && h.t > 3) {
-        const uint32_t words = (h.pc * P.label_bytes + 3) / 4;
-        const uint32_t* src = (const uint32_t*)(P.vol + h.pal_off);
-        for (uint32_t w = threadIdx.x; w < words; w += NT) ((uint32_t*)sh.U)[w] = src[w];
-        __syncthreads();
-    }
-    write_output<NT, V>(P, sh, st);
-}
-
 template <int NT>
-__device__ __forceinline__ void decode_task(const Params& P, Shared& sh, uint16_t* slots_lds, uint8_t* scratch,
-                                            Ahead& ah) {
+__device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8_t* scratch, Ahead& ah) {
+    Shared& sh = *reinterpret_cast<Shared*>(lds);
     const TaskHdr& h = sh.h;
     if (h.status != kTaskOk) {
         if (h.status == kTaskCorrupt && h.write_ok) zero_output<NT>(P, h);
         return;
     }
-    // The symbols (4 bits each) are read by the level passes as aligned 32-bit
-    // words: from the work-group's scratch, or for a cube of side <= 16 (levels
-    // 0..4, whose parent lists take at most 1 KiB) from the rest of the parent
-    // list area when they fit there.
-    constexpr uint32_t kListMax4 = 1024;
-    const bool sym_lds = h.t <= 4 && (h.nsym + 1u) / 2u + 4u <= kUBytes - kListMax4;
-    uint8_t* const nib = sym_lds ? sh.U + kListMax4 : scratch + kScrSym;
-    bool tab_used = false;
-    int small_upto = -1;  // last level decoded during the rANS decode
-    if (h.coder == kRaw4) {
-        const uint32_t bytes = (h.nsym + 1u) / 2u, words = bytes / 4u;
-        const uint32_t* src = (const uint32_t*)(P.vol + h.pay_off);
-        for (uint32_t w = threadIdx.x; w < words; w += NT) ((uint32_t*)nib)[w] = src[w];
-        for (uint32_t b = 4u * words + threadIdx.x; b < bytes; b += NT) nib[b] = P.vol[h.pay_off + b];
-        __syncthreads();
-    } else {
-        // the rANS table sits in the last 16 KiB of the slot area until level 5
-        // of a fast-path task overwrites it (later tasks find it there until
-        // then); the grids, parent list and the rest of the slot area before it
-        // can stage the record's words and the decoded symbols
-        uint8_t* const stage = (uint8_t*)sh.G;
-        const uint32_t stage_bytes = (uint32_t)(sizeof(sh.G) + sizeof(sh.U)) + 2u * P.cap16 - 4u * kRansM;
-        uint32_t* tab = (uint32_t*)(stage + stage_bytes);
-        tab_used = true;
-        if (!sh.tab_ok) {
-            const uint4* src = (const uint4*)P.rans_tab;
-            for (uint32_t w = threadIdx.x; w < kRansM / 4; w += NT) ((uint4*)tab)[w] = src[w];
+    const uint32_t u_bytes = list_bytes(P.cap16);
+    uint8_t* const u_area = lds + sizeof(Shared);
+    uint16_t* const slots = (uint16_t*)(u_area + u_bytes);
+    // The symbols, 4 bits each, are read by the level passes as aligned 32-bit
+    // words: plain payloads from the record itself, rANS symbols from LDS for a
+    // cube of side <= 16, else from the work-group's scratch.
+    const uint32_t wave = threadIdx.x >> 6, n_words = (h.nsym + 7u) / 8u;
+    const bool rans = h.coder == kRans;
+    // The decoding table sits in the last 16 KiB of the slot area until a level 5
+    // overwrites it (later tasks find it there until then).  What lies between the
+    // level 0..3 grids and the table stages the record's words and takes the
+    // symbols, which end at the table.
+    constexpr uint32_t kLoGrid = 1280;  // bytes of the level 0..3 grids (1184), rounded up
+    const uint32_t o_words = (uint32_t)offsetof(Shared, G) + kLoGrid;
+    const uint32_t o_tab = (uint32_t)sizeof(Shared) + u_bytes + 2u * P.cap16 - 4u * kRansM;
+    const uint32_t G = rans ? ((1u << h.log2W) + 63u) / 64u : 0u;
+    const uint32_t words_bytes = rans ? (2u * (h.gstart[G - 1] + h.gw[G - 1]) + 15u) & ~15u : 0u, sym_bytes = 4u * n_words;
+    const bool fits = rans && (uint64_t)o_words + words_bytes + sym_bytes + 16u <= o_tab;
+    const uint32_t o_sym = fits ? (o_tab - sym_bytes) & ~15u : 0u;
+    // Overlap, for a cube with a level 3 whose lane groups leave a wavefront free:
+    // wavefronts 0..G-1 decode the lane groups, wavefront G decodes levels 0..3 as
+    // soon as every group is past their symbols.  (two or more lanes: a round
+    // writes whole bytes of symbol pairs)
+    const bool overlap = fits && G < NT / 64 && h.log2W >= 1u && h.t >= 3;
+    const uint32_t small = min(h.t, 3u), need = h.sym_end[small];
+    uint8_t* const nib = scratch + kScrSym;
+    const uint32_t* sym = fits ? (const uint32_t*)(lds + o_sym) : (const uint32_t*)nib;
+    uint32_t x0 = 0;
+    if (!rans) {
+        if (h.pay_off + 4ull * max(n_words, 1u) <= P.vol_bytes) {
+            sym = (const uint32_t*)(P.vol + h.pay_off);
+        } else {  // the last record's last word would end past the container
+            for (uint32_t b = threadIdx.x; b < (h.nsym + 1u) / 2u; b += NT) nib[b] = P.vol[h.pay_off + b];
             __syncthreads();
         }
-        const uint32_t G = ((1u << h.log2W) + 63u) / 64u, tw = h.gstart[G - 1] + h.gw[G - 1];
-        const uint32_t words_bytes = (2u * tw + 15u) & ~15u;
-        const uint32_t sym_bytes = ((h.nsym + 1u) / 2u + 3u) / 4u * 4u;
-        // symbols bound for the parent list area: the staged words must end before it
-        const uint32_t u_at = (uint32_t)(offsetof(Shared, U) - offsetof(Shared, G));
-        const uint32_t nl_at = u_at + kListMax4;
-        // Overlap, for a fast-path cube with a level 3 whose lane groups leave a
-        // wavefront free: words staged after the grids of levels 0..3, symbols in
-        // the parent-list area when they are read there, else at the end of the
-        // stage (clear of the level 1..3 parent lists).  Wavefronts
-        // 0..G-1 decode the lane groups, wavefront G decodes levels 0..2 (0..3 for
-        // a cube with a level 5, whose rounds last long enough) as soon as every
-        // group is past their symbols, and the last wavefront, when it is not G,
-        // parses the next task.
-        constexpr uint32_t kLoGrid = 1280;  // bytes of the level 0..3 grids (1184), rounded up
-        const uint32_t G1 = ((1u << h.log2W) + 63u) / 64u;
-        // (two or more lanes: a round writes whole bytes of symbol pairs)
-        const bool overlap = G1 < NT / 64 && h.log2W >= 1u && !h.big && h.t >= 3 && h.t <= 5 &&
-                             kLoGrid + words_bytes <= u_at && (sym_lds || sym_bytes + u_at + 160u <= stage_bytes);
-        if (overlap) {
-            const uint32_t wave = threadIdx.x >> 6;
-            uint16_t* const wl = (uint16_t*)(stage + kLoGrid);
-            uint8_t* const nl = sym_lds ? nib : stage + ((stage_bytes - sym_bytes) & ~15u);
-            if (threadIdx.x < 4) sh.prog[threadIdx.x] = 0;
-            const uint32_t x0 = rans_stage_words<NT>(P, h, wl);
-            __syncthreads();
-            const uint32_t last = h.t >= 5 ? 3u : 2u;
-            const uint32_t need = h.sym_end[last];
-            if (wave < G1) {
-                rans_rounds<NT>(P, sh, tab, wl, nl, x0, need ? need : 1u);
-            } else if (wave == G1) {
-                // bounded: every group publishes ~0 when its rounds end
-                for (uint32_t g = 0; g < G1; ++g)
-                    while (__hip_atomic_load(&sh.prog[g], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < need)
-                        __builtin_amdgcn_s_sleep(1);
-                small_levels<uint16_t, false, true>(P, sh, make_store<uint16_t, false, false>(P, sh, slots_lds, scratch), nl, last);
-            } else if (threadIdx.x == NT - 64 && !ah.done) {
-                parse_ahead(P, sh.hn, ah.jt);
-                ah.done = true;
-            }
-            __syncthreads();
-            if (!sym_lds) {
-                const uint32_t nw = ((h.nsym + 1u) / 2u + 3u) / 4u;
-                for (uint32_t q = threadIdx.x; q < nw; q += NT) ((uint32_t*)nib)[q] = ((const uint32_t*)nl)[q];
-            }
-            small_upto = (int)last;
-        } else if (sym_lds && words_bytes <= nl_at) rans_decode_lds<NT>(P, sh, tab, stage, nib, nullptr);
-        else if (!sym_lds && words_bytes + sym_bytes <= stage_bytes)
-            rans_decode_lds<NT>(P, sh, tab, stage, stage + words_bytes, nib);
-        else rans_decode<NT>(P, sh, tab, nib);
+    } else {
+        if (!sh.tab_ok) {
+            const uint4* src = (const uint4*)P.rans_tab;
+            for (uint32_t w = threadIdx.x; w < kRansM / 4; w += NT) ((uint4*)(lds + o_tab))[w] = src[w];
+        }
+        if (threadIdx.x < 4) sh.prog[threadIdx.x] = 0;
+        if (fits) x0 = rans_stage_words<NT>(P, h, (uint16_t*)(lds + o_words));
         __syncthreads();
     }
-    // level 5 of a fast-path task overwrites the table
-    const bool tab_lost = !h.big && !h.c5g && h.t >= 5;
-    if (!sh.err) {
-        if (h.big) run_levels<NT, uint32_t, true, false>(P, sh, slots_lds, scratch, nib, ah, small_upto);
-        else if (h.c5g) run_levels<NT, uint16_t, false, true>(P, sh, slots_lds, scratch, nib, ah, small_upto);
-        else run_levels<NT, uint16_t, false, false>(P, sh, slots_lds, scratch, nib, ah, small_upto);
+    // step 0 decodes the symbols; step 1 levels 0..3, on one wavefront, while lane
+    // 0 of the last wavefront parses the next task; with overlap both in step 1
+#pragma nounroll
+    for (uint32_t step = rans && !overlap ? 0u : 1u; step < 2u; ++step) {
+        const uint32_t* const tab = (const uint32_t*)(lds + o_tab);
+        if (fits && (step == 0u || wave < (overlap ? G : 0u))) {
+            rans_rounds<NT>(P, sh, tab, (const uint16_t*)(lds + o_words), lds + o_sym, x0, overlap ? max(need, 1u) : 0u);
+        } else if (step == 0u) {
+            rans_decode<NT>(P, sh, tab, nib);
+        } else if (wave == (overlap ? G : 0u)) {
+            // bounded: every group publishes ~0 when its rounds end
+            if (overlap)
+                for (uint32_t g = 0; g < G; ++g)
+                    while (__hip_atomic_load(&sh.prog[g], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < need)
+                        __builtin_amdgcn_s_sleep(1);
+            small_levels(sh, sym, small);
+        } else if (threadIdx.x == NT - 64 && !ah.done) {
+            parse_ahead(P, sh.hn, ah.jt);
+            ah.done = true;
+        }
+        __syncthreads();
+    }
+    // (sh.err is not written again before the next barrier)
+    bool ok = !sh.err;
+    if (ok) {
+        if (fits && (h.t > 4 || o_sym < (uint32_t)sizeof(Shared))) {  // not clear of the grids and slots
+            for (uint32_t q = threadIdx.x; q < n_words; q += NT) ((uint32_t*)nib)[q] = sym[q];
+            sym = (const uint32_t*)nib;
+            __syncthreads();
+        }
+        uint16_t* c5g = nullptr;
+        bool labels;
+        ok = decode_levels<NT>(P, sh, u_area, slots, scratch, sym, c5g, labels);
+        if (ok && labels) write_output<NT>(P, sh, u_area, u_bytes, slots, c5g);
     }
     __syncthreads();
-    if (sh.err) {
+    if (!ok) {
         if (threadIdx.x == 0) sh.h.status = kTaskCorrupt;
         zero_output<NT>(P, h);
     }
     // (read again only after the task loop's next barriers)
-    if (threadIdx.x == 0) sh.tab_ok = tab_lost ? 0u : tab_used ? 1u : sh.tab_ok;
+    if (threadIdx.x == 0) sh.tab_ok = h.t >= 5 ? 0u : rans ? 1u : sh.tab_ok;
 }
 
 // at least 4 waves per SIMD: 128 VGPRs per lane at most
@@ -1317,7 +1410,6 @@ template <int NT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) decode_kernel(Params P) {
     extern __shared__ uint8_t dyn_smem[];
     Shared& sh = *reinterpret_cast<Shared*>(dyn_smem);
-    uint16_t* slots_lds = reinterpret_cast<uint16_t*>(dyn_smem + sizeof(Shared));
     const uint32_t tid = threadIdx.x;
     uint8_t* scratch = P.scratch + (uint64_t)blockIdx.x * P.scratch_stride;
     // lane 0 of the last wavefront claims and parses the next task while the
@@ -1342,7 +1434,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
             ah.jt = P.queue && ah.jt < P.n_tasks ? atomicAdd(P.queue, 1u) : P.n_tasks;
             ah.done = false;
         }
-        decode_task<NT>(P, sh, slots_lds, scratch, ah);
+        decode_task<NT>(P, dyn_smem, scratch, ah);
         if (tid == PT && !ah.done) {
             parse_ahead(P, sh.hn, ah.jt);
             ah.done = true;
@@ -1512,7 +1604,10 @@ __global__ void __launch_bounds__(1024) dense_offsets_kernel(Params P, uint64_t*
 }
 
 // ------------------------------------------------------------ host launch
-size_t shared_bytes(uint32_t cap16) { return sizeof(Shared) + 2ull * (cap16 < kMinCap16 ? kMinCap16 : cap16); }
+size_t shared_bytes(uint32_t cap16) {
+    const uint32_t c = cap16 < kMinCap16 ? kMinCap16 : cap16;
+    return sizeof(Shared) + list_bytes(c) + 2ull * c;
+}
 
 template <int NT>
 static hipError_t launch_nt(const Params& P, uint32_t grid, hipStream_t s) {
