@@ -102,6 +102,10 @@ static_assert(offsetof(Shared, G) + sizeof(Shared::G) == sizeof(Shared),
 
 // ------------------------------------------------------ wave/block helpers
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
+// a value that is the same in every lane of the wavefront, in a scalar register
+__device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uni64(uint64_t v) { return ((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v); }
+__device__ __forceinline__ uint32_t wave_id() { return uni(threadIdx.x >> 6); }
 
 __device__ __forceinline__ uint32_t mbcnt(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -279,15 +283,15 @@ __device__ __forceinline__ void parse_ahead(const Params& P, TaskHdr& hn, uint32
 template <int NT>
 __device__ __forceinline__ void rans_decode(const Params& P, Shared& sh, const uint32_t* tab, uint8_t* nib) {
     const TaskHdr& h = sh.h;
-    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
-    const uint32_t W = 1u << h.log2W, G = (W + 63) / 64, lanes = W < 64 ? W : 64;
-    const uint32_t nsym = h.nsym;
-    const uint16_t* words = (const uint16_t*)(P.vol + h.pay_off);
-    const uint32_t* states = (const uint32_t*)(P.vol + h.states_off);
+    const uint32_t lane = lane_id(), wave = wave_id();
+    const uint32_t W = 1u << uni(h.log2W), G = (W + 63) / 64, lanes = W < 64 ? W : 64;
+    const uint32_t nsym = uni(h.nsym);
+    const uint16_t* words = (const uint16_t*)(P.vol + uni64(h.pay_off));
+    const uint32_t* states = (const uint32_t*)(P.vol + uni64(h.states_off));
     for (uint32_t g = wave; g < G; g += NT / 64) {
         const bool active = lane < lanes;
         const uint32_t gl = 64 * g + lane;
-        const uint32_t gcount = h.gw[g], gbase = h.gstart[g];
+        const uint32_t gcount = uni(h.gw[g]), gbase = uni(h.gstart[g]);
         uint32_t x = active ? states[gl] : 0u;
         uint32_t wbase = 0;
         uint32_t win0 = lane < gcount ? words[gbase + lane] : 0u;
@@ -345,11 +349,11 @@ __device__ __forceinline__ void rans_decode(const Params& P, Shared& sh, const u
 // thread's state for its wavefront's first lane group.
 template <int NT>
 __device__ __forceinline__ uint32_t rans_stage_words(const Params& P, const TaskHdr& h, uint16_t* wl) {
-    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const uint32_t W = 1u << h.log2W, G = (W + 63) / 64, lanes = W < 64 ? W : 64;
-    const uint32_t tw = h.gstart[G - 1] + h.gw[G - 1];
-    const uint16_t* const wg = (const uint16_t*)(P.vol + h.pay_off);
-    const uint32_t* states = (const uint32_t*)(P.vol + h.states_off);
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+    const uint32_t W = 1u << uni(h.log2W), G = (W + 63) / 64, lanes = W < 64 ? W : 64;
+    const uint32_t tw = uni(h.gstart[G - 1]) + uni(h.gw[G - 1]);
+    const uint16_t* const wg = (const uint16_t*)(P.vol + uni64(h.pay_off));
+    const uint32_t* states = (const uint32_t*)(P.vol + uni64(h.states_off));
     const uint32_t x0 = wave < G && lane < lanes ? states[64 * wave + lane] : 0u;
     for (uint32_t q = tid; q < tw / 2u; q += NT) ((uint32_t*)wl)[q] = ((const uint32_t*)wg)[q];
     if ((tw & 1u) && tid == 0) wl[tw - 1u] = wg[tw - 1u];
@@ -362,40 +366,59 @@ __device__ __forceinline__ uint32_t rans_stage_words(const Params& P, const Task
 // w, w + NW, ...  With `mark`, lane 0 publishes in sh.prog[g], with release
 // order, that group g's symbols below index `mark` are out as soon as they are
 // (its next round would start at or past `mark`), and ~0 when the group is done.
+// A round is a serial chain (table, multiply, ballot, word, next state), so what
+// counts is its length: a full round of 64 lanes has no lane checks, and a
+// group that consumes more words than it has is found out at its end (the word
+// index is held inside the staged words plus one round).
 template <int NT>
 __device__ __forceinline__ void rans_rounds(const Params& P, Shared& sh, const uint32_t* tab, const uint16_t* wl,
                                             uint8_t* nl, uint32_t x0, uint32_t mark) {
     const TaskHdr& h = sh.h;
-    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
-    const uint32_t W = 1u << h.log2W, G = (W + 63) / 64, lanes = W < 64 ? W : 64;
-    const uint32_t nsym = h.nsym;
-    const uint32_t* states = (const uint32_t*)(P.vol + h.states_off);
-    for (uint32_t g = wave; g < G; g += NT / 64) {
-        const bool active = lane < lanes;
-        const uint32_t gcount = h.gw[g], gbase = h.gstart[g];
-        uint32_t x = g == wave ? x0 : active ? states[64 * g + lane] : 0u;
-        uint32_t gpos = 0, pend = 0;
-        const uint32_t gcm1 = gcount ? gcount - 1u : 0u;  // word reads stay inside the group
-        bool bad = false, marked = mark == 0;
+    const uint32_t lane = lane_id(), wave = wave_id();
+    const uint32_t W = 1u << uni(h.log2W), G = (W + 63) / 64, lanes = W < 64 ? W : 64;
+    const uint32_t nsym = uni(h.nsym);
+    const uint32_t* states = (const uint32_t*)(P.vol + uni64(h.states_off));
+    for (uint32_t g = uni(wave); g < G; g += NT / 64) {
+        const uint32_t gcount = uni(h.gw[g]), gbase = uni(h.gstart[g]);
+        uint32_t x = g == wave ? x0 : lane < lanes ? states[64 * g + lane] : 0u;
+        uint32_t gpos = 0, pend = 0, r0 = 64 * g;
+        bool marked = mark == 0;
+        auto publish = [&] {
+            if (!marked && r0 + W >= mark) {
+                marked = true;
+                if (lane == 0) __hip_atomic_store(&sh.prog[g], mark, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        };
         __builtin_amdgcn_s_waitcnt(0);
-        // a round without branches: every lane looks its state up and reads a
-        // word; a lane past the symbols keeps its state
-        for (uint32_t r0 = 64 * g; r0 < nsym; r0 += W) {
+        if (W >= 64) {
+            for (; r0 + 64u <= nsym; r0 += W) {
+                const uint32_t e = tab[x & (kRansM - 1)];
+                const uint32_t xd = ((e >> 4) & 0x1FFFu) * (x >> kRansBits) + (e >> 17);
+                const bool need = xd < kRansL;
+                const uint64_t m = __ballot(need);
+                uint32_t wv = wl[gbase + min(gpos, gcount) + mbcnt(m)];
+                asm volatile("" : "+v"(wv));  // (read by every lane: a branch around the read costs more)
+                x = need ? ((xd << 16) | wv) : xd;
+                gpos += (uint32_t)__popcll(m);
+                // two consecutive symbols per byte
+                const uint32_t s = e & 15u, hi = dpp<0xB1>(0u, s);  // quad_perm [1,0,3,2]: the pair partner
+                if (!(lane & 1u)) nl[(r0 >> 1) + (lane >> 1)] = (uint8_t)(s | (hi << 4));
+                publish();
+            }
+        }
+        for (; r0 < nsym; r0 += W) {
             const uint32_t j = r0 + lane;
-            const bool act = active && j < nsym;
+            const bool act = lane < lanes && j < nsym;
             const uint32_t e = tab[x & (kRansM - 1)];
             const uint32_t s = e & 15u;
             const uint32_t xd = ((e >> 4) & 0x1FFFu) * (x >> kRansBits) + (e >> 17);
             const bool need = act && xd < kRansL;
             const uint64_t m = __ballot(need);
-            const uint32_t widx = gpos + mbcnt(m);
-            const uint32_t wv = wl[gbase + min(widx, gcm1)];
-            bad = bad || (need && widx >= gcount);
+            const uint32_t wv = wl[gbase + min(gpos, gcount) + mbcnt(m)];
             x = need ? ((xd << 16) | wv) : act ? xd : x;
             gpos += (uint32_t)__popcll(m);
-            // two consecutive symbols per byte
             if (W >= 2) {
-                const uint32_t hi = dpp<0xB1>(0u, s);  // quad_perm [1,0,3,2]: the pair partner
+                const uint32_t hi = dpp<0xB1>(0u, s);
                 if (act && !(lane & 1)) nl[j >> 1] = (uint8_t)(s | (j + 1 < nsym ? hi << 4 : 0u));
             } else if (lane == 0) {
                 if (!(j & 1)) {
@@ -405,12 +428,9 @@ __device__ __forceinline__ void rans_rounds(const Params& P, Shared& sh, const u
                     nl[j >> 1] = (uint8_t)(pend | (s << 4));
                 }
             }
-            if (!marked && r0 + W >= mark) {
-                marked = true;
-                if (lane == 0) __hip_atomic_store(&sh.prog[g], mark, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
+            publish();
         }
-        if (__ballot(bad) && lane == 0) atomicOr(&sh.err, 1u);
+        if (gpos > gcount && lane == 0) atomicOr(&sh.err, 1u);
         if (mark && lane == 0) __hip_atomic_store(&sh.prog[g], 0xFFFFFFFFu, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 }
@@ -462,9 +482,9 @@ __device__ __forceinline__ void store2(LT* o, LT a, LT b, bool vec) {
 
 template <int NT>
 __device__ __forceinline__ void zero_output(const Params& P, const TaskHdr& h) {
-    const uint32_t t = h.t;
+    const uint32_t t = uni(h.t);
     const uint64_t unit = P.pal_bits ? 4u : P.label_bytes;
-    uint8_t* out = P.out + h.out_off * unit;
+    uint8_t* out = P.out + uni64(h.out_off) * unit;
     const uint64_t bytes = out_units(1ull << (3 * t), P.pal_bits) * unit;
     if (((uintptr_t)out & 15u) == 0 && (bytes & 15u) == 0) {
         for (uint64_t u = threadIdx.x; u < bytes / 16; u += NT) ((uint4*)out)[u] = make_uint4(0, 0, 0, 0);
@@ -513,11 +533,16 @@ __device__ __forceinline__ uint32_t level_prefix(uint2* ep, uint32_t words) {
 // q is the state before symbol q (up to the parity).
 constexpr uint32_t kNib = 0x11111111u;  // bit 4q <-> symbol q of a word ("nibble mask")
 
-// nibble mask of the symbols whose low 3 bits equal c (c given in every nibble)
-__device__ __forceinline__ uint32_t nib_eq(uint32_t lo3, uint32_t c) {
-    const uint32_t t = lo3 ^ c;
-    return ~(t | (t >> 1) | (t >> 2)) & kNib;
-}
+// nibble masks of a word's symbols by operation code (4 ADV, 5 LAST, 6 DELTA, 7 invalid)
+// and bit 3; other bits of the masks are arbitrary
+struct Planes {
+    uint32_t b0, b1, b2, b3;
+    __device__ __forceinline__ explicit Planes(uint32_t w) : b0(w), b1(w >> 1), b2(w >> 2), b3(w >> 3) {}
+    __device__ __forceinline__ uint32_t adv() const { return b2 & ~(b1 | b0); }
+    __device__ __forceinline__ uint32_t last() const { return b2 & ~b1 & b0; }
+    __device__ __forceinline__ uint32_t delta() const { return b2 & b1 & ~b0; }
+    __device__ __forceinline__ uint32_t bad() const { return b2 & b1 & b0; }
+};
 
 struct WordRun {
     uint32_t A, B, par;  // carry chain; inclusive parity of the inversions
@@ -527,8 +552,8 @@ struct WordRun {
 };
 
 // V: the symbols of the word that belong to the level; the others keep the state
-__device__ __forceinline__ WordRun word_run(uint32_t word, uint32_t V) {
-    const uint32_t D = nib_eq(word & 0x77777777u, 0x66666666u), C = word >> 3;
+__device__ __forceinline__ WordRun word_run(const Planes& pl, uint32_t V) {
+    const uint32_t D = pl.delta(), C = pl.b3;
     const uint32_t set = D & C & V, rst = ~(D | C) & V;
     uint32_t p = D & ~C & V;
     p ^= p << 4;
@@ -558,11 +583,13 @@ struct RunState {
     uint32_t adv;    // PALETTE_ADV operations so far, all levels
 };
 
-// slot values: a final palette index, or an operation that copies (its code, 0..3)
+// slot values: a final palette index, or an operation that copies (its code, 0..3).
+// 16-bit slots hold 15-bit indices (13 with a stop bit: levels up to 4), 32-bit
+// slots 21 bits (a 64^3 brick has fewer than 2^19 nodes).
 template <bool W32>
 struct SlotBits {
-    static constexpr uint32_t kFinal = W32 ? 0x80000000u : 0x8000u;
-    static constexpr uint32_t kStop = W32 ? 0x40000000u : 0x4000u;
+    static constexpr uint32_t kFinal = W32 ? 0x800000u : 0x8000u;
+    static constexpr uint32_t kStop = W32 ? 0x400000u : 0x4000u;
 };
 
 // One pass over words [w_at, w_at + nw) of a level with symbols [s0, s1): every
@@ -580,7 +607,7 @@ __device__ __forceinline__ bool ops_pass(Shared& sh, const uint32_t* sym, uint32
                                          RunState& rs, uint32_t& pbuf, bool& bad) {
     constexpr uint32_t NW = NT / 64;
     constexpr uint32_t FIN = SlotBits<W32>::kFinal, STP = SlotBits<W32>::kStop;
-    const uint32_t tid = threadIdx.x & (NT - 1), wave = tid >> 6;
+    const uint32_t tid = threadIdx.x & (NT - 1), wave = NW == 1 ? 0u : wave_id();
     const uint32_t w_last = (s1 - 1u) >> 3, w_end = w_at + nw, w0 = w_at + (tid << lr), R = 1u << lr;
     // the thread's words and the one after them (delta entries), at clamped indices
     uint32_t W[5];
@@ -594,17 +621,21 @@ __device__ __forceinline__ bool ops_pass(Shared& sh, const uint32_t* sym, uint32
     auto valid = [&](uint32_t r) -> uint32_t { return w0 + r < w_end ? word_valid(w0 + r, s0, s1) : 0u; };
     const bool wave_on = w_at + ((64u * wave) << lr) < w_end;
     uint32_t n0 = 0, n1 = 0, i0 = 0, i1 = 0, x0 = 0, x1 = 1;  // counts, their scans, the wave's exit states
+    uint32_t O0[4], O1[4];                                     // the words' operations (nibble masks)
     uint64_t m0 = 0, m1 = 0;                                   // the lanes' entry states
     if (wave_on) {
         uint32_t e0 = 0, e1 = 1;
 #pragma unroll
         for (uint32_t r = 0; r < 4; ++r) {
             if (r < R) {
-                const uint32_t V = valid(r), advm = nib_eq(W[r] & 0x77777777u, 0x44444444u);
-                const WordRun wr = word_run(W[r], V);
-                const uint32_t o0 = V & ~wr.entries(e0), o1 = V & ~wr.entries(e1);
-                n0 += (uint32_t)__popc(o0) | ((uint32_t)__popc(o0 & advm) << 16);
-                n1 += (uint32_t)__popc(o1) | ((uint32_t)__popc(o1 & advm) << 16);
+                const uint32_t V = valid(r);
+                const Planes pl(W[r]);
+                const WordRun wr = word_run(pl, V);
+                const uint32_t advm = pl.adv();
+                O0[r] = V & ~wr.entries(e0);
+                O1[r] = V & ~wr.entries(e1);
+                n0 += (uint32_t)__popc(O0[r]) | ((uint32_t)__popc(O0[r] & advm) << 16);
+                n1 += (uint32_t)__popc(O1[r]) | ((uint32_t)__popc(O1[r] & advm) << 16);
                 e0 = wr.exit(e0);
                 e1 = wr.exit(e1);
             }
@@ -660,50 +691,56 @@ __device__ __forceinline__ bool ops_pass(Shared& sh, const uint32_t* sym, uint32
     rs = RunState{st, k, adv};
     if (k > expected) return false;
     if (!wave_on) return true;
-    uint32_t e = lane_bit(my_st ? m1 : m0);
+    const uint32_t e = lane_bit(my_st ? m1 : m0);
     const uint32_t excl = (my_st ? i1 : i0) - (e ? n1 : n0);
     uint32_t kk = my_k - kbase + (excl & 0xFFFFu), aa = my_adv + (excl >> 16);
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r)
+        if (r < R) O0[r] = e ? O1[r] : O0[r];
+#pragma nounroll
     for (uint32_t r = 0; r < R; ++r) {
-        const uint32_t word = W[0], V = valid(r), lo3 = word & 0x77777777u;
-        const WordRun wr = word_run(word, V);
-        const uint32_t opm = V & ~wr.entries(e), advm = opm & nib_eq(lo3, 0x44444444u);
-        e = wr.exit(e);
-        bad = bad || (opm & nib_eq(lo3, 0x77777777u));
-        uint32_t kq = kk, aq = aa;
+        const uint32_t word = W[0], opm = O0[0];
+        const Planes pl(word);
+        const uint32_t advm = opm & pl.adv();
+        bad = bad || (opm & pl.bad());
+        // Slot of symbol q, by nibbles: a copy's code, or for a palette operation
+        // its distance from the palette index before the word's first ADV (the
+        // ADVs before it, less one for LAST, plus one) with the base aa - 1 added
+        const uint32_t pal = pl.b2 & kNib, pal15 = (pal << 4) - pal;
+        const uint32_t off = (advm * 0x11111110u) + (kNib & ~pl.last());
+        const uint32_t nibs = (off & pal15) | (word & 0x33333333u & ~pal15), base = FIN | (aa - 1u);
+        SLOT* at = slot + kk;
 #pragma unroll
         for (uint32_t q = 0; q < 8; ++q) {
             if ((opm >> (4 * q)) & 1u) {
-                const uint32_t op = (word >> (4 * q)) & 7u;
-                uint32_t v = op < 4u ? op : FIN | (aq - min(op - 4u, 1u));  // (back references: below)
-                if (STOP) v |= ((word >> (4 * q + 3)) & 1u) ? STP : 0u;
-                slot[kq] = (SLOT)v;
-                kq += 1u;
-                aq += (advm >> (4 * q)) & 1u;
+                uint32_t v = __umul24((pal >> (4 * q)) & 1u, base) + ((nibs >> (4 * q)) & 15u);
+                if (STOP) v += __umul24((word >> (4 * q + 3)) & 1u, STP);
+                *at++ = (SLOT)v;
             }
         }
         // back references: the entries that follow, in the word, the next word, or (rarely) beyond
-        for (uint32_t m = opm & nib_eq(lo3, 0x66666666u); m; m &= m - 1u) {
+        for (uint32_t m = opm & pl.delta(); m; m &= m - 1u) {
             const uint32_t b = (uint32_t)__builtin_ctz(m), below = (1u << b) - 1u;
             const uint32_t a = aa + (uint32_t)__popc(advm & below);
-            uint64_t win = ((((uint64_t)W[1]) << 32) | word) >> b;
-            uint32_t d = 0, left = 15u - (b >> 2), j = 8u * (w0 + r) + (b >> 2), en;
-            do {
-                ++j;
-                if (left) {
-                    win >>= 4;
-                    en = (uint32_t)win & 15u;
-                    --left;
-                } else {
-                    en = j < s1 ? (sym[j >> 3] >> (4u * (j & 7u))) & 15u : 0u;
+            uint32_t win = (uint32_t)(((((uint64_t)W[1]) << 32) | word) >> (b + 4u));  // the next entries: 8 at least
+            uint32_t en = win & 15u, d = en & 7u, j = 8u * (w0 + r) + (b >> 2) + 1u, left = 7u;
+            while (en & 8u) {
+                if (++j >= s1) break;  // (the chain leaves the level: its end state says so)
+                win >>= 4;
+                if (left == 0u) {
+                    win = sym[j >> 3] >> (4u * (j & 7u));
+                    left = 8u - (j & 7u);
                 }
+                --left;
+                en = win & 15u;
                 d = d >= (1u << 29) ? 0xFFFFFFFFu : ((d << 3) | (en & 7u));
-            } while ((en & 8u) && j < s1);
-            if (d == 0u || d > a) {
+            }
+            if (d - 1u >= a) {
                 bad = true;
                 d = a;
             }
             uint32_t v = FIN | (a - d);
-            if (STOP) v |= ((word >> (b + 3u)) & 1u) ? STP : 0u;
+            if (STOP) v += __umul24((word >> (b + 3u)) & 1u, STP);
             slot[kk + (uint32_t)__popc(opm & below)] = (SLOT)v;
         }
         kk += (uint32_t)__popc(opm);
@@ -712,6 +749,9 @@ __device__ __forceinline__ bool ops_pass(Shared& sh, const uint32_t* sym, uint32
         W[1] = W[2];
         W[2] = W[3];
         W[3] = W[4];
+        O0[0] = O0[1];
+        O0[1] = O0[2];
+        O0[2] = O0[3];
     }
     return true;
 }
@@ -731,16 +771,23 @@ __device__ __forceinline__ bool ops_level(Shared& sh, const uint32_t* sym, uint3
                 return false;
     }
     adv = rs.adv;
-    return rs.k == expected && rs.state == 0u && adv <= sh.h.pc;
+    return rs.k == expected && rs.state == 0u && adv <= uni(sh.h.pc);
 }
 
 // -------------------------------------------------------- operations to values
-// The 8 children of one expanding parent: op(c) is child c's slot as ops_pass
-// left it (without its stop bit), pv the parent's value, ext(axis, c) the value
-// of (or a reference to) the node beside child c across the parent's lower
-// face; inv[axis]: there is no such node.  A copy from a sibling takes the
-// sibling's value, which may be a reference itself.
-template <uint32_t FIN, typename OP, typename EXT>
+// A level's values: in 16-bit slots a palette index, or with the top bit
+// (kOpen) set a reference to the slot of a node before it whose value it takes.
+// (So a value is used without masking, and a test for its sign finds what is
+// open.)  A row of slots as ops_pass leaves it, with the top bits inverted, has
+// the palette operations final and the copies open.
+constexpr uint32_t kOpen = 0x8000u;
+
+// The 8 children of one expanding parent: op(c) is child c's operation (open:
+// its code in the low bits, else the palette index), pv the parent's value,
+// ext(axis, c) the value of (or a reference to) the node beside child c across
+// the parent's lower face; inv[axis]: there is no such node.  A copy from a
+// sibling takes the sibling's value, which may be a reference itself.
+template <uint32_t OPEN, typename OP, typename EXT>
 __device__ __forceinline__ void resolve8(uint32_t v[8], OP op, uint32_t pv, EXT ext, const bool inv[3], bool& bad) {
 #pragma unroll
     for (uint32_t c = 0; c < 8; ++c) {
@@ -748,7 +795,7 @@ __device__ __forceinline__ void resolve8(uint32_t v[8], OP op, uint32_t pv, EXT 
         uint32_t r = pv;
 #pragma unroll
         for (uint32_t a = 0; a < 3; ++a) {
-            const bool is = o == a + 1u;
+            const bool is = o == (OPEN | (a + 1u));
             if (c & (1u << a)) {
                 r = is ? v[c ^ (1u << a)] : r;
             } else {
@@ -756,10 +803,14 @@ __device__ __forceinline__ void resolve8(uint32_t v[8], OP op, uint32_t pv, EXT 
                 bad = bad || (is && inv[a]);
             }
         }
-        v[c] = (o & FIN) ? o : r;
+        v[c] = (o & OPEN) ? r : o;
     }
 }
 
+__device__ __forceinline__ uint4 flip8(const uint4& w) {
+    constexpr uint32_t m = kOpen * 0x10001u;
+    return make_uint4(w.x ^ m, w.y ^ m, w.z ^ m, w.w ^ m);
+}
 __device__ __forceinline__ uint4 pack8(const uint32_t v[8]) {
     return make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
 }
@@ -779,20 +830,20 @@ __device__ __forceinline__ uint32_t node_below(uint32_t q, uint32_t am) {
 // source in Morton order, so chains end.
 __device__ __forceinline__ void chase8(const uint16_t* base, uint4* at) {
     const uint4 w = *at;
-    if ((w.x & w.y & w.z & w.w & 0x80008000u) == 0x80008000u) return;
-    uint32_t v[8];
+    if (!((w.x | w.y | w.z | w.w) & (kOpen * 0x10001u))) return;
+    int32_t v[8], low;  // sign-extended: open slots are negative
 #pragma unroll
-    for (uint32_t c = 0; c < 8; ++c) v[c] = half_of(w, c);
-    uint32_t all;
+    for (uint32_t c = 0; c < 8; ++c) v[c] = (int16_t)half_of(w, c);
     do {
-        all = 0x8000u;
 #pragma unroll
-        for (uint32_t c = 0; c < 8; ++c) {
-            if (!(v[c] & 0x8000u)) v[c] = base[v[c]];
-            all &= v[c];
-        }
-    } while (!all);
-    *at = pack8(v);
+        for (uint32_t c = 0; c < 8; ++c)
+            if (v[c] < 0) v[c] = ((const int16_t*)base)[v[c] + (int32_t)kOpen];
+        low = min(min(min(v[0], v[1]), min(v[2], v[3])), min(min(v[4], v[5]), min(v[6], v[7])));
+    } while (low < 0);
+    uint32_t u[8];
+#pragma unroll
+    for (uint32_t c = 0; c < 8; ++c) u[c] = (uint32_t)v[c];
+    *at = pack8(u);
 }
 
 // ------------------------------------------------------------- full levels
@@ -805,14 +856,14 @@ template <int NT>
 __device__ __forceinline__ bool full_level(Shared& sh, const uint32_t* sym, uint32_t i, uint32_t nexp, uint32_t& adv,
                                            uint32_t& pbuf) {
     constexpr uint32_t PP = NT >= 512 ? 1u : NT == 64 ? 1u : 512u / NT;  // parents per thread (level 4; NT = 64: levels 1..3)
-    constexpr uint32_t FIN = SlotBits<false>::kFinal, STP = SlotBits<false>::kStop;
+    constexpr uint32_t STP = SlotBits<false>::kStop;
     const uint32_t tid = threadIdx.x & (NT - 1);
     uint16_t* const grid = sh.G + fbase(i);
     const uint16_t* const par = sh.G + fbase(i - 1);
     const uint2* const ep = sh.EP + ebase(i - 1);
     const uint32_t np = 1u << (3 * (i - 1));
     bool bad = false;
-    if (!ops_level<NT, true>(sh, sym, sh.h.sym_end[i - 1], sh.h.sym_end[i], 8u * nexp, grid, adv, pbuf, bad)) return false;
+    if (!ops_level<NT, true>(sh, sym, uni(sh.h.sym_end[i - 1]), uni(sh.h.sym_end[i]), 8u * nexp, grid, adv, pbuf, bad)) return false;
     lsync<NT>();
     uint4 raw[PP];
     bool ex[PP];
@@ -842,13 +893,18 @@ __device__ __forceinline__ bool full_level(Shared& sh, const uint32_t* sym, uint
                     const uint32_t am = mx << a, tq = node_below(q, am);
                     inv[a] = !(q & am);
                     const bool te = !inv[a] && ep_bit(ep[tq >> 5], tq);
-                    eb[a] = te ? 8u * tq : par[tq];
+                    eb[a] = te ? kOpen | (8u * tq) : par[tq];
                     ea[a] = te ? 7u : 0u;
                 }
-                resolve8<FIN>(v, [&](uint32_t c) { return half_of(raw[p], c) & ~STP; }, pv,
-                              [&](uint32_t a, uint32_t c) { return eb[a] + ((c | (1u << a)) & ea[a]); }, inv, bad);
-#pragma unroll
-                for (uint32_t c = 0; c < 8; ++c) bits |= (half_of(raw[p], c) & STP) ? 0u : 1u << c;
+                const uint4 w = raw[p];
+                const uint32_t keep = ~(STP * 0x10001u);
+                const uint4 ops = flip8(make_uint4(w.x & keep, w.y & keep, w.z & keep, w.w & keep));
+                resolve8<kOpen>(v, [&](uint32_t c) { return half_of(ops, c); }, pv,
+                              [&](uint32_t a, uint32_t c) { return eb[a] | ((c | (1u << a)) & ea[a]); }, inv, bad);
+                // (stop bits: children 0, 2, 4, 6 in the low halves, 1, 3, 5, 7 in the high ones)
+                const uint32_t m = ((w.x >> 14) & 0x10001u) | ((w.y >> 12) & 0x40004u) | ((w.z >> 10) & 0x100010u) |
+                                   ((w.w >> 8) & 0x400040u);
+                bits = ~(m | (m >> 15)) & 0xFFu;
             } else {
 #pragma unroll
                 for (uint32_t c = 0; c < 8; ++c) v[c] = pv;
@@ -873,12 +929,12 @@ __device__ __forceinline__ bool full_level(Shared& sh, const uint32_t* sym, uint
 // PALETTE_ADV (entry 0), with or without a stop bit.
 __device__ __forceinline__ void small_levels(Shared& sh, const uint32_t* sym, uint32_t last) {
     const uint32_t s0 = sym[0] & 15u;
-    if (sh.h.sym_end[0] != 1u || (s0 & 7u) != kAdv || sh.h.pc == 0u) {
+    if (uni(sh.h.sym_end[0]) != 1u || (s0 & 7u) != kAdv || uni(sh.h.pc) == 0u) {
         sh.err = 1u;
         return;
     }
     if (lane_id() == 0) {
-        sh.G[fbase(0)] = 0x8000u;
+        sh.G[fbase(0)] = 0u;
         sh.EP[ebase(0)] = make_uint2(s0 & 8u ? 0u : 1u, 0u);
     }
     lsync<64>();
@@ -902,11 +958,11 @@ __device__ __forceinline__ void small_levels(Shared& sh, const uint32_t* sym, ui
 // Level 5 of a 32^3 cube at full resolution: its explicit nodes by operation
 // rank in the slot area (child c of the r-th expanding parent at 8r + c).
 template <int NT>
-__device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t* c5, uint16_t* list, uint32_t nexp,
-                                       uint32_t& adv, uint32_t& pbuf) {
-    constexpr uint32_t FIN = SlotBits<false>::kFinal;
+__device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t* c5, uint8_t* u_area, uint32_t nexp,
+                                       uint32_t pal_words, const uint32_t* pal, uint32_t& adv, uint32_t& pbuf) {
     const uint2* const ep = sh.EP + ebase(4);
     const uint16_t* const par = sh.G + fbase(4);
+    uint16_t* const list = (uint16_t*)u_area;
     // the expanding parents by rank: each thread lists those of some bytes of the bitmap
     for (uint32_t b = threadIdx.x; b < 512u; b += NT) {
         const uint2 e = ep[b >> 2];
@@ -916,11 +972,11 @@ __device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t
             if ((bits >> c) & 1u) list[r++] = (uint16_t)(8u * b + c);
     }
     bool bad = false;
-    if (!ops_level<NT, false>(sh, sym, sh.h.sym_end[4], sh.h.sym_end[5], 8u * nexp, c5, adv, pbuf, bad)) return false;
+    if (!ops_level<NT, false>(sh, sym, uni(sh.h.sym_end[4]), uni(sh.h.sym_end[5]), 8u * nexp, c5, adv, pbuf, bad)) return false;
     __syncthreads();
     for (uint32_t r = threadIdx.x; r < nexp; r += NT) {
         const uint32_t q = list[r], pv = par[q];
-        const uint4 raw = ((const uint4*)c5)[r];
+        const uint4 raw = flip8(((const uint4*)c5)[r]);
         uint32_t eb[3], ea[3], v[8];
         bool inv[3];
 #pragma unroll
@@ -929,15 +985,17 @@ __device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t
             const uint2 e = ep[tq >> 5];
             inv[a] = !(q & am);
             const bool te = !inv[a] && ep_bit(e, tq);
-            eb[a] = te ? 8u * ep_rank(e, tq) : par[tq];
+            eb[a] = te ? kOpen | (8u * ep_rank(e, tq)) : par[tq];
             ea[a] = te ? 7u : 0u;
         }
-        resolve8<FIN>(v, [&](uint32_t c) { return half_of(raw, c); }, pv,
-                      [&](uint32_t a, uint32_t c) { return eb[a] + ((c | (1u << a)) & ea[a]); }, inv, bad);
+        resolve8<kOpen>(v, [&](uint32_t c) { return half_of(raw, c); }, pv,
+                      [&](uint32_t a, uint32_t c) { return eb[a] | ((c | (1u << a)) & ea[a]); }, inv, bad);
         ((uint4*)c5)[r] = pack8(v);
     }
     if (bad) sh.err = 1u;
     __syncthreads();
+    // the palette over the parent list, for the output pass
+    for (uint32_t w = threadIdx.x; w < pal_words; w += NT) ((uint32_t*)u_area)[w] = pal[w];
     for (uint32_t r = threadIdx.x; r < nexp; r += NT) chase8(c5, (uint4*)c5 + r);
     return true;
 }
@@ -952,7 +1010,7 @@ __device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t
 //   LABELS  the task's output, which holds the labels of all nodes before the
 //           chunk and of all implied nodes (fill_implied);
 //   else    the work-group's scratch (c5: the palette index by operation rank).
-constexpr uint32_t kChunkDone = 0x20000000u;  // slot: the result is where the low bits say (c5 rank, output voxel)
+constexpr uint32_t kChunkDone = 0x200000u;  // slot: the result is where the low bits say (c5 rank, output voxel)
 
 struct ChunkMem {
     uint2* ep5;      // level-5 bitmap (64^3 cubes), 1024 entries at the start of the slot area
@@ -967,19 +1025,19 @@ struct ChunkMem {
 __device__ __forceinline__ uint32_t value5(const Shared& sh, const ChunkMem& cm, uint32_t node) {
     const uint32_t q = node >> 3;
     const uint2 e = sh.EP[ebase(4) + (q >> 5)];
-    return ep_bit(e, q) ? (uint32_t)cm.c5[8u * ep_rank(e, q) + (node & 7u)] : (uint32_t)sh.G[fbase(4) + q] & 0x7FFFu;
+    return ep_bit(e, q) ? (uint32_t)cm.c5[8u * ep_rank(e, q) + (node & 7u)] : (uint32_t)sh.G[fbase(4) + q];
 }
 
 template <int NT, bool LABELS, typename LT>
 __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const ChunkMem& cm, const uint32_t* sym, uint32_t i,
                                             uint32_t nexp, uint32_t& adv, uint32_t& pbuf) {
-    constexpr uint32_t FIN = SlotBits<true>::kFinal, STP = SlotBits<true>::kStop;
-    const uint32_t tid = threadIdx.x, S = 1u << i, pc = sh.h.pc;
+    constexpr uint32_t OPEN = SlotBits<true>::kFinal, STP = SlotBits<true>::kStop;
+    const uint32_t tid = threadIdx.x, S = 1u << i, pc = uni(sh.h.pc);
     const LT* const pal = (const LT*)cm.pal;
     const uint2* const ep = i == 5 ? sh.EP + ebase(4) : cm.ep5;
     const uint16_t* const par4 = sh.G + fbase(4);
-    const bool with_bits = i == 5 && sh.h.t == 6;
-    LT* const out = (LT*)(P.out + sh.h.out_off * sizeof(LT));
+    const bool with_bits = i == 5 && uni(sh.h.t) == 6;
+    LT* const out = (LT*)(P.out + uni64(sh.h.out_off) * sizeof(LT));
     const bool vec = ((uintptr_t)out & (2 * sizeof(LT) - 1)) == 0;
     // expanding parents by rank
     const uint32_t nb = 1u << (3 * (i - 1) - 3);
@@ -991,7 +1049,7 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
     if (with_bits)
         for (uint32_t w = tid; w < 1024u; w += NT) cm.ep5[w].x = 0;
     __syncthreads();
-    const uint32_t s0 = sh.h.sym_end[i - 1], s1 = sh.h.sym_end[i], expected = 8u * nexp;
+    const uint32_t s0 = uni(sh.h.sym_end[i - 1]), s1 = uni(sh.h.sym_end[i]), expected = 8u * nexp;
     const uint32_t mx = 0x09249249u & ((1u << (3 * (i - 1))) - 1u);
     RunState rs{0u, 0u, adv};
     uint32_t r_next = 0;
@@ -1011,7 +1069,7 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
             bool inv[3], in[3], te[3];
 #pragma unroll
             for (uint32_t c = 0; c < 8; ++c) raw[c] = cm.buf[8u * x + c];
-            const uint32_t pv = FIN | (i == 5 ? (uint32_t)par4[q] & 0x7FFFu : value5(sh, cm, q));
+            const uint32_t pv = i == 5 ? (uint32_t)par4[q] : value5(sh, cm, q);
             const uint32_t vox = (compact3(q >> 2) * 2u * S + compact3(q >> 1) * 2u) * S + compact3(q) * 2u;  // child 0's
 #pragma unroll
             for (uint32_t a = 0; a < 3; ++a) {
@@ -1021,17 +1079,17 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
                 te[a] = !inv[a] && ep_bit(e, tq);
                 const uint32_t kt = 8u * ep_rank(e, tq);
                 in[a] = te[a] && kt >= kbase;
-                eb[a] = in[a] ? kt - kbase : kt;
-                if (!te[a] && i == 5) eb[a] = FIN | ((uint32_t)par4[tq] & 0x7FFFu);
+                eb[a] = in[a] ? OPEN | (kt - kbase) : kChunkDone | kt;
+                if (!te[a] && i == 5) eb[a] = par4[tq];
             }
             auto ext = [&](uint32_t a, uint32_t c) -> uint32_t {
                 const uint32_t ct = c | (1u << a);
                 if (!te[a] && i == 5) return eb[a];
-                if (!LABELS) return in[a] ? eb[a] + ct : FIN | kChunkDone | (eb[a] + ct);
+                if (!LABELS) return eb[a] | ct;
                 const uint32_t at = vox + ((c >> 2) * S + ((c >> 1) & 1u)) * S + (c & 1u) - (a == 0 ? 1u : a == 1 ? S : S * S);
-                return in[a] ? eb[a] + ct : inv[a] ? FIN : FIN | kChunkDone | at;
+                return in[a] ? eb[a] | ct : inv[a] ? 0u : kChunkDone | at;
             };
-            resolve8<FIN>(v, [&](uint32_t c) { return raw[c] & ~STP; }, pv, ext, inv, bad);
+            resolve8<OPEN>(v, [&](uint32_t c) { return (raw[c] & ~STP) ^ OPEN; }, pv, ext, inv, bad);
             if (with_bits) {
                 uint32_t bits = 0;
 #pragma unroll
@@ -1046,17 +1104,17 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
         __syncthreads();
         for (uint32_t x = tid; x < n_par; x += NT) {
             const uint32_t q = cm.list[r_next + x];
-            uint32_t v[8], all;
+            uint32_t v[8], open;
 #pragma unroll
             for (uint32_t c = 0; c < 8; ++c) v[c] = cm.buf[8u * x + c];
             do {
-                all = FIN;
+                open = 0;
 #pragma unroll
                 for (uint32_t c = 0; c < 8; ++c) {
-                    if (!(v[c] & FIN)) v[c] = cm.buf[v[c]];
-                    all &= v[c];
+                    if (v[c] & OPEN) v[c] = cm.buf[v[c] ^ OPEN];
+                    open |= v[c];
                 }
-            } while (!all);
+            } while (open & OPEN);
             // (both candidates are loaded, at clamped places: no branch around the loads)
             if (!LABELS) {
 #pragma unroll
@@ -1093,13 +1151,12 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
 
 // Labels of the implied nodes of level t = 5 or 6 (children of the level t - 1
 // nodes that do not expand), by pairs of such nodes along x.
-template <int NT, typename LT>
-__device__ __forceinline__ void fill_implied(const Params& P, Shared& sh, const ChunkMem& cm) {
-    const uint32_t t = sh.h.t, S = 1u << t, hb = t - 1, H = 1u << hb, pc = sh.h.pc;
-    const LT* const pal = (const LT*)cm.pal;
-    LT* const out = (LT*)(P.out + sh.h.out_off * sizeof(LT));
+template <int NT, typename LT, bool L6>
+__device__ __forceinline__ void fill_implied(const Params& P, Shared& sh, const ChunkMem& cm, const LT* pal) {
+    const uint32_t t = L6 ? 6u : 5u, S = 1u << t, hb = t - 1, H = 1u << hb, pc = uni(sh.h.pc);
+    LT* const out = (LT*)(P.out + uni64(sh.h.out_off) * sizeof(LT));
     const bool vec = ((uintptr_t)out & (4 * sizeof(LT) - 1)) == 0;
-    const uint2* const ep = t == 5 ? sh.EP + ebase(4) : cm.ep5;
+    const uint2* const ep = L6 ? cm.ep5 : sh.EP + ebase(4);
     for (uint32_t u = threadIdx.x; u < (H >> 1) * H * H; u += NT) {
         const uint32_t px = u & ((H >> 1) - 1), qy = (u >> (hb - 1)) & (H - 1), qz = u >> (2 * hb - 1);
         const uint32_t q = spread3(2 * px) | (spread3(qy) << 1) | (spread3(qz) << 2);
@@ -1108,7 +1165,7 @@ __device__ __forceinline__ void fill_implied(const Params& P, Shared& sh, const 
         LT l[2];
 #pragma unroll
         for (uint32_t hx = 0; hx < 2; ++hx) {
-            const uint32_t idx = t == 5 ? (uint32_t)sh.G[fbase(4) + q + hx] & 0x7FFFu : value5(sh, cm, q + hx);
+            const uint32_t idx = L6 ? value5(sh, cm, q + hx) : (uint32_t)sh.G[fbase(4) + q + hx];
             l[hx] = pal[min(idx, pc - 1u)];
         }
         LT* const o = out + ((2 * qz) * S + 2 * qy) * S + 4 * px;
@@ -1121,27 +1178,39 @@ __device__ __forceinline__ void fill_implied(const Params& P, Shared& sh, const 
     }
 }
 
+template <int NT, typename LT>
+__device__ __forceinline__ bool chunk_labels(const Params& P, Shared& sh, const ChunkMem& cm, const uint32_t* sym, uint32_t& adv,
+                                             uint32_t& pbuf) {
+    const uint32_t t = uni(sh.h.t);
+    if (t == 6) fill_implied<NT, LT, true>(P, sh, cm, (const LT*)cm.pal);
+    else fill_implied<NT, LT, false>(P, sh, cm, (const LT*)cm.pal);
+    return chunk_level<NT, true, LT>(P, sh, cm, sym, t, uni(sh.nexp), adv, pbuf);
+}
+
 // Levels 4..t (0..3 are decoded); wavefront 0 computes a level's parent prefix
 // before the barrier that ends it.  False (to every thread) on an error; labels:
-// the output pass is left to do, from c5g (scratch) when it is set.
+// the output pass is left to do, from c5g (scratch) when it is set; pal_lds: the
+// palette is in the list area.
 template <int NT>
 __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8_t* u_area, uint16_t* slots, uint8_t* scratch,
-                                              const uint32_t* sym, uint16_t*& c5g, bool& labels) {
-    const uint32_t t = sh.h.t, wave = threadIdx.x >> 6;
-    uint32_t adv = sh.adv, pbuf = 0;
+                                              const uint32_t* sym, uint16_t*& c5g, bool& labels, bool& pal_lds) {
+    const uint32_t t = uni(sh.h.t), wave = wave_id();
+    uint32_t adv = uni(sh.adv), pbuf = 0;
     bool ok = true;
     labels = true;
     if (t >= 4) {
-        ok = full_level<NT>(sh, sym, 4, sh.nexp, adv, pbuf);
+        ok = full_level<NT>(sh, sym, 4, uni(sh.nexp), adv, pbuf);
         if (ok && t >= 5) {
             if (wave == 0) {
                 const uint32_t n = level_prefix(sh.EP + ebase(4), ewords(4));
                 if (threadIdx.x == 0) sh.nexp = n;
             }
             __syncthreads();
-            const uint32_t nexp = sh.nexp;
-            if (t == 5 && 8u * nexp <= P.cap16 && sh.h.pc <= 32768u) {
-                ok = level5<NT>(sh, sym, slots, (uint16_t*)u_area, nexp, adv, pbuf);
+            const uint32_t nexp = uni(sh.nexp);
+            if (t == 5 && 8u * nexp <= P.cap16 && uni(sh.h.pc) <= 32768u) {
+                pal_lds = !P.pal_bits && uni(sh.h.pc) <= list_bytes(P.cap16) / P.label_bytes;
+                ok = level5<NT>(sh, sym, slots, u_area, nexp, pal_lds ? uni(sh.h.pc) * P.label_bytes / 4u : 0u,
+                                (const uint32_t*)(P.vol + uni64(sh.h.pal_off)), adv, pbuf);
             } else {
                 ChunkMem cm;
                 cm.ep5 = (uint2*)slots;
@@ -1149,9 +1218,9 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
                 cm.cap = P.cap16 / 2u - 2048u;
                 cm.c5 = (uint16_t*)(scratch + kScrComp);
                 cm.list = (uint16_t*)(scratch + kScrList);
-                cm.pal = P.vol + sh.h.pal_off;
-                const uint32_t pb = sh.h.pc * P.label_bytes;
-                if (sh.h.pc <= kUBytesMin / P.label_bytes && !P.pal_bits) {  // (staged behind the next barrier)
+                cm.pal = P.vol + uni64(sh.h.pal_off);
+                const uint32_t pb = uni(sh.h.pc) * P.label_bytes;
+                if (uni(sh.h.pc) <= kUBytesMin / P.label_bytes && !P.pal_bits) {  // (staged behind the next barrier)
                     for (uint32_t w = threadIdx.x; w < pb / 4u; w += NT) ((uint32_t*)u_area)[w] = ((const uint32_t*)cm.pal)[w];
                     cm.pal = u_area;
                 }
@@ -1168,77 +1237,92 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
                 __syncthreads();
                 if (ok && !P.pal_bits) {
                     labels = false;
-                    if (P.label_bytes == 4) {
-                        fill_implied<NT, uint32_t>(P, sh, cm);
-                        ok = chunk_level<NT, true, uint32_t>(P, sh, cm, sym, t, sh.nexp, adv, pbuf);
-                    } else {
-                        fill_implied<NT, uint64_t>(P, sh, cm);
-                        ok = chunk_level<NT, true, uint64_t>(P, sh, cm, sym, t, sh.nexp, adv, pbuf);
-                    }
+                    ok = P.label_bytes == 4 ? chunk_labels<NT, uint32_t>(P, sh, cm, sym, adv, pbuf)
+                                            : chunk_labels<NT, uint64_t>(P, sh, cm, sym, adv, pbuf);
                 }
             }
         }
     }
     __syncthreads();
-    return ok && !(t == sh.h.L && adv != sh.h.pc) && !sh.err;
+    return ok && !(t == uni(sh.h.L) && adv != uni(sh.h.pc)) && !uni(sh.err);
 }
-// Labels of level t <= 5 (all slots final) as an S^3 x-fastest cube.  Full
-// levels voxel by voxel (4 per thread); level 5 by pairs of 2x2x2 blocks along
-// x under two level-4 nodes: a node that does not expand gives its value to its
-// 8 children, an expanding one has 8 explicit children.
+// Labels of a level 5 in LDS as a 32^3 cube, x fastest, by pairs of 2x2x2 blocks
+// along x under two level-4 nodes; a wavefront writes whole lines (the blocks of
+// the expanding parents alone, written as they were decoded, left L2 with
+// partly written lines: 0.41 ms against 0.28 for 4096 cubes of Voronoi cells).
+// With the palette in LDS every block takes its 8 indices from a row of slots,
+// a block of an implied node from a row made of its one value: looking 16
+// indices up in every lane costs less than branching over the two kinds, which
+// occur in nearly every wavefront.
 template <int NT, typename LT, bool PAL_LDS>
-__device__ __forceinline__ void write_labels(const Params& P, Shared& sh, const uint8_t* u_area, const uint16_t* c5) {
-    const TaskHdr& h = sh.h;
-    const uint32_t t = h.t, S = 1u << t, pc = h.pc;
-    LT* out = (LT*)(P.out + h.out_off * sizeof(LT));
-    const LT* pal = PAL_LDS ? (const LT*)u_area : (const LT*)(P.vol + h.pal_off);
+__device__ __forceinline__ void write_labels5(const Params& P, Shared& sh, const uint8_t* u_area, const uint16_t* c5) {
+    const uint32_t pc = uni(sh.h.pc), tid = threadIdx.x;
+    LT* const out = (LT*)(P.out + uni64(sh.h.out_off) * sizeof(LT));
+    const LT* const pal = PAL_LDS ? (const LT*)u_area : (const LT*)(P.vol + uni64(sh.h.pal_off));
     const bool vec = ((uintptr_t)out & (4 * sizeof(LT) - 1)) == 0;
-    if (t <= 4) {
-        const uint16_t* g = sh.G + fbase(t);
-        if (S < 4) {
-            const uint32_t n = S * S * S;
-            for (uint32_t v = threadIdx.x; v < n; v += NT) {
-                const uint32_t x = v & (S - 1), y = (v >> t) & (S - 1), z = v >> (2 * t);
-                const LT l = pal_get<LT, PAL_LDS>(pal, g[spread3(x) | (spread3(y) << 1) | (spread3(z) << 2)] & 0x7FFFu, pc);
-                __builtin_nontemporal_store(l, out + v);
-            }
-            return;
-        }
-        const uint32_t units = (S * S * S) >> 2;
-        for (uint32_t u = threadIdx.x; u < units; u += NT) {
-            const uint32_t lin = u << 2;
-            const uint32_t x = lin & (S - 1), y = (lin >> t) & (S - 1), z = lin >> (2 * t);
-            const uint32_t m = spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
-            store4<LT>(out + lin, pal_get<LT, PAL_LDS>(pal, g[m] & 0x7FFFu, pc), pal_get<LT, PAL_LDS>(pal, g[m + 1] & 0x7FFFu, pc),
-                       pal_get<LT, PAL_LDS>(pal, g[m + 8] & 0x7FFFu, pc), pal_get<LT, PAL_LDS>(pal, g[m + 9] & 0x7FFFu, pc), vec);
-        }
-        return;
-    }
-    for (uint32_t u = threadIdx.x; u < 2048u; u += NT) {
-        const uint32_t px = u & 7u, qy = (u >> 3) & 15u, qz = u >> 7;
-        LT* const o = out + ((2 * qz) * S + 2 * qy) * S + 4 * px;
-        const uint32_t q = spread3(2 * px) | (spread3(qy) << 1) | (spread3(qz) << 2);
+    // unit u = px + 8 qy + 128 qz: the pair of level-4 nodes (2 px, qy, qz), (2 px + 1, qy, qz)
+    const uint32_t px = tid & 7u, qy = (tid >> 3) & 15u;
+    const uint32_t q_xy = spread3(2 * px) | (spread3(qy) << 1), at_xy = 64u * qy + 4u * px;
+    for (uint32_t u = tid; u < 2048u; u += NT) {
+        const uint32_t qz = u >> 7, q = q_xy | (spread3(qz) << 2);
         const uint2 e = sh.EP[ebase(4) + (q >> 5)];
-        const uint32_t r = ep_rank(e, q), ex = (e.x >> (q & 31)) & 3u;  // the x neighbour differs in bit 0
+        const uint32_t r = ep_rank(e, q), ex = e.x >> (q & 31);  // the x neighbour differs in bit 0
         const uint32_t f2 = *(const uint32_t*)(sh.G + fbase(4) + q);
-        // palette indices of the 8 children of each of the two nodes (child c = x | y << 1 | z << 2)
         LT l[2][8];
 #pragma unroll
         for (uint32_t hx = 0; hx < 2; ++hx) {
-            const uint32_t f = (hx ? f2 >> 16 : f2) & 0x7FFFu;
-            if ((ex >> hx) & 1u) {
-                const uint4 w = ((const uint4*)c5)[r + (hx & ex)];
+            const uint32_t f = hx ? f2 >> 16 : f2 & 0xFFFFu;
+            const bool expl = (ex >> hx) & 1u;
+            const uint4* const row = (const uint4*)c5 + (r + (hx & ex));
+            if (PAL_LDS) {
+                const uint32_t ff = f | (f << 16);
+                uint4 w = make_uint4(ff, ff, ff, ff);
+                if (expl) w = *row;
 #pragma unroll
-                for (uint32_t c = 0; c < 8; ++c) l[hx][c] = pal_get<LT, PAL_LDS>(pal, half_of(w, c) & 0x7FFFu, pc);
+                for (uint32_t c = 0; c < 8; ++c) l[hx][c] = pal[half_of(w, c)];
+            } else if (expl) {
+                const uint4 w = *row;
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c) l[hx][c] = pal_get<LT, false>(pal, half_of(w, c), pc);
             } else {
-                const LT v = pal_get<LT, PAL_LDS>(pal, f, pc);
+                const LT v = pal_get<LT, false>(pal, f, pc);
 #pragma unroll
                 for (uint32_t c = 0; c < 8; ++c) l[hx][c] = v;
             }
         }
+        LT* const o = out + (at_xy + 2048u * qz);
 #pragma unroll
         for (uint32_t zy = 0; zy < 4; ++zy)
-            store4<LT>(o + ((zy >> 1) * S + (zy & 1u)) * S, l[0][2 * zy], l[0][2 * zy + 1], l[1][2 * zy], l[1][2 * zy + 1], vec);
+            store4<LT>(o + ((zy >> 1) * 32u + (zy & 1u)) * 32u, l[0][2 * zy], l[0][2 * zy + 1], l[1][2 * zy], l[1][2 * zy + 1], vec);
+    }
+}
+
+// Labels of level t <= 4 (all slots final) as an S^3 x-fastest cube, 4 voxels
+// per thread.
+template <int NT, typename LT, bool PAL_LDS>
+__device__ __forceinline__ void write_labels(const Params& P, Shared& sh, const uint8_t* u_area) {
+    const TaskHdr& h = sh.h;
+    const uint32_t t = uni(h.t), S = 1u << t, pc = uni(h.pc);
+    LT* out = (LT*)(P.out + uni64(h.out_off) * sizeof(LT));
+    const LT* pal = PAL_LDS ? (const LT*)u_area : (const LT*)(P.vol + uni64(h.pal_off));
+    const bool vec = ((uintptr_t)out & (4 * sizeof(LT) - 1)) == 0;
+    const uint16_t* g = sh.G + fbase(t);
+    if (S < 4) {
+        const uint32_t n = S * S * S;
+        for (uint32_t v = threadIdx.x; v < n; v += NT) {
+            const uint32_t x = v & (S - 1), y = (v >> t) & (S - 1), z = v >> (2 * t);
+            const LT l = pal_get<LT, PAL_LDS>(pal, g[spread3(x) | (spread3(y) << 1) | (spread3(z) << 2)], pc);
+            __builtin_nontemporal_store(l, out + v);
+        }
+        return;
+    }
+    const uint32_t units = (S * S * S) >> 2;
+    for (uint32_t u = threadIdx.x; u < units; u += NT) {
+        const uint32_t lin = u << 2;
+        const uint32_t x = lin & (S - 1), y = (lin >> t) & (S - 1), z = lin >> (2 * t);
+        const uint32_t m = spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
+        store4<LT>(out + lin, pal_get<LT, PAL_LDS>(pal, g[m], pc), pal_get<LT, PAL_LDS>(pal, g[m + 1], pc),
+                   pal_get<LT, PAL_LDS>(pal, g[m + 8], pc), pal_get<LT, PAL_LDS>(pal, g[m + 9], pc), vec);
     }
 }
 
@@ -1250,9 +1334,9 @@ __device__ __forceinline__ void write_labels(const Params& P, Shared& sh, const 
 template <int NT, bool C5G>
 __device__ __forceinline__ void write_indices(const Params& P, Shared& sh, const uint16_t* c5) {
     const TaskHdr& h = sh.h;
-    const uint32_t t = h.t, S = 1u << t, bits = P.pal_bits, e = 32u / bits;
+    const uint32_t t = uni(h.t), S = 1u << t, bits = P.pal_bits, e = 32u / bits;
     const uint32_t n = S * S * S, words = (n + e - 1u) / e;
-    uint32_t* const out = (uint32_t*)P.out + h.out_off;
+    uint32_t* const out = (uint32_t*)P.out + uni64(h.out_off);
     for (uint32_t w = threadIdx.x; w < words; w += NT) {
         uint32_t acc = 0, last_q = 0xFFFFFFFFu, base = 0;
         bool expands = false;
@@ -1263,16 +1347,16 @@ __device__ __forceinline__ void write_indices(const Params& P, Shared& sh, const
             const uint32_t m = spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
             uint32_t idx;
             if (t <= 4) {
-                idx = sh.G[fbase(t) + m] & 0x7FFFu;
+                idx = sh.G[fbase(t) + m];
             } else {
                 const uint32_t pq = m >> 3;
                 if (pq != last_q) {
                     last_q = pq;
                     const uint2 ep = sh.EP[ebase(4) + (pq >> 5)];
                     expands = ep_bit(ep, pq);
-                    base = expands ? 8u * ep_rank(ep, pq) : (uint32_t)sh.G[fbase(4) + pq] & 0x7FFFu;
+                    base = expands ? 8u * ep_rank(ep, pq) : (uint32_t)sh.G[fbase(4) + pq];
                 }
-                idx = expands ? (uint32_t)c5[base + (m & 7u)] & (C5G ? 0xFFFFu : 0x7FFFu) : base;
+                idx = expands ? (uint32_t)c5[base + (m & 7u)] : base;
             }
             acc |= idx << (q * bits);
         }
@@ -1280,31 +1364,21 @@ __device__ __forceinline__ void write_indices(const Params& P, Shared& sh, const
     }
 }
 
-// Output pass; c5g: the level-5 palette indices in scratch (null: slots in LDS).
-template <int NT>
-__device__ __forceinline__ void write_output(const Params& P, Shared& sh, uint8_t* u_area, uint32_t u_bytes,
-                                             const uint16_t* slots, const uint16_t* c5g) {
-    const TaskHdr& h = sh.h;
-    if (P.pal_bits) {
-        if (c5g) write_indices<NT, true>(P, sh, c5g);
-        else write_indices<NT, false>(P, sh, slots);
-        return;
-    }
-    // the palette is staged in LDS over the parent list when it fits there (a
-    // cube of side <= 8 reads its few labels straight from the record)
-    const bool lds = h.t > 3 && (uint64_t)h.pc * P.label_bytes <= u_bytes;
-    if (lds) {
-        const uint32_t words = h.pc * P.label_bytes / 4u;
-        const uint32_t* src = (const uint32_t*)(P.vol + h.pal_off);
-        for (uint32_t w = threadIdx.x; w < words; w += NT) ((uint32_t*)u_area)[w] = src[w];
+// Output pass; c5g: the level-5 palette indices in scratch (null: slots in LDS);
+// pal_lds: the palette is staged already (level 5).
+template <int NT, typename LT>
+__device__ __forceinline__ void write_output(const Params& P, Shared& sh, uint8_t* u_area, const uint16_t* slots, bool pal_lds) {
+    const uint32_t t = uni(sh.h.t), pc = uni(sh.h.pc);
+    if (t == 5) {
+        if (pal_lds) write_labels5<NT, LT, true>(P, sh, u_area, slots);
+        else write_labels5<NT, LT, false>(P, sh, u_area, slots);
+    } else if (t == 4 && pc <= list_bytes(P.cap16) / (uint32_t)sizeof(LT)) {
+        const uint32_t* src = (const uint32_t*)(P.vol + uni64(sh.h.pal_off));
+        for (uint32_t w = threadIdx.x; w < pc * (uint32_t)sizeof(LT) / 4u; w += NT) ((uint32_t*)u_area)[w] = src[w];
         __syncthreads();
-    }
-    if (P.label_bytes == 4) {
-        if (lds) write_labels<NT, uint32_t, true>(P, sh, u_area, slots);
-        else write_labels<NT, uint32_t, false>(P, sh, u_area, slots);
-    } else {
-        if (lds) write_labels<NT, uint64_t, true>(P, sh, u_area, slots);
-        else write_labels<NT, uint64_t, false>(P, sh, u_area, slots);
+        write_labels<NT, LT, true>(P, sh, u_area);
+    } else {  // (a cube of side <= 8 reads its few labels straight from the record)
+        write_labels<NT, LT, false>(P, sh, u_area);
     }
 }
 
@@ -1313,8 +1387,8 @@ template <int NT>
 __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8_t* scratch, Ahead& ah) {
     Shared& sh = *reinterpret_cast<Shared*>(lds);
     const TaskHdr& h = sh.h;
-    if (h.status != kTaskOk) {
-        if (h.status == kTaskCorrupt && h.write_ok) zero_output<NT>(P, h);
+    if (uni(h.status) != kTaskOk) {
+        if (uni(h.status) == kTaskCorrupt && uni(h.write_ok)) zero_output<NT>(P, h);
         return;
     }
     const uint32_t u_bytes = list_bytes(P.cap16);
@@ -1323,8 +1397,8 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     // The symbols, 4 bits each, are read by the level passes as aligned 32-bit
     // words: plain payloads from the record itself, rANS symbols from LDS for a
     // cube of side <= 16, else from the work-group's scratch.
-    const uint32_t wave = threadIdx.x >> 6, n_words = (h.nsym + 7u) / 8u;
-    const bool rans = h.coder == kRans;
+    const uint32_t wave = wave_id(), t = uni(h.t), nsym = uni(h.nsym), n_words = (nsym + 7u) / 8u;
+    const bool rans = uni(h.coder) == kRans;
     // The decoding table sits in the last 16 KiB of the slot area until a level 5
     // overwrites it (later tasks find it there until then).  What lies between the
     // level 0..3 grids and the table stages the record's words and takes the
@@ -1332,28 +1406,28 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     constexpr uint32_t kLoGrid = 1280;  // bytes of the level 0..3 grids (1184), rounded up
     const uint32_t o_words = (uint32_t)offsetof(Shared, G) + kLoGrid;
     const uint32_t o_tab = (uint32_t)sizeof(Shared) + u_bytes + 2u * P.cap16 - 4u * kRansM;
-    const uint32_t G = rans ? ((1u << h.log2W) + 63u) / 64u : 0u;
-    const uint32_t words_bytes = rans ? (2u * (h.gstart[G - 1] + h.gw[G - 1]) + 15u) & ~15u : 0u, sym_bytes = 4u * n_words;
-    const bool fits = rans && (uint64_t)o_words + words_bytes + sym_bytes + 16u <= o_tab;
+    const uint32_t G = rans ? ((1u << uni(h.log2W)) + 63u) / 64u : 0u;
+    const uint32_t words_bytes = rans ? (2u * (uni(h.gstart[G - 1]) + uni(h.gw[G - 1])) + 15u) & ~15u : 0u, sym_bytes = 4u * n_words;
+    const bool fits = rans && (uint64_t)o_words + words_bytes + sym_bytes + 16u + 128u <= o_tab;
     const uint32_t o_sym = fits ? (o_tab - sym_bytes) & ~15u : 0u;
     // Overlap, for a cube with a level 3 whose lane groups leave a wavefront free:
     // wavefronts 0..G-1 decode the lane groups, wavefront G decodes levels 0..3 as
     // soon as every group is past their symbols.  (two or more lanes: a round
     // writes whole bytes of symbol pairs)
-    const bool overlap = fits && G < NT / 64 && h.log2W >= 1u && h.t >= 3;
-    const uint32_t small = min(h.t, 3u), need = h.sym_end[small];
+    const bool overlap = fits && G < NT / 64 && uni(h.log2W) >= 1u && t >= 3;
+    const uint32_t small = min(t, 3u), need = uni(h.sym_end[small]);
     uint8_t* const nib = scratch + kScrSym;
     const uint32_t* sym = fits ? (const uint32_t*)(lds + o_sym) : (const uint32_t*)nib;
     uint32_t x0 = 0;
     if (!rans) {
-        if (h.pay_off + 4ull * max(n_words, 1u) <= P.vol_bytes) {
-            sym = (const uint32_t*)(P.vol + h.pay_off);
+        if (uni64(h.pay_off) + 4ull * max(n_words, 1u) <= P.vol_bytes) {
+            sym = (const uint32_t*)(P.vol + uni64(h.pay_off));
         } else {  // the last record's last word would end past the container
-            for (uint32_t b = threadIdx.x; b < (h.nsym + 1u) / 2u; b += NT) nib[b] = P.vol[h.pay_off + b];
+            for (uint32_t b = threadIdx.x; b < (nsym + 1u) / 2u; b += NT) nib[b] = P.vol[uni64(h.pay_off) + b];
             __syncthreads();
         }
     } else {
-        if (!sh.tab_ok) {
+        if (!uni(sh.tab_ok)) {
             const uint4* src = (const uint4*)P.rans_tab;
             for (uint32_t w = threadIdx.x; w < kRansM / 4; w += NT) ((uint4*)(lds + o_tab))[w] = src[w];
         }
@@ -1384,17 +1458,26 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
         __syncthreads();
     }
     // (sh.err is not written again before the next barrier)
-    bool ok = !sh.err;
+    bool ok = !uni(sh.err);
     if (ok) {
-        if (fits && (h.t > 4 || o_sym < (uint32_t)sizeof(Shared))) {  // not clear of the grids and slots
+        if (fits && (t > 4 || o_sym < (uint32_t)sizeof(Shared))) {  // not clear of the grids and slots
             for (uint32_t q = threadIdx.x; q < n_words; q += NT) ((uint32_t*)nib)[q] = sym[q];
             sym = (const uint32_t*)nib;
             __syncthreads();
         }
         uint16_t* c5g = nullptr;
-        bool labels;
-        ok = decode_levels<NT>(P, sh, u_area, slots, scratch, sym, c5g, labels);
-        if (ok && labels) write_output<NT>(P, sh, u_area, u_bytes, slots, c5g);
+        bool labels, pal_lds = false;
+        ok = decode_levels<NT>(P, sh, u_area, slots, scratch, sym, c5g, labels, pal_lds);
+        if (ok && labels) {
+            if (P.pal_bits) {
+                if (c5g) write_indices<NT, true>(P, sh, c5g);
+                else write_indices<NT, false>(P, sh, slots);
+            } else if (P.label_bytes == 4) {
+                write_output<NT, uint32_t>(P, sh, u_area, slots, pal_lds);
+            } else {
+                write_output<NT, uint64_t>(P, sh, u_area, slots, pal_lds);
+            }
+        }
     }
     __syncthreads();
     if (!ok) {
@@ -1402,7 +1485,7 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
         zero_output<NT>(P, h);
     }
     // (read again only after the task loop's next barriers)
-    if (threadIdx.x == 0) sh.tab_ok = h.t >= 5 ? 0u : rans ? 1u : sh.tab_ok;
+    if (threadIdx.x == 0) sh.tab_ok = t >= 5 ? 0u : rans ? 1u : sh.tab_ok;
 }
 
 // at least 4 waves per SIMD: 128 VGPRs per lane at most
@@ -1428,7 +1511,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
         if (tid < sizeof(TaskHdr) / 4) ((uint32_t*)&sh.h)[tid] = ((const uint32_t*)&sh.hn)[tid];
         if (tid == 0) sh.err = 0;
         __syncthreads();
-        const uint32_t task = sh.h.task;
+        const uint32_t task = uni(sh.h.task);
         if (task == 0xFFFFFFFFu) break;
         if (tid == PT) {
             ah.jt = P.queue && ah.jt < P.n_tasks ? atomicAdd(P.queue, 1u) : P.n_tasks;
@@ -1439,7 +1522,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
             parse_ahead(P, sh.hn, ah.jt);
             ah.done = true;
         }
-        if (tid == 0 && P.status) P.status[task] = sh.h.status;
+        if (tid == 0 && P.status) P.status[task] = uni(sh.h.status);
     }
 }
 
@@ -1538,7 +1621,7 @@ __global__ void cost_scan_kernel(uint32_t* hist, uint32_t* cursor) {
 __global__ void __launch_bounds__(256) cost_scatter_kernel(uint32_t n, const uint32_t* cls, uint32_t* cursor, uint32_t* order) {
     __shared__ uint32_t cnt[4][64];
     __shared__ uint32_t base[64];
-    const uint32_t tid = threadIdx.x, j = blockIdx.x * 256 + tid, lane = lane_id(), wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, j = blockIdx.x * 256 + tid, lane = lane_id(), wave = wave_id();
     cnt[wave][lane] = 0;
     __syncthreads();
     const uint32_t c = j < n ? cls[j] : 64u;
@@ -1572,7 +1655,7 @@ __global__ void zero_u32_kernel(uint32_t* p, uint32_t n) {
 __global__ void __launch_bounds__(1024) dense_offsets_kernel(Params P, uint64_t* offs) {
     __shared__ uint64_t wsum[16];
     __shared__ uint64_t carry;
-    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = wave_id();
     if (tid == 0) carry = 0;
     __syncthreads();
     for (uint32_t c = 0; c < P.n_tasks; c += 1024) {
