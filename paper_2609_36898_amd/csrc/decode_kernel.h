@@ -21,6 +21,13 @@ constexpr uint32_t kMaxCap16 = 32760;    // largest LDS slot share accepted
 constexpr uint32_t kDefaultCap16 = 10240;
 // parent list of level 5 (one 16-bit entry per 8 slots) | staged palette
 __host__ __device__ constexpr uint32_t list_bytes(uint32_t cap16) { return (cap16 / 4u + 15u) & ~15u; }
+// Slot area: the slots and, up to the LDS that four default work-groups leave of
+// a CU's 160 KiB, room for the record's symbols behind the rANS table.
+constexpr uint32_t kSlotBytesShared = 26624;
+__host__ __device__ constexpr uint32_t slot_bytes(uint32_t cap16) {
+    const uint32_t with = 2u * cap16 + 6144u;
+    return with <= kSlotBytesShared ? with : 2u * cap16 > kSlotBytesShared ? 2u * cap16 : kSlotBytesShared;
+}
 static_assert(list_bytes(kMinCap16) >= kUBytesMin, "palette area");
 
 // ---- per work-group global scratch (byte offsets).  Big-path level storage

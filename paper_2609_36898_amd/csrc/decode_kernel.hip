@@ -127,8 +127,17 @@ __device__ __forceinline__ uint32_t compact3(uint32_t v) {
     return v;
 }
 
-// Barrier of the threads that decode a level: the work-group, or (NT = 64)
-// wavefront 0 alone, whose LDS accesses complete in order.
+// Work-group barrier for data exchanged through LDS: outstanding global stores
+// and loads are not waited for.  Data exchanged through global memory takes
+// __syncthreads().
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Barrier of the threads that decode a level: the work-group, or (NT = 64) one
+// wavefront alone, whose LDS accesses complete in order.
 template <int NT>
 __device__ __forceinline__ void lsync() {
     if (NT == 64) {
@@ -136,7 +145,7 @@ __device__ __forceinline__ void lsync() {
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     } else {
-        __syncthreads();
+        lds_barrier();
     }
 }
 
@@ -345,18 +354,39 @@ __device__ __forceinline__ void rans_decode(const Params& P, Shared& sh, const u
     }
 }
 
-// Copy the record's rANS words into LDS at `wl` (no barrier) and return this
-// thread's state for its wavefront's first lane group.
+// Copy the record's rANS words into LDS at `wl` and, with `tab`, the decoding
+// table (no barrier); returns this thread's state for its wavefront's first
+// lane group.  All loads are issued before the first one is waited for: the
+// words of a typical 32^3 record are one 16-byte load per thread.
+typedef uint32_t u32x4_a4 __attribute__((vector_size(16), aligned(4)));
 template <int NT>
-__device__ __forceinline__ uint32_t rans_stage_words(const Params& P, const TaskHdr& h, uint16_t* wl) {
+__device__ __forceinline__ uint32_t rans_stage(const Params& P, const TaskHdr& h, uint16_t* wl, uint32_t wl_bytes, uint4* tab) {
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = wave_id();
     const uint32_t W = 1u << uni(h.log2W), G = (W + 63) / 64, lanes = W < 64 ? W : 64;
-    const uint32_t tw = uni(h.gstart[G - 1]) + uni(h.gw[G - 1]);
-    const uint16_t* const wg = (const uint16_t*)(P.vol + uni64(h.pay_off));
+    const uint8_t* const src = P.vol + uni64(h.pay_off);
     const uint32_t* states = (const uint32_t*)(P.vol + uni64(h.states_off));
+    constexpr uint32_t TN = kRansM / 4 / NT;
     const uint32_t x0 = wave < G && lane < lanes ? states[64 * wave + lane] : 0u;
-    for (uint32_t q = tid; q < tw / 2u; q += NT) ((uint32_t*)wl)[q] = ((const uint32_t*)wg)[q];
-    if ((tw & 1u) && tid == 0) wl[tw - 1u] = wg[tw - 1u];
+    const bool wide = uni64(h.pay_off) + wl_bytes <= P.vol_bytes;  // (wl_bytes is rounded up to 16)
+    u32x4_a4 first = {0u, 0u, 0u, 0u};
+    if (wide && 16u * tid < wl_bytes) first = *(const u32x4_a4*)(src + 16u * tid);
+    if (tab) {
+        uint4 t[TN];
+#pragma unroll
+        for (uint32_t k = 0; k < TN; ++k) t[k] = ((const uint4*)P.rans_tab)[k * NT + tid];
+#pragma unroll
+        for (uint32_t k = 0; k < TN; ++k) tab[k * NT + tid] = t[k];
+    }
+    if (wide) {
+        if (16u * tid < wl_bytes) ((uint4*)wl)[tid] = make_uint4(first[0], first[1], first[2], first[3]);
+        for (uint32_t q = tid + NT; 16u * q < wl_bytes; q += NT) {
+            const u32x4_a4 v = *(const u32x4_a4*)(src + 16u * q);
+            ((uint4*)wl)[q] = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+    } else {
+        const uint32_t tw = uni(h.gstart[G - 1]) + uni(h.gw[G - 1]);
+        for (uint32_t q = tid; q < tw; q += NT) wl[q] = ((const uint16_t*)src)[q];
+    }
     return x0;
 }
 
@@ -674,7 +704,7 @@ __device__ __forceinline__ bool ops_pass(Shared& sh, const uint32_t* sym, uint32
         add_run(x0 | (x1 << 1), t0, t1);
     } else {
         if (lane_id() == 0) sh.pub[pbuf][wave] = make_uint4(x0 | (x1 << 1), t0, t1, 0u);
-        __syncthreads();
+        lds_barrier();
 #pragma unroll
         for (uint32_t w = 0; w < NW; ++w) {
             const uint4 pw = sh.pub[pbuf][w];
@@ -958,11 +988,10 @@ __device__ __forceinline__ void small_levels(Shared& sh, const uint32_t* sym, ui
 // Level 5 of a 32^3 cube at full resolution: its explicit nodes by operation
 // rank in the slot area (child c of the r-th expanding parent at 8r + c).
 template <int NT>
-__device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t* c5, uint8_t* u_area, uint32_t nexp,
+__device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t* c5, uint16_t* list, uint8_t* u_area, uint32_t nexp,
                                        uint32_t pal_words, const uint32_t* pal, uint32_t& adv, uint32_t& pbuf) {
     const uint2* const ep = sh.EP + ebase(4);
     const uint16_t* const par = sh.G + fbase(4);
-    uint16_t* const list = (uint16_t*)u_area;
     // the expanding parents by rank: each thread lists those of some bytes of the bitmap
     for (uint32_t b = threadIdx.x; b < 512u; b += NT) {
         const uint2 e = ep[b >> 2];
@@ -973,7 +1002,7 @@ __device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t
     }
     bool bad = false;
     if (!ops_level<NT, false>(sh, sym, uni(sh.h.sym_end[4]), uni(sh.h.sym_end[5]), 8u * nexp, c5, adv, pbuf, bad)) return false;
-    __syncthreads();
+    lds_barrier();
     for (uint32_t r = threadIdx.x; r < nexp; r += NT) {
         const uint32_t q = list[r], pv = par[q];
         const uint4 raw = flip8(((const uint4*)c5)[r]);
@@ -993,8 +1022,8 @@ __device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t
         ((uint4*)c5)[r] = pack8(v);
     }
     if (bad) sh.err = 1u;
-    __syncthreads();
-    // the palette over the parent list, for the output pass
+    lds_barrier();
+    // the palette, over the parent list (which has been read), for the output pass
     for (uint32_t w = threadIdx.x; w < pal_words; w += NT) ((uint32_t*)u_area)[w] = pal[w];
     for (uint32_t r = threadIdx.x; r < nexp; r += NT) chase8(c5, (uint4*)c5 + r);
     return true;
@@ -1190,10 +1219,11 @@ __device__ __forceinline__ bool chunk_labels(const Params& P, Shared& sh, const 
 // Levels 4..t (0..3 are decoded); wavefront 0 computes a level's parent prefix
 // before the barrier that ends it.  False (to every thread) on an error; labels:
 // the output pass is left to do, from c5g (scratch) when it is set; pal_lds: the
-// palette is in the list area.
+// palette is in the list area.  sym_at: place of the symbols in the slot area (0:
+// they are elsewhere).
 template <int NT>
 __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8_t* u_area, uint16_t* slots, uint8_t* scratch,
-                                              const uint32_t* sym, uint16_t*& c5g, bool& labels, bool& pal_lds) {
+                                              const uint32_t* sym, uint32_t sym_at, uint16_t*& c5g, bool& labels, bool& pal_lds) {
     const uint32_t t = uni(sh.h.t), wave = wave_id();
     uint32_t adv = uni(sh.adv), pbuf = 0;
     bool ok = true;
@@ -1205,11 +1235,23 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
                 const uint32_t n = level_prefix(sh.EP + ebase(4), ewords(4));
                 if (threadIdx.x == 0) sh.nexp = n;
             }
-            __syncthreads();
+            lds_barrier();
             const uint32_t nexp = uni(sh.nexp);
-            if (t == 5 && 8u * nexp <= P.cap16 && uni(sh.h.pc) <= 32768u) {
+            // level 5 in LDS when its rows (and the parent list, behind them when it
+            // is longer than its own area) end before its symbols
+            const bool own_list = 2u * nexp <= list_bytes(P.cap16);
+            const uint32_t room = sym_at ? sym_at + 4u * (uni(sh.h.sym_end[4]) >> 3) : slot_bytes(P.cap16);
+            const uint32_t rows = (own_list ? 16u : 18u) * nexp;
+            const bool in_lds = t == 5 && rows <= slot_bytes(P.cap16) && uni(sh.h.pc) <= 32768u;
+            if (sym_at && !(in_lds && rows <= room)) {
+                uint32_t* const nib = (uint32_t*)(scratch + kScrSym);
+                for (uint32_t q = threadIdx.x; q < (uni(sh.h.nsym) + 7u) / 8u; q += NT) nib[q] = sym[q];
+                sym = nib;
+                __syncthreads();
+            }
+            if (in_lds) {
                 pal_lds = !P.pal_bits && uni(sh.h.pc) <= list_bytes(P.cap16) / P.label_bytes;
-                ok = level5<NT>(sh, sym, slots, u_area, nexp, pal_lds ? uni(sh.h.pc) * P.label_bytes / 4u : 0u,
+                ok = level5<NT>(sh, sym, slots, own_list ? (uint16_t*)u_area : slots + 8u * nexp, u_area, nexp, pal_lds ? uni(sh.h.pc) * P.label_bytes / 4u : 0u,
                                 (const uint32_t*)(P.vol + uni64(sh.h.pal_off)), adv, pbuf);
             } else {
                 ChunkMem cm;
@@ -1243,7 +1285,7 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
             }
         }
     }
-    __syncthreads();
+    lds_barrier();
     return ok && !(t == uni(sh.h.L) && adv != uni(sh.h.pc)) && !uni(sh.err);
 }
 // Labels of a level 5 in LDS as a 32^3 cube, x fastest, by pairs of 2x2x2 blocks
@@ -1375,7 +1417,7 @@ __device__ __forceinline__ void write_output(const Params& P, Shared& sh, uint8_
     } else if (t == 4 && pc <= list_bytes(P.cap16) / (uint32_t)sizeof(LT)) {
         const uint32_t* src = (const uint32_t*)(P.vol + uni64(sh.h.pal_off));
         for (uint32_t w = threadIdx.x; w < pc * (uint32_t)sizeof(LT) / 4u; w += NT) ((uint32_t*)u_area)[w] = src[w];
-        __syncthreads();
+        lds_barrier();
         write_labels<NT, LT, true>(P, sh, u_area);
     } else {  // (a cube of side <= 8 reads its few labels straight from the record)
         write_labels<NT, LT, false>(P, sh, u_area);
@@ -1399,17 +1441,19 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     // cube of side <= 16, else from the work-group's scratch.
     const uint32_t wave = wave_id(), t = uni(h.t), nsym = uni(h.nsym), n_words = (nsym + 7u) / 8u;
     const bool rans = uni(h.coder) == kRans;
-    // The decoding table sits in the last 16 KiB of the slot area until a level 5
-    // overwrites it (later tasks find it there until then).  What lies between the
-    // level 0..3 grids and the table stages the record's words and takes the
-    // symbols, which end at the table.
+    // While the symbols are decoded: the words between the level 0..3 grids and
+    // the slot area, the decoding table in its first 16 KiB (it stays until a
+    // level 5 overwrites it; later tasks find it there until then), the symbols at
+    // its end, where the level passes read them.
     constexpr uint32_t kLoGrid = 1280;  // bytes of the level 0..3 grids (1184), rounded up
     const uint32_t o_words = (uint32_t)offsetof(Shared, G) + kLoGrid;
-    const uint32_t o_tab = (uint32_t)sizeof(Shared) + u_bytes + 2u * P.cap16 - 4u * kRansM;
+    const uint32_t o_tab = (uint32_t)sizeof(Shared) + u_bytes, o_end = o_tab + slot_bytes(P.cap16);
     const uint32_t G = rans ? ((1u << uni(h.log2W)) + 63u) / 64u : 0u;
-    const uint32_t words_bytes = rans ? (2u * (uni(h.gstart[G - 1]) + uni(h.gw[G - 1])) + 15u) & ~15u : 0u, sym_bytes = 4u * n_words;
-    const bool fits = rans && (uint64_t)o_words + words_bytes + sym_bytes + 16u + 128u <= o_tab;
-    const uint32_t o_sym = fits ? (o_tab - sym_bytes) & ~15u : 0u;
+    const uint64_t words = rans ? (uint64_t)uni(h.gstart[G - 1]) + uni(h.gw[G - 1]) : 0u;
+    const uint32_t sym_bytes = 4u * n_words;
+    // (a round may read up to 63 words past a group's end)
+    const bool fits = rans && o_words + 2u * words + 16u + 128u <= o_tab && o_tab + 4u * kRansM + sym_bytes + 16u <= o_end;
+    const uint32_t words_bytes = fits ? (2u * (uint32_t)words + 15u) & ~15u : 0u, o_sym = fits ? (o_end - sym_bytes) & ~15u : 0u;
     // Overlap, for a cube with a level 3 whose lane groups leave a wavefront free:
     // wavefronts 0..G-1 decode the lane groups, wavefront G decodes levels 0..3 as
     // soon as every group is past their symbols.  (two or more lanes: a round
@@ -1427,13 +1471,9 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
             __syncthreads();
         }
     } else {
-        if (!uni(sh.tab_ok)) {
-            const uint4* src = (const uint4*)P.rans_tab;
-            for (uint32_t w = threadIdx.x; w < kRansM / 4; w += NT) ((uint4*)(lds + o_tab))[w] = src[w];
-        }
         if (threadIdx.x < 4) sh.prog[threadIdx.x] = 0;
-        if (fits) x0 = rans_stage_words<NT>(P, h, (uint16_t*)(lds + o_words));
-        __syncthreads();
+        x0 = rans_stage<NT>(P, h, (uint16_t*)(lds + o_words), words_bytes, uni(sh.tab_ok) ? nullptr : (uint4*)(lds + o_tab));
+        lds_barrier();
     }
     // step 0 decodes the symbols; step 1 levels 0..3, on one wavefront, while lane
     // 0 of the last wavefront parses the next task; with overlap both in step 1
@@ -1444,6 +1484,7 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
             rans_rounds<NT>(P, sh, tab, (const uint16_t*)(lds + o_words), lds + o_sym, x0, overlap ? max(need, 1u) : 0u);
         } else if (step == 0u) {
             rans_decode<NT>(P, sh, tab, nib);
+            __syncthreads();
         } else if (wave == (overlap ? G : 0u)) {
             // bounded: every group publishes ~0 when its rounds end
             if (overlap)
@@ -1455,19 +1496,14 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
             parse_ahead(P, sh.hn, ah.jt);
             ah.done = true;
         }
-        __syncthreads();
+        lds_barrier();
     }
     // (sh.err is not written again before the next barrier)
     bool ok = !uni(sh.err);
     if (ok) {
-        if (fits && (t > 4 || o_sym < (uint32_t)sizeof(Shared))) {  // not clear of the grids and slots
-            for (uint32_t q = threadIdx.x; q < n_words; q += NT) ((uint32_t*)nib)[q] = sym[q];
-            sym = (const uint32_t*)nib;
-            __syncthreads();
-        }
         uint16_t* c5g = nullptr;
         bool labels, pal_lds = false;
-        ok = decode_levels<NT>(P, sh, u_area, slots, scratch, sym, c5g, labels, pal_lds);
+        ok = decode_levels<NT>(P, sh, u_area, slots, scratch, sym, fits ? o_sym - o_tab : 0u, c5g, labels, pal_lds);
         if (ok && labels) {
             if (P.pal_bits) {
                 if (c5g) write_indices<NT, true>(P, sh, c5g);
@@ -1479,8 +1515,8 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
             }
         }
     }
-    __syncthreads();
     if (!ok) {
+        __syncthreads();  // the zeros come after what the work-group has written
         if (threadIdx.x == 0) sh.h.status = kTaskCorrupt;
         zero_output<NT>(P, h);
     }
@@ -1507,10 +1543,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
     }
     if (tid == 0) sh.tab_ok = 0;
     for (;;) {
-        __syncthreads();  // sh.hn is parsed, the last task's status written
+        lds_barrier();  // sh.hn is parsed, the last task's status written
         if (tid < sizeof(TaskHdr) / 4) ((uint32_t*)&sh.h)[tid] = ((const uint32_t*)&sh.hn)[tid];
         if (tid == 0) sh.err = 0;
-        __syncthreads();
+        lds_barrier();
         const uint32_t task = uni(sh.h.task);
         if (task == 0xFFFFFFFFu) break;
         if (tid == PT) {
@@ -1689,7 +1725,7 @@ __global__ void __launch_bounds__(1024) dense_offsets_kernel(Params P, uint64_t*
 // ------------------------------------------------------------ host launch
 size_t shared_bytes(uint32_t cap16) {
     const uint32_t c = cap16 < kMinCap16 ? kMinCap16 : cap16;
-    return sizeof(Shared) + list_bytes(c) + 2ull * c;
+    return sizeof(Shared) + list_bytes(c) + slot_bytes(c);
 }
 
 template <int NT>
