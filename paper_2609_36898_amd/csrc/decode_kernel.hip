@@ -988,10 +988,11 @@ __device__ __forceinline__ void small_levels(Shared& sh, const uint32_t* sym, ui
 // Level 5 of a 32^3 cube at full resolution: its explicit nodes by operation
 // rank in the slot area (child c of the r-th expanding parent at 8r + c).
 template <int NT>
-__device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t* c5, uint16_t* list, uint8_t* u_area, uint32_t nexp,
+__device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t* c5, uint8_t* u_area, uint32_t nexp,
                                        uint32_t pal_words, const uint32_t* pal, uint32_t& adv, uint32_t& pbuf) {
     const uint2* const ep = sh.EP + ebase(4);
     const uint16_t* const par = sh.G + fbase(4);
+    uint16_t* const list = (uint16_t*)u_area;
     // the expanding parents by rank: each thread lists those of some bytes of the bitmap
     for (uint32_t b = threadIdx.x; b < 512u; b += NT) {
         const uint2 e = ep[b >> 2];
@@ -1220,10 +1221,10 @@ __device__ __forceinline__ bool chunk_labels(const Params& P, Shared& sh, const 
 // before the barrier that ends it.  False (to every thread) on an error; labels:
 // the output pass is left to do, from c5g (scratch) when it is set; pal_lds: the
 // palette is in the list area.  sym_at: place of the symbols in the slot area (0:
-// they are elsewhere).
+// they are elsewhere); rows: level 5's slots in LDS.
 template <int NT>
 __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8_t* u_area, uint16_t* slots, uint8_t* scratch,
-                                              const uint32_t* sym, uint32_t sym_at, uint16_t*& c5g, bool& labels, bool& pal_lds) {
+                                              const uint32_t* sym, uint32_t sym_at, uint16_t*& rows, uint16_t*& c5g, bool& labels, bool& pal_lds) {
     const uint32_t t = uni(sh.h.t), wave = wave_id();
     uint32_t adv = uni(sh.adv), pbuf = 0;
     bool ok = true;
@@ -1237,13 +1238,12 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
             }
             lds_barrier();
             const uint32_t nexp = uni(sh.nexp);
-            // level 5 in LDS when its rows (and the parent list, behind them when it
-            // is longer than its own area) end before its symbols
-            const bool own_list = 2u * nexp <= list_bytes(P.cap16);
-            const uint32_t room = sym_at ? sym_at + 4u * (uni(sh.h.sym_end[4]) >> 3) : slot_bytes(P.cap16);
-            const uint32_t rows = (own_list ? 16u : 18u) * nexp;
-            const bool in_lds = t == 5 && rows <= slot_bytes(P.cap16) && uni(sh.h.pc) <= 32768u;
-            if (sym_at && !(in_lds && rows <= room)) {
+            // level 5 in LDS: the parent list from u_area on, the rows of slots behind
+            // it, both before the level's symbols when those are in LDS (else they
+            // go to scratch)
+            const uint32_t o_rows = max(list_bytes(P.cap16), (2u * nexp + 15u) & ~15u), end5 = o_rows + 16u * nexp;
+            const bool in_lds = t == 5 && end5 <= list_bytes(P.cap16) + slot_bytes(P.cap16) && uni(sh.h.pc) <= 32768u;
+            if (sym_at && !(in_lds && end5 <= list_bytes(P.cap16) + sym_at + 4u * (uni(sh.h.sym_end[4]) >> 3))) {
                 uint32_t* const nib = (uint32_t*)(scratch + kScrSym);
                 for (uint32_t q = threadIdx.x; q < (uni(sh.h.nsym) + 7u) / 8u; q += NT) nib[q] = sym[q];
                 sym = nib;
@@ -1251,7 +1251,8 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
             }
             if (in_lds) {
                 pal_lds = !P.pal_bits && uni(sh.h.pc) <= list_bytes(P.cap16) / P.label_bytes;
-                ok = level5<NT>(sh, sym, slots, own_list ? (uint16_t*)u_area : slots + 8u * nexp, u_area, nexp, pal_lds ? uni(sh.h.pc) * P.label_bytes / 4u : 0u,
+                rows = (uint16_t*)(u_area + o_rows);
+                ok = level5<NT>(sh, sym, rows, u_area, nexp, pal_lds ? uni(sh.h.pc) * P.label_bytes / 4u : 0u,
                                 (const uint32_t*)(P.vol + uni64(sh.h.pal_off)), adv, pbuf);
             } else {
                 ChunkMem cm;
@@ -1501,17 +1502,17 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     // (sh.err is not written again before the next barrier)
     bool ok = !uni(sh.err);
     if (ok) {
-        uint16_t* c5g = nullptr;
+        uint16_t *rows = slots, *c5g = nullptr;
         bool labels, pal_lds = false;
-        ok = decode_levels<NT>(P, sh, u_area, slots, scratch, sym, fits ? o_sym - o_tab : 0u, c5g, labels, pal_lds);
+        ok = decode_levels<NT>(P, sh, u_area, slots, scratch, sym, fits ? o_sym - o_tab : 0u, rows, c5g, labels, pal_lds);
         if (ok && labels) {
             if (P.pal_bits) {
                 if (c5g) write_indices<NT, true>(P, sh, c5g);
-                else write_indices<NT, false>(P, sh, slots);
+                else write_indices<NT, false>(P, sh, rows);
             } else if (P.label_bytes == 4) {
-                write_output<NT, uint32_t>(P, sh, u_area, slots, pal_lds);
+                write_output<NT, uint32_t>(P, sh, u_area, rows, pal_lds);
             } else {
-                write_output<NT, uint64_t>(P, sh, u_area, slots, pal_lds);
+                write_output<NT, uint64_t>(P, sh, u_area, rows, pal_lds);
             }
         }
     }
