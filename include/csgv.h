@@ -82,7 +82,7 @@ enum {
 
 /* Decoder forms. */
 enum {
-    CSGV_MODE_PLAIN = 0,      /* one kernel launch per task (a single work-group each) */
+    CSGV_MODE_PLAIN = 0,      /* task order: work-group b decodes tasks b, b + grid, ... of one launch */
     CSGV_MODE_PERSISTENT = 2  /* one launch of resident work-groups popping tasks from a device queue */
 };
 
@@ -110,7 +110,7 @@ typedef struct {
     int wgs_per_cu;      /* persistent form: work-groups per compute unit; default = as many
                             as LDS and wave slots allow                                     */
     int sort_tasks;      /* persistent form: pop tasks in decreasing estimated cost
-                            (record bytes + output bytes, by powers of two); default 1      */
+                            (cube side, then record bytes); default 1                       */
     int bricks_per_wave; /* tasks a wavefront takes at a time; only 1 is implemented        */
     int lds_slots;       /* LDS split: 16-bit slots per work-group for the explicit nodes of
                             level 5 (bricks needing more use global scratch); the area also
@@ -203,10 +203,10 @@ csgv_status csgv_check_status(const uint32_t* d_status, uint32_t n, hipStream_t 
 /*
  * Batched plans: the decode stage of Methods > "GPU rendering pipeline" as
  * one persistent launch -- resident work-groups popping tasks from a device
- * queue, optionally in decreasing estimated cost -- plus the rANS table and
- * dense-offset kernels, all captured into one HIP graph.  The plan owns its
- * device scratch (sized by vol->max_log2b and the grid).  A plan serves one
- * stream at a time; distinct plans may be used from different threads.
+ * queue, optionally in decreasing estimated cost -- after one kernel that
+ * sorts the tasks into cost classes and computes dense offsets (when either is
+ * needed).  The plan owns its device scratch (sized by vol->max_log2b and the
+ * grid) and the volume's rANS table.  A plan serves one stream at a time; distinct plans may be used from different threads.
  * max_tasks bounds n of every launch.
  */
 typedef struct csgv_plan csgv_plan;
@@ -220,13 +220,11 @@ csgv_status csgv_plan_launch(csgv_plan* plan, hipStream_t stream, const void* d_
                              const uint8_t* d_lods, const uint64_t* d_out_offsets, uint32_t n, void* d_out,
                              uint64_t out_capacity, uint32_t* d_status);
 
-/* Launch through a captured HIP graph of the whole sequence (default 1), or
-   enqueue the kernels directly (0).  A graph is re-captured whenever the task
-   arguments or the shape differ from the previous launch. */
+/* Accepted for both values and without effect: a launch is one or two kernels,
+   which are enqueued directly (a graph of them would start later). */
 csgv_status csgv_plan_set_graph(csgv_plan* plan, int enable);
 
-/* When enabled, launches bypass the graph and bracket the decode kernel with
-   HIP events on the launch stream (read with csgv_plan_last_kernel_ms). */
+/* When enabled, launches bracket the decode kernel with HIP events on the launch stream (read with csgv_plan_last_kernel_ms). */
 csgv_status csgv_plan_set_timing(csgv_plan* plan, int enable);
 
 /* Change the launch shape (fields left 0, or -1 for sort_tasks and

@@ -1,5 +1,5 @@
 // C ABI of the decoder: argument checks, scratch, the plain and persistent
-// launch forms, and batched plans (cost-sorted queue, captured HIP graph).
+// launch forms, and batched plans.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -109,6 +109,7 @@ Params make_params(const csgv_volume_info* vol, const void* d_container, const u
     P.out_cap = cap;
     P.status = status;
     P.scratch_stride = scratch_per_wg(P.max_log2b);
+    P.scratch_sym = scr_sym(P.max_log2b);
     P.cap16 = kDefaultCap16;
     return P;
 }
@@ -141,52 +142,65 @@ csgv_status check_opts(const csgv_decode_opts* o) {
 // device memory of one launch sequence (a plan's, or a one-shot call's)
 struct Bufs {
     uint8_t* scratch = nullptr;
-    uint32_t* queue = nullptr;
-    uint32_t* hist = nullptr;   // 128
-    uint32_t* cls = nullptr;    // max_tasks
-    uint32_t* order = nullptr;  // max_tasks
+    Control* ctl = nullptr;
+    uint32_t* lists = nullptr;   // kClasses * max_tasks
+    uint32_t list_cap = 0;
     uint32_t* rans_tab = nullptr;
-    uint64_t* dense = nullptr;  // max_tasks
-    bool table_built = false;   // rans_tab already holds the volume's table
+    uint64_t* dense = nullptr;   // max_tasks
+    uint64_t* base = nullptr;    // one per block of kBinTasks
+    uint64_t* totals = nullptr;  // one per block of kBinTasks
+    bool prepared = false;       // the table is built and the control words are zero
 };
 
+uint64_t bin_blocks(uint64_t max_tasks) { return (max_tasks + kBinTasks - 1) / kBinTasks; }
+
 uint64_t aux_bytes(uint32_t max_tasks) {
-    return 256 + 4 * 128 + 8ull * max_tasks + 4ull * kRansM + 8ull * max_tasks + 256;
+    return 256 + 4ull * kRansM + 4ull * kClasses * max_tasks + 8 + 8ull * max_tasks + 16 * bin_blocks(max_tasks) + 256;
 }
 
 void carve(uint8_t* base, uint64_t scratch_bytes, uint32_t max_tasks, Bufs* b) {
     b->scratch = base;
     uint8_t* a = base + scratch_bytes;
-    b->queue = (uint32_t*)a;
-    b->hist = (uint32_t*)(a + 256);
-    b->cls = b->hist + 128;
-    b->order = b->cls + max_tasks;
-    b->rans_tab = b->order + max_tasks;
-    uint8_t* d = (uint8_t*)(b->rans_tab + kRansM);
-    d = (uint8_t*)(((uintptr_t)d + 255) & ~(uintptr_t)255);
-    b->dense = (uint64_t*)d;
+    b->ctl = (Control*)a;
+    b->rans_tab = (uint32_t*)(a + 256);
+    b->dense = (uint64_t*)(b->rans_tab + kRansM);
+    b->base = b->dense + max_tasks;
+    b->totals = b->base + bin_blocks(max_tasks);
+    b->lists = (uint32_t*)(b->totals + bin_blocks(max_tasks));
+    b->list_cap = max_tasks;
 }
 
-// everything a persistent launch enqueues, in order
-hipError_t enqueue_persistent(Params P, const Bufs& b, const csgv_volume_info* vol, int wg, uint32_t grid, bool sort,
-                              hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+// Everything a launch enqueues, in order: for buffers that are not prepared, the
+// rANS table and zeroed control words; the task lists when tasks have to wait
+// for a work-group and their cost decides the order, and the dense offsets when
+// they are asked for; the decode.  With no more tasks than work-groups every
+// task starts at once, so there is no queue and no order.  (Direct launches: a
+// plan's one or two kernels leave 5.6 us between calls, a captured graph of
+// them 8.4.)
+hipError_t enqueue(Params P, const Bufs& b, const csgv_volume_info* vol, int wg, uint32_t grid, bool queue, bool sort,
+                   hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     P.scratch = b.scratch;
-    P.queue = b.queue;
     P.rans_tab = b.rans_tab;
-    hipError_t e = launch_reset(P.queue, s);
-    if (e != hipSuccess) return e;
-    bool ok;
-    const RansFreq f = pack_freq(vol, &ok);
-    if (ok && !b.table_built && (e = launch_rans_table(b.rans_tab, f, s)) != hipSuccess) return e;
+    queue = queue && P.n_tasks > grid;
+    sort = sort && queue;
+    hipError_t e;
+    if (!b.prepared) {
+        bool ok;
+        const RansFreq f = pack_freq(vol, &ok);
+        if ((e = launch_prepare(b.ctl, ok ? b.rans_tab : nullptr, &f, s)) != hipSuccess) return e;
+    }
+    P.ctl = b.ctl;
+    P.list_cap = b.list_cap;
     if (!P.out_offs) {
         P.dense_offs = b.dense;
-        if ((e = launch_dense_offsets(P, b.dense, s)) != hipSuccess) return e;
+        P.dense_base = b.base;
     }
-    // with no more tasks than work-groups every task starts at once: order is moot
-    if (sort && P.n_tasks > grid) {
-        if ((e = launch_sort(P, b.cls, b.hist, b.order, s)) != hipSuccess) return e;
-        P.order = b.order;
+    if (sort || !P.out_offs) {
+        if ((e = launch_bin(P, sort ? b.lists : nullptr, P.out_offs ? nullptr : b.dense, b.base, b.totals, s)) != hipSuccess)
+            return e;
     }
+    if (sort) P.lists = b.lists;
+    if (!queue) P.ctl = nullptr;
     if (ev0 && (e = hipEventRecord(ev0, s)) != hipSuccess) return e;
     if ((e = launch_decode(P, wg, grid, s)) != hipSuccess) return e;
     if (ev1 && (e = hipEventRecord(ev1, s)) != hipSuccess) return e;
@@ -249,28 +263,11 @@ csgv_status csgv_volume_parse(const void* h_container, uint64_t bytes, csgv_volu
 namespace {
 
 // Enqueue one call of csgv_decode_bricks on buffers b (scratch of `grid`
-// work-groups in persistent mode, of one in plain mode).
-csgv_status decode_on(hipStream_t stream, const csgv_volume_info* vol, Params P, const csgv_decode_opts* opts,
+// work-groups).
+csgv_status decode_on(hipStream_t stream, const csgv_volume_info* vol, const Params& P, const csgv_decode_opts* opts,
                       int mode, int wg, uint32_t grid, const Bufs& b) {
-    hipError_t e = hipSuccess;
-    if (mode == CSGV_MODE_PERSISTENT) {
-        const bool sort = opts ? opts->sort_tasks != 0 : true;
-        e = enqueue_persistent(P, b, vol, wg, grid, sort, stream, nullptr, nullptr);
-    } else {
-        P.scratch = b.scratch;
-        P.rans_tab = b.rans_tab;
-        bool ok;
-        const RansFreq f = pack_freq(vol, &ok);
-        if (ok) e = launch_rans_table(b.rans_tab, f, stream);
-        if (e == hipSuccess && !P.out_offs) {
-            P.dense_offs = b.dense;
-            e = launch_dense_offsets(P, b.dense, stream);
-        }
-        for (uint32_t j = 0; j < P.n_tasks && e == hipSuccess; ++j) {
-            P.task0 = j;
-            e = launch_decode(P, wg, 1, stream);
-        }
-    }
+    const bool queue = mode == CSGV_MODE_PERSISTENT, sort = opts ? opts->sort_tasks != 0 : true;
+    const hipError_t e = enqueue(P, b, vol, wg, grid, queue, sort, stream, nullptr, nullptr);
     if (e != hipSuccess) return fail(CSGV_EHIP, "decode launch: %s", hipGetErrorString(e));
     return CSGV_OK;
 }
@@ -307,8 +304,7 @@ csgv_status csgv_decode_bricks(hipStream_t stream, const csgv_volume_info* vol, 
     csgv_status st = prepare_call(vol, d_container, d_brick_ids, d_lods, d_out_offsets, n, d_out, out_capacity,
                                   d_status, opts, &P, &mode, &wg, &per_cu);
     if (st != CSGV_OK || n == 0) return st;
-    uint32_t grid = 1;
-    if (mode == CSGV_MODE_PERSISTENT) grid = (uint32_t)std::min<uint64_t>((uint64_t)device_cus() * per_cu, n);
+    const uint32_t grid = (uint32_t)std::min<uint64_t>((uint64_t)device_cus() * per_cu, n);
     const uint64_t sb = P.scratch_stride * grid;
     void* mem = nullptr;
     HIP_TRY(hipMallocAsync(&mem, sb + aux_bytes(n), stream));
@@ -343,26 +339,9 @@ struct csgv_plan {
     uint64_t scratch_bytes = 0;
     uint8_t* mem = nullptr;
     Bufs b;
-    hipStream_t cap_stream = nullptr;
-    hipGraphExec_t exec = nullptr;
-    bool use_graph = true;
     bool timing = false;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool ev_valid = false;
-    // arguments the cached graph was captured with
-    struct Key {
-        const void* c;
-        const void* ids;
-        const void* lods;
-        const void* offs;
-        uint32_t n;
-        void* out;
-        uint64_t cap;
-        void* status;
-        int wg, grid, sort, cap16, pal_bits;
-        bool operator==(const Key& o) const { return memcmp(this, &o, sizeof(Key)) == 0; }
-    } key;
-    bool have_key = false;
 };
 
 namespace {
@@ -375,9 +354,8 @@ csgv_status plan_enqueue(csgv_plan* p, hipStream_t s, const Params& P0, bool wit
     Params P = P0;
     P.cap16 = std::max<uint32_t>((uint32_t)p->opts.lds_slots, kMinCap16) & ~7u;
     P.pal_bits = p->opts.palette_bits > 0 ? (uint32_t)p->opts.palette_bits : 0u;
-    hipError_t e = enqueue_persistent(P, p->b, &p->vol, p->opts.wg_size, plan_grid(p, P.n_tasks),
-                                      p->opts.sort_tasks != 0, s, with_events ? p->ev0 : nullptr,
-                                      with_events ? p->ev1 : nullptr);
+    hipError_t e = enqueue(P, p->b, &p->vol, p->opts.wg_size, plan_grid(p, P.n_tasks), true, p->opts.sort_tasks != 0, s,
+                           with_events ? p->ev0 : nullptr, with_events ? p->ev1 : nullptr);
     if (e != hipSuccess) return fail(CSGV_EHIP, "plan launch: %s", hipGetErrorString(e));
     return CSGV_OK;
 }
@@ -403,14 +381,14 @@ csgv_status plan_alloc(csgv_plan* p) {
     carve(p->mem, sb, p->max_tasks, &p->b);
     p->grid = grid;
     p->scratch_bytes = sb;
-    // the volume's rANS table, built once for every launch of the plan
+    // the volume's rANS table, built once for every launch of the plan, and the
+    // control words, which every launch leaves zero
     bool ok;
     const RansFreq f = pack_freq(&p->vol, &ok);
-    if (ok) {
-        if ((e = launch_rans_table(p->b.rans_tab, f, nullptr)) != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess)
-            return fail(CSGV_EHIP, "rANS table: %s", hipGetErrorString(e));
-    }
-    p->b.table_built = true;
+    if ((e = launch_prepare(p->b.ctl, ok ? p->b.rans_tab : nullptr, &f, nullptr)) != hipSuccess ||
+        (e = hipDeviceSynchronize()) != hipSuccess)
+        return fail(CSGV_EHIP, "rANS table: %s", hipGetErrorString(e));
+    p->b.prepared = true;
     return CSGV_OK;
 }
 
@@ -439,19 +417,17 @@ csgv_status csgv_plan_create(const csgv_volume_info* vol, uint32_t max_tasks, co
         delete p;
         return st;
     }
-    if (hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreate(&p->ev0) != hipSuccess || hipEventCreate(&p->ev1) != hipSuccess) {
+    if (hipEventCreate(&p->ev0) != hipSuccess || hipEventCreate(&p->ev1) != hipSuccess) {
         csgv_plan_destroy(p);
-        return fail(CSGV_EHIP, "plan stream/events");
+        return fail(CSGV_EHIP, "plan events");
     }
     *out = p;
     return CSGV_OK;
 }
 
 csgv_status csgv_plan_set_graph(csgv_plan* p, int enable) {
-    if (!p) return fail(CSGV_EINVAL, "NULL plan");
-    p->use_graph = enable != 0;
-    return CSGV_OK;
+    (void)enable;
+    return p ? CSGV_OK : fail(CSGV_EINVAL, "NULL plan");
 }
 
 csgv_status csgv_plan_set_timing(csgv_plan* p, int enable) {
@@ -477,7 +453,6 @@ csgv_status csgv_plan_set_opts(csgv_plan* p, const csgv_decode_opts* o) {
         p->opts = old;
         return st;
     }
-    p->have_key = false;
     return CSGV_OK;
 }
 
@@ -490,39 +465,9 @@ csgv_status csgv_plan_launch(csgv_plan* p, hipStream_t stream, const void* d_con
     if (n == 0) return CSGV_OK;
     if (n > p->max_tasks) return fail(CSGV_EINVAL, "n = %u exceeds the plan's max_tasks = %u", n, p->max_tasks);
     Params P = make_params(&p->vol, d_container, d_brick_ids, d_lods, d_out_offsets, n, d_out, out_capacity, d_status);
-    if (p->timing || !p->use_graph) {
-        st = plan_enqueue(p, stream, P, p->timing);
-        p->ev_valid = st == CSGV_OK && p->timing;
-        return st;
-    }
-    csgv_plan::Key k;
-    memset(&k, 0, sizeof(k));
-    k.c = d_container; k.ids = d_brick_ids; k.lods = d_lods; k.offs = d_out_offsets; k.n = n; k.out = d_out;
-    k.cap = out_capacity; k.status = d_status; k.wg = p->opts.wg_size; k.grid = (int)p->grid;
-    k.sort = p->opts.sort_tasks; k.cap16 = p->opts.lds_slots; k.pal_bits = p->opts.palette_bits;
-    if (!p->have_key || !(k == p->key) || !p->exec) {
-        if (p->exec) {
-            (void)hipGraphExecDestroy(p->exec);
-            p->exec = nullptr;
-        }
-        HIP_TRY(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
-        st = plan_enqueue(p, p->cap_stream, P, false);
-        hipGraph_t g = nullptr;
-        hipError_t e = hipStreamEndCapture(p->cap_stream, &g);
-        if (st != CSGV_OK) {
-            if (g) (void)hipGraphDestroy(g);
-            return st;
-        }
-        if (e != hipSuccess) return fail(CSGV_EHIP, "end capture: %s", hipGetErrorString(e));
-        e = hipGraphInstantiate(&p->exec, g, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(g);
-        if (e != hipSuccess) return fail(CSGV_EHIP, "graph instantiate: %s", hipGetErrorString(e));
-        p->key = k;
-        p->have_key = true;
-    }
-    HIP_TRY(hipGraphLaunch(p->exec, stream));
-    p->ev_valid = false;
-    return CSGV_OK;
+    st = plan_enqueue(p, stream, P, p->timing);
+    p->ev_valid = st == CSGV_OK && p->timing;
+    return st;
 }
 
 csgv_status csgv_plan_get_opts(const csgv_plan* p, csgv_decode_opts* out) {
@@ -542,8 +487,6 @@ csgv_status csgv_plan_last_kernel_ms(csgv_plan* p, float* ms) {
 
 void csgv_plan_destroy(csgv_plan* p) {
     if (!p) return;
-    if (p->exec) (void)hipGraphExecDestroy(p->exec);
-    if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
     if (p->ev0) (void)hipEventDestroy(p->ev0);
     if (p->ev1) (void)hipEventDestroy(p->ev1);
     if (p->mem) (void)hipFree(p->mem);
@@ -732,9 +675,7 @@ csgv_status csgv_decode_bricks_noalloc(hipStream_t stream, const csgv_volume_inf
     if (fit == 0)
         return fail(CSGV_EINVAL, "records of brick side 2^%u need %llu scratch bytes per work-group, more than the "
                     "fixed scratch holds", P.max_log2b, (unsigned long long)P.scratch_stride);
-    uint32_t grid = 1;
-    if (mode == CSGV_MODE_PERSISTENT)
-        grid = (uint32_t)std::min<uint64_t>(std::min<uint64_t>((uint64_t)device_cus() * per_cu, n), fit);
+    const uint32_t grid = (uint32_t)std::min<uint64_t>(std::min<uint64_t>((uint64_t)device_cus() * per_cu, n), fit);
     uint8_t* base = nullptr;
     if ((st = noalloc_base(&base)) != CSGV_OK) return st;
     Bufs b;

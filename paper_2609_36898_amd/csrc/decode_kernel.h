@@ -30,21 +30,27 @@ __host__ __device__ constexpr uint32_t slot_bytes(uint32_t cap16) {
 }
 static_assert(list_bytes(kMinCap16) >= kUBytesMin, "palette area");
 
-// ---- per work-group global scratch (byte offsets).  Big-path level storage
-// (32-bit slots: full grids of levels 0..4, level 5 by rank), the level-5
-// bitmap used by 64^3 bricks, parent lists of level 6 (and of every level on
-// the big path), then the decoded rANS symbols (4 bits each) whose size
-// depends on the largest brick side of the volume.
-constexpr uint64_t kScrFull = 0;                                   // 4688 x u32
-constexpr uint64_t kScrComp = 18944;                               // 32768 x u32
-constexpr uint64_t kScrE5 = kScrComp + 4ull * 32768;               // 1024 x u32
-constexpr uint64_t kScrWpre5 = kScrE5 + 4096;                      // 1024 x u16
-constexpr uint64_t kScrList = kScrWpre5 + 2048;                    // 32768 x u16
-constexpr uint64_t kScrPval = kScrList + 65536;                    // 32768 x u32
-constexpr uint64_t kScrSym = kScrPval + 131072;                    // 4-bit symbols
+// ---- per work-group global scratch (byte offsets): palette indices of a level 5
+// decoded in chunks (16 bits each), its and level 6's parent lists, then the
+// record's 4-bit symbols, whose size depends on the largest brick side of the
+// volume (as does the list's: level 6 occurs in 64^3 bricks only).
+constexpr uint64_t kScrComp = 0;                                   // 32768 x u16
+constexpr uint64_t kScrList = kScrComp + 2ull * 32768;             // 4096 or 32768 x u16
+constexpr uint64_t scr_sym(uint32_t max_log2b) { return kScrList + 2ull * (max_log2b > 5 ? 32768 : 4096); }
 constexpr uint64_t scratch_per_wg(uint32_t max_log2b) {
-    return kScrSym + ((4 * total_nodes(max_log2b) + 255) / 256) * 256;
+    return scr_sym(max_log2b) + ((4 * total_nodes(max_log2b) + 255) / 256) * 256;
 }
+
+// ---- task lists of a queue launch, by decreasing cost: each class has room for
+// every task; a claim walks the classes in order.
+constexpr uint32_t kClasses = 6;
+// control words of a launch (device memory, zero between launches)
+struct Control {
+    uint32_t queue;             // claims so far
+    uint32_t ticket;            // blocks of the binning kernel done
+    uint32_t count[kClasses];   // tasks per class
+};
+constexpr uint32_t kBinTasks = 256;  // tasks per block of the binning kernel
 
 struct RansFreq {
     uint32_t w[8];  // 16 x u16 frequencies, two per word
@@ -62,16 +68,18 @@ struct Params {
     const uint32_t* ids;
     const uint8_t* lods;
     const uint64_t* out_offs;    // caller's element offsets, or null
-    const uint64_t* dense_offs;  // offsets computed on the device when out_offs is null
+    const uint64_t* dense_offs;  // offsets computed on the device when out_offs is null: within the
+    const uint64_t* dense_base;  // task's block of kBinTasks, and the block's own
     uint32_t n_tasks;
-    uint32_t task0;     // first task of a non-queue launch
     uint8_t* out;
     uint64_t out_cap;   // elements
     uint32_t* status;   // may be null
-    uint32_t* queue;    // persistent form: next-task counter (null otherwise)
-    const uint32_t* order;  // optional pop order
+    Control* ctl;           // queue launch: claims and class counts (null: work-group b takes tasks b, b + grid, ...)
+    const uint32_t* lists;  // queue launch: tasks of class c at c * list_cap
+    uint32_t list_cap;
     uint8_t* scratch;
     uint64_t scratch_stride;
+    uint64_t scratch_sym;   // scr_sym of the volume
     uint32_t cap16;     // LDS slots for the explicit nodes of level 5 (>= kMinCap16)
     uint32_t pal_bits;  // 0: labels; I > 0: packed I-bit palette indices, floor(32/I) per word
 };
@@ -87,9 +95,7 @@ size_t shared_bytes(uint32_t cap16);
 int max_resident_per_cu(int wg_size, uint32_t cap16);  // occupancy of the decode kernel
 hipError_t set_kernel_attrs();
 hipError_t launch_decode(const Params& P, int wg_size, uint32_t grid, hipStream_t s);
-hipError_t launch_reset(uint32_t* q, hipStream_t s);
-hipError_t launch_rans_table(uint32_t* tab, const RansFreq& f, hipStream_t s);
-hipError_t launch_sort(const Params& P, uint32_t* cls, uint32_t* hist, uint32_t* order, hipStream_t s);
-hipError_t launch_dense_offsets(const Params& P, uint64_t* offs, hipStream_t s);
+hipError_t launch_prepare(Control* ctl, uint32_t* tab, const RansFreq* f, hipStream_t s);
+hipError_t launch_bin(const Params& P, uint32_t* lists, uint64_t* dense, uint64_t* base, uint64_t* totals, hipStream_t s);
 
 }  // namespace csgv

@@ -91,6 +91,8 @@ struct Shared {
     uint32_t prog[4];               // per rANS lane group: symbols out so far (release/acquire)
     uint32_t nexp;                  // expanding nodes of the parent level of the next level
     uint32_t adv;                   // PALETTE_ADV operations decoded so far (handed between phases)
+    uint32_t n_jobs;                // tasks of the launch, and of each of its lists
+    uint32_t job[kClasses];
     alignas(16) uint4 pub[2][kMaxWaves];  // per pass and wave: run summary (exit states, counts)
     alignas(16) uint2 EP[kEWords];        // expansion bitmaps of levels 0..4: bits, prefix
     alignas(16) uint16_t G[kFullSlots];   // full grids of levels 0..4
@@ -193,7 +195,7 @@ __device__ __forceinline__ void parse_task(const Params& P, uint32_t task, TaskH
     h.write_ok = 0;
     const uint32_t id = P.ids[task];
     const uint32_t lod = P.lods[task];
-    const uint64_t out_off = P.out_offs ? P.out_offs[task] : P.dense_offs[task];
+    const uint64_t out_off = P.out_offs ? P.out_offs[task] : P.dense_base[task / kBinTasks] + P.dense_offs[task];
     h.out_off = out_off;
     if (id >= P.n_bricks) { h.status = kTaskInvalid; return; }
     const uint64_t* offs = (const uint64_t*)(P.vol + P.off_pos);
@@ -279,9 +281,34 @@ struct Ahead {
     bool done;
 };
 
-__device__ __forceinline__ void parse_ahead(const Params& P, TaskHdr& hn, uint32_t jt) {
-    if (jt < P.n_tasks) parse_task(P, P.order ? P.order[jt] : jt, hn);
-    else hn.task = 0xFFFFFFFFu;
+// (The claim's result is waited for here, not where it was claimed.)
+__device__ __forceinline__ void parse_ahead(const Params& P, Shared& sh, uint32_t jt) {
+    TaskHdr& hn = sh.hn;
+    const uint32_t n = sh.n_jobs;
+    if (jt >= n) {
+        hn.task = 0xFFFFFFFFu;
+        // In a queue launch every work-group ends with one claim past the tasks;
+        // the one that makes their number complete is the last, nothing reads the
+        // control words any more, and it leaves them zero for the next launch.
+        if (P.ctl && jt == n + gridDim.x - 1u) {
+            P.ctl->queue = 0;
+            for (uint32_t c = 0; c < kClasses; ++c) P.ctl->count[c] = 0;
+        }
+        return;
+    }
+    uint32_t task = jt;
+    if (P.lists) {  // the jt-th task over the classes' lists
+        uint32_t c = 0;
+        for (; c < kClasses - 1u && jt >= sh.job[c]; ++c) jt -= sh.job[c];
+        task = P.lists[(uint64_t)c * P.list_cap + jt];
+    }
+    parse_task(P, task, hn);
+}
+
+// the next claim of a work-group after jt
+__device__ __forceinline__ uint32_t claim(const Params& P, const Shared& sh, uint32_t jt) {
+    if (jt >= sh.n_jobs) return jt;
+    return P.ctl ? atomicAdd(&P.ctl->queue, 1u) : jt + gridDim.x;
 }
 
 // ----------------------------------------------------------------- rANS
@@ -1244,7 +1271,7 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
             const uint32_t o_rows = max(list_bytes(P.cap16), (2u * nexp + 15u) & ~15u), end5 = o_rows + 16u * nexp;
             const bool in_lds = t == 5 && end5 <= list_bytes(P.cap16) + slot_bytes(P.cap16) && uni(sh.h.pc) <= 32768u;
             if (sym_at && !(in_lds && end5 <= list_bytes(P.cap16) + sym_at + 4u * (uni(sh.h.sym_end[4]) >> 3))) {
-                uint32_t* const nib = (uint32_t*)(scratch + kScrSym);
+                uint32_t* const nib = (uint32_t*)(scratch + P.scratch_sym);
                 for (uint32_t q = threadIdx.x; q < (uni(sh.h.nsym) + 7u) / 8u; q += NT) nib[q] = sym[q];
                 sym = nib;
                 __syncthreads();
@@ -1461,7 +1488,7 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     // writes whole bytes of symbol pairs)
     const bool overlap = fits && G < NT / 64 && uni(h.log2W) >= 1u && t >= 3;
     const uint32_t small = min(t, 3u), need = uni(h.sym_end[small]);
-    uint8_t* const nib = scratch + kScrSym;
+    uint8_t* const nib = scratch + P.scratch_sym;
     const uint32_t* sym = fits ? (const uint32_t*)(lds + o_sym) : (const uint32_t*)nib;
     uint32_t x0 = 0;
     if (!rans) {
@@ -1494,7 +1521,7 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
                         __builtin_amdgcn_s_sleep(1);
             small_levels(sh, sym, small);
         } else if (threadIdx.x == NT - 64 && !ah.done) {
-            parse_ahead(P, sh.hn, ah.jt);
+            parse_ahead(P, sh, ah.jt);
             ah.done = true;
         }
         lds_barrier();
@@ -1538,9 +1565,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
     constexpr uint32_t PT = NT - 64;
     Ahead ah{0u, true};
     if (tid == PT) {
-        const uint32_t j0 = P.queue ? atomicAdd(P.queue, 1u) : P.task0 + blockIdx.x;
-        parse_ahead(P, sh.hn, j0);
-        ah.jt = j0 < P.n_tasks ? j0 : P.n_tasks;
+        ah.jt = P.ctl ? atomicAdd(&P.ctl->queue, 1u) : blockIdx.x;
+        uint32_t n = P.n_tasks;
+        if (P.lists) {
+            n = 0;
+#pragma unroll
+            for (uint32_t c = 0; c < kClasses; ++c) n += sh.job[c] = P.ctl->count[c];
+        }
+        sh.n_jobs = n;
+        parse_ahead(P, sh, ah.jt);
     }
     if (tid == 0) sh.tab_ok = 0;
     for (;;) {
@@ -1551,12 +1584,12 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
         const uint32_t task = uni(sh.h.task);
         if (task == 0xFFFFFFFFu) break;
         if (tid == PT) {
-            ah.jt = P.queue && ah.jt < P.n_tasks ? atomicAdd(P.queue, 1u) : P.n_tasks;
+            ah.jt = claim(P, sh, ah.jt);
             ah.done = false;
         }
         decode_task<NT>(P, dyn_smem, scratch, ah);
         if (tid == PT && !ah.done) {
-            parse_ahead(P, sh.hn, ah.jt);
+            parse_ahead(P, sh, ah.jt);
             ah.done = true;
         }
         if (tid == 0 && P.status) P.status[task] = uni(sh.h.status);
@@ -1564,14 +1597,12 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
 }
 
 // ------------------------------------------------------------ small kernels
-__global__ void reset_queue_kernel(uint32_t* q) {
-    if (threadIdx.x == 0) q[0] = 0;
-}
-
-// rANS decoding table of the volume: slot -> symbol | freq << 4 | (slot - cum) << 17
-__global__ void rans_table_kernel(uint32_t* tab, RansFreq f) {
+// The control words of a one-shot call and the volume's rANS decoding table:
+// slot -> symbol | freq << 4 | (slot - cum) << 17
+__global__ void prepare_kernel(Control* ctl, uint32_t* tab, RansFreq f) {
     const uint32_t slot = blockIdx.x * blockDim.x + threadIdx.x;
-    if (slot >= kRansM) return;
+    if (ctl && slot < sizeof(Control) / 4) ((uint32_t*)ctl)[slot] = 0;
+    if (!tab || slot >= kRansM) return;
     uint32_t cum = 0, s = 0, fs = 0;
     for (uint32_t k = 0; k < 16; ++k) {
         const uint32_t fk = (f.w[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
@@ -1616,111 +1647,95 @@ __device__ __forceinline__ void for_each_class(uint32_t c, F f) {
     }
 }
 
-// Task cost classes for a decreasing-cost pop order: the class of a task is
-// floor(log2(record bytes + output bytes + 1)); also the class histogram.  256 threads per block.
-__global__ void __launch_bounds__(256) cost_class_kernel(Params P, uint32_t* cls, uint32_t* hist) {
-    __shared__ uint32_t cnt[64];
-    const uint32_t tid = threadIdx.x, j = blockIdx.x * 256 + tid, lane = lane_id();
-    if (tid < 64) cnt[tid] = 0;
-    __syncthreads();
-    uint32_t c = 64;
-    if (j < P.n_tasks) {
-        uint64_t rec;
-        const uint32_t t = task_t(P, j, &rec);
-        const uint64_t unit = P.pal_bits ? 4u : P.label_bytes;
-        const uint64_t cost = rec + (t <= kMaxLog2b ? out_units((uint64_t)1 << (3 * t), P.pal_bits) * unit : 0) + 1;
-        c = 63u - (uint32_t)__clzll(cost);
-        cls[j] = c;
-    }
-    for_each_class(c, [&](uint32_t cc, uint64_t m, uint32_t lead) {
-        if (lane == lead) atomicAdd(&cnt[cc], (uint32_t)__popcll(m));
-    });
-    __syncthreads();
-    if (tid < 64 && cnt[tid]) atomicAdd(&hist[tid], cnt[tid]);
+// Cost class of a task: the cube's side, then the compressed size; a cube takes
+// longer the more of it is explicit, which its record's bytes follow.
+__device__ __forceinline__ uint32_t cost_class(uint32_t t, uint64_t rec_bytes) {
+    if (t > kMaxLog2b) return kClasses - 1;  // unusable: refused when it is parsed
+    const bool heavy = rec_bytes > (t == 6 ? 65536u : 8192u);
+    return t == 6 ? (heavy ? 0u : 1u) : t == 5 ? (heavy ? 1u : 2u) : t == 4 ? 3u : t == 3 ? 4u : 5u;
 }
 
-// exclusive scan of the 64-bin histogram in decreasing class order (one wave)
-__global__ void cost_scan_kernel(uint32_t* hist, uint32_t* cursor) {
-    const uint32_t lane = threadIdx.x;
-    const uint32_t c = 63 - lane;  // lane 0 = most expensive class
-    const uint32_t v = hist[c];
-    uint32_t incl = v;
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t o = __shfl_up(incl, d, 64);
-        if (lane >= (uint32_t)d) incl += o;
-    }
-    cursor[c] = incl - v;
-}
-
-// Scatter task indices to their class's range of the order: a block reserves
-// one range per class it holds, and ranks its lanes within it by wavefront
-// and lane.  256 threads per block.
-__global__ void __launch_bounds__(256) cost_scatter_kernel(uint32_t n, const uint32_t* cls, uint32_t* cursor, uint32_t* order) {
-    __shared__ uint32_t cnt[4][64];
-    __shared__ uint32_t base[64];
-    const uint32_t tid = threadIdx.x, j = blockIdx.x * 256 + tid, lane = lane_id(), wave = wave_id();
-    cnt[wave][lane] = 0;
-    __syncthreads();
-    const uint32_t c = j < n ? cls[j] : 64u;
-    uint32_t rank = 0;
-    for_each_class(c, [&](uint32_t cc, uint64_t m, uint32_t lead) {
-        if (c == cc) rank = mbcnt(m);
-        if (lane == lead) cnt[wave][cc] = (uint32_t)__popcll(m);
-    });
-    __syncthreads();
-    if (tid < 64) {
-        const uint32_t tot = cnt[0][tid] + cnt[1][tid] + cnt[2][tid] + cnt[3][tid];
-        base[tid] = tot ? atomicAdd(&cursor[tid], tot) : 0u;
-    }
-    __syncthreads();
-    if (j < n) {
-        uint32_t pos = base[c] + rank;
-        for (uint32_t w = 0; w < wave; ++w) pos += cnt[w][c];
-        order[pos] = j;
-    }
-}
-
-__global__ void zero_u32_kernel(uint32_t* p, uint32_t n) {
-    const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < n) p[j] = 0;
-}
-
-// Dense output offsets: exclusive prefix sum of the tasks' cube sizes (labels,
-// or words of packed indices) in task order (a task whose record or LOD is
-// unusable occupies nothing).  One
-// work-group of 1024 threads walks the task list in chunks.
-__global__ void __launch_bounds__(1024) dense_offsets_kernel(Params P, uint64_t* offs) {
-    __shared__ uint64_t wsum[16];
-    __shared__ uint64_t carry;
-    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    for (uint32_t c = 0; c < P.n_tasks; c += 1024) {
-        const uint32_t j = c + tid;
-        uint64_t sz = 0;
-        if (j < P.n_tasks) {
-            uint64_t rec;
-            const uint32_t t = task_t(P, j, &rec);
-            sz = t <= kMaxLog2b ? out_units(1ull << (3 * t), P.pal_bits) : 0;
+// One pass over the tasks, kBinTasks per block: each goes to its class's list
+// (one atomic per block and class), and with `dense` it gets its output offset
+// within the block; the block that finishes last turns the blocks' totals into
+// the blocks' own offsets.  A task that names no brick is refused here and goes
+// to no list.  (One launch; a histogram, a scan and a scatter took four, 4.7 us
+// each.)
+__global__ void __launch_bounds__(kBinTasks) bin_kernel(Params P, uint32_t* lists, uint64_t* dense, uint64_t* base,
+                                                        uint64_t* totals) {
+    __shared__ uint32_t cnt[4][8];
+    __shared__ uint32_t first[8];
+    __shared__ uint64_t wsum[4];
+    __shared__ uint32_t last;
+    const uint32_t tid = threadIdx.x, j = blockIdx.x * kBinTasks + tid, lane = lane_id(), wave = tid >> 6;
+    uint64_t rec = 0;
+    const bool in = j < P.n_tasks;
+    const uint32_t t = in ? task_t(P, j, &rec) : 0xFFu;
+    if (lists) {
+        uint32_t c = 64;
+        if (in) {
+            if (P.ids[j] < P.n_bricks) c = cost_class(t, rec);
+            else if (P.status) P.status[j] = kTaskInvalid;
         }
-        uint64_t incl = sz;
+        if (lane < 8) cnt[wave][lane] = 0;
+        uint32_t rank = 0;
+        for_each_class(c, [&](uint32_t cc, uint64_t m, uint32_t lead) {
+            if (c == cc) rank = mbcnt(m);
+            if (lane == lead) cnt[wave][cc] = (uint32_t)__popcll(m);
+        });
+        __syncthreads();
+        if (tid < kClasses) {
+            const uint32_t tot = cnt[0][tid] + cnt[1][tid] + cnt[2][tid] + cnt[3][tid];
+            first[tid] = tot ? atomicAdd(&P.ctl->count[tid], tot) : 0u;
+        }
+        __syncthreads();
+        if (c < kClasses) {
+            uint32_t pos = first[c] + rank;
+            for (uint32_t w = 0; w < wave; ++w) pos += cnt[w][c];
+            lists[(uint64_t)c * P.list_cap + pos] = j;
+        }
+    }
+    if (!dense) return;
+    // exclusive prefix of the tasks' cube sizes (labels, or words of packed
+    // indices) in task order; an unusable task occupies nothing
+    const uint64_t sz = t <= kMaxLog2b ? out_units(1ull << (3 * t), P.pal_bits) : 0;
+    auto block_scan = [&](uint64_t v, uint64_t* total) -> uint64_t {
+        uint64_t incl = v;
         for (int d = 1; d < 64; d <<= 1) {
             const uint64_t o = __shfl_up(incl, d, 64);
             if (lane >= (uint32_t)d) incl += o;
         }
+        __syncthreads();
         if (lane == 63) wsum[wave] = incl;
         __syncthreads();
-        uint64_t base = carry;
-        uint64_t tot = 0;
-        for (uint32_t w = 0; w < 16; ++w) {
-            base += w < wave ? wsum[w] : 0;
+        uint64_t before = 0, tot = 0;
+        for (uint32_t w = 0; w < 4; ++w) {
+            before += w < wave ? wsum[w] : 0;
             tot += wsum[w];
         }
-        if (j < P.n_tasks) offs[j] = base + incl - sz;
-        __syncthreads();
-        if (tid == 0) carry += tot;
-        __syncthreads();
+        *total = tot;
+        return before + incl - v;
+    };
+    uint64_t total;
+    const uint64_t off = block_scan(sz, &total);
+    if (in) dense[j] = off;
+    if (tid == 0) {
+        __hip_atomic_store(&totals[blockIdx.x], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+        last = atomicAdd(&P.ctl->ticket, 1u) == gridDim.x - 1u;
     }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    uint64_t carry = 0;
+    for (uint32_t b = 0; b < gridDim.x; b += kBinTasks) {
+        const uint64_t v = b + tid < gridDim.x
+                               ? __hip_atomic_load(&totals[b + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        const uint64_t o = block_scan(v, &total);
+        if (b + tid < gridDim.x) base[b + tid] = carry + o;
+        carry += total;
+    }
+    if (tid == 0) P.ctl->ticket = 0;
 }
 
 // ------------------------------------------------------------ host launch
@@ -1775,27 +1790,14 @@ hipError_t launch_decode(const Params& P, int wg_size, uint32_t grid, hipStream_
     }
 }
 
-hipError_t launch_reset(uint32_t* q, hipStream_t s) {
-    hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, q);
+hipError_t launch_prepare(Control* ctl, uint32_t* tab, const RansFreq* f, hipStream_t s) {
+    hipLaunchKernelGGL(prepare_kernel, dim3(tab ? kRansM / 256 : 1), dim3(256), 0, s, ctl, tab, f ? *f : RansFreq{});
     return hipGetLastError();
 }
 
-hipError_t launch_rans_table(uint32_t* tab, const RansFreq& f, hipStream_t s) {
-    hipLaunchKernelGGL(rans_table_kernel, dim3(kRansM / 256), dim3(256), 0, s, tab, f);
-    return hipGetLastError();
-}
-
-hipError_t launch_sort(const Params& P, uint32_t* cls, uint32_t* hist, uint32_t* order, hipStream_t s) {
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(2), dim3(64), 0, s, hist, 128u);
-    const uint32_t blocks = (P.n_tasks + 255) / 256;
-    hipLaunchKernelGGL(cost_class_kernel, dim3(blocks), dim3(256), 0, s, P, cls, hist);
-    hipLaunchKernelGGL(cost_scan_kernel, dim3(1), dim3(64), 0, s, hist, hist + 64);
-    hipLaunchKernelGGL(cost_scatter_kernel, dim3(blocks), dim3(256), 0, s, P.n_tasks, cls, hist + 64, order);
-    return hipGetLastError();
-}
-
-hipError_t launch_dense_offsets(const Params& P, uint64_t* offs, hipStream_t s) {
-    hipLaunchKernelGGL(dense_offsets_kernel, dim3(1), dim3(1024), 0, s, P, offs);
+hipError_t launch_bin(const Params& P, uint32_t* lists, uint64_t* dense, uint64_t* base, uint64_t* totals, hipStream_t s) {
+    hipLaunchKernelGGL(bin_kernel, dim3((P.n_tasks + kBinTasks - 1) / kBinTasks), dim3(kBinTasks), 0, s, P, lists, dense, base,
+                       totals);
     return hipGetLastError();
 }
 
