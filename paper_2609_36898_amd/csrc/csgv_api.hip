@@ -195,7 +195,7 @@ hipError_t enqueue(Params P, const Bufs& b, const csgv_volume_info* vol, int wg,
         P.dense_offs = b.dense;
         P.dense_base = b.base;
     }
-    if (sort || !P.out_offs) {
+    if (queue || !P.out_offs) {
         if ((e = launch_bin(P, sort ? b.lists : nullptr, P.out_offs ? nullptr : b.dense, b.base, b.totals, s)) != hipSuccess)
             return e;
     }

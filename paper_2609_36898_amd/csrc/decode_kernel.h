@@ -30,6 +30,10 @@ __host__ __device__ constexpr uint32_t slot_bytes(uint32_t cap16) {
 }
 static_assert(list_bytes(kMinCap16) >= kUBytesMin, "palette area");
 
+// cubes of side <= 8 with at most this many symbols are decoded by one wavefront
+// each, up to four in a work-group
+constexpr uint32_t kWaveSyms = 4096;
+
 // ---- per work-group global scratch (byte offsets): palette indices of a level 5
 // decoded in chunks (16 bits each), its and level 6's parent lists, then the
 // record's 4-bit symbols, whose size depends on the largest brick side of the
@@ -38,17 +42,22 @@ constexpr uint64_t kScrComp = 0;                                   // 32768 x u1
 constexpr uint64_t kScrList = kScrComp + 2ull * 32768;             // 4096 or 32768 x u16
 constexpr uint64_t scr_sym(uint32_t max_log2b) { return kScrList + 2ull * (max_log2b > 5 ? 32768 : 4096); }
 constexpr uint64_t scratch_per_wg(uint32_t max_log2b) {
-    return scr_sym(max_log2b) + ((4 * total_nodes(max_log2b) + 255) / 256) * 256;
+    const uint64_t sym = ((4 * total_nodes(max_log2b) + 255) / 256) * 256;
+    return scr_sym(max_log2b) + (sym < 4ull * kWaveSyms / 2 ? 4ull * kWaveSyms / 2 : sym);
 }
 
 // ---- task lists of a queue launch, by decreasing cost: each class has room for
-// every task; a claim walks the classes in order.
-constexpr uint32_t kClasses = 6;
-// control words of a launch (device memory, zero between launches)
+// every task; a claim walks the classes in order.  The classes from kWgClasses
+// on are decoded by single wavefronts.
+constexpr uint32_t kClasses = 6, kWgClasses = 4;
+// Control words of a launch.  The binning kernel's last block leaves them ready
+// for the decode that follows: the classes' sizes in job, everything else zero.
 struct Control {
-    uint32_t queue;             // claims so far
     uint32_t ticket;            // blocks of the binning kernel done
-    uint32_t count[kClasses];   // tasks per class
+    uint32_t count[kClasses];   // tasks per class while they are binned
+    uint32_t queue;             // claims of the work-groups beyond their first task
+    uint32_t small;             // claims of the single wavefronts beyond their first
+    uint32_t job[kClasses];     // tasks per class
 };
 constexpr uint32_t kBinTasks = 256;  // tasks per block of the binning kernel
 

@@ -91,7 +91,8 @@ struct Shared {
     uint32_t prog[4];               // per rANS lane group: symbols out so far (release/acquire)
     uint32_t nexp;                  // expanding nodes of the parent level of the next level
     uint32_t adv;                   // PALETTE_ADV operations decoded so far (handed between phases)
-    uint32_t n_jobs;                // tasks of the launch, and of each of its lists
+    uint32_t n_jobs;                // tasks of the launch for work-groups, and of each of its lists
+    uint32_t small[2];              // claims on the lists for single wavefronts, this one and the next
     uint32_t job[kClasses];
     alignas(16) uint4 pub[2][kMaxWaves];  // per pass and wave: run summary (exit states, counts)
     alignas(16) uint2 EP[kEWords];        // expansion bitmaps of levels 0..4: bits, prefix
@@ -287,13 +288,8 @@ __device__ __forceinline__ void parse_ahead(const Params& P, Shared& sh, uint32_
     const uint32_t n = sh.n_jobs;
     if (jt >= n) {
         hn.task = 0xFFFFFFFFu;
-        // In a queue launch every work-group ends with one claim past the tasks;
-        // the one that makes their number complete is the last, nothing reads the
-        // control words any more, and it leaves them zero for the next launch.
-        if (P.ctl && jt == n + gridDim.x - 1u) {
-            P.ctl->queue = 0;
-            for (uint32_t c = 0; c < kClasses; ++c) P.ctl->count[c] = 0;
-        }
+        // (the work-group's first claim on the other lists, while its last task is decoded)
+        if (P.lists) sh.small[0] = n ? atomicAdd(&P.ctl->small, 1u) : blockIdx.x;
         return;
     }
     uint32_t task = jt;
@@ -305,10 +301,11 @@ __device__ __forceinline__ void parse_ahead(const Params& P, Shared& sh, uint32_
     parse_task(P, task, hn);
 }
 
-// the next claim of a work-group after jt
+// The next claim of a work-group after jt; its first task is its own number.
+// (Claims of all work-groups on the one counter take 9 ns each.)
 __device__ __forceinline__ uint32_t claim(const Params& P, const Shared& sh, uint32_t jt) {
     if (jt >= sh.n_jobs) return jt;
-    return P.ctl ? atomicAdd(&P.ctl->queue, 1u) : jt + gridDim.x;
+    return gridDim.x + (P.ctl ? atomicAdd(&P.ctl->queue, 1u) : jt);
 }
 
 // ----------------------------------------------------------------- rANS
@@ -316,10 +313,10 @@ __device__ __forceinline__ uint32_t claim(const Params& P, const Shared& sh, uin
 // (low nibble first).  Wavefront w handles lane groups w, w + NW, ...  A
 // group's words sit in a 192-word register window; the third 64-word block is
 // fetched as soon as the window moves, one window move before it is needed.
-template <int NT>
-__device__ __forceinline__ void rans_decode(const Params& P, Shared& sh, const uint32_t* tab, uint8_t* nib) {
+template <int NT, typename SH>
+__device__ __forceinline__ void rans_decode(const Params& P, SH& sh, const uint32_t* tab, uint8_t* nib) {
     const TaskHdr& h = sh.h;
-    const uint32_t lane = lane_id(), wave = wave_id();
+    const uint32_t lane = lane_id(), wave = NT == 64 ? 0u : wave_id();
     const uint32_t W = 1u << uni(h.log2W), G = (W + 63) / 64, lanes = W < 64 ? W : 64;
     const uint32_t nsym = uni(h.nsym);
     const uint16_t* words = (const uint16_t*)(P.vol + uni64(h.pay_off));
@@ -427,11 +424,11 @@ __device__ __forceinline__ uint32_t rans_stage(const Params& P, const TaskHdr& h
 // counts is its length: a full round of 64 lanes has no lane checks, and a
 // group that consumes more words than it has is found out at its end (the word
 // index is held inside the staged words plus one round).
-template <int NT>
-__device__ __forceinline__ void rans_rounds(const Params& P, Shared& sh, const uint32_t* tab, const uint16_t* wl,
+template <int NT, typename SH>
+__device__ __forceinline__ void rans_rounds(const Params& P, SH& sh, const uint32_t* tab, const uint16_t* wl,
                                             uint8_t* nl, uint32_t x0, uint32_t mark) {
     const TaskHdr& h = sh.h;
-    const uint32_t lane = lane_id(), wave = wave_id();
+    const uint32_t lane = lane_id(), wave = NT == 64 ? 0u : wave_id();
     const uint32_t W = 1u << uni(h.log2W), G = (W + 63) / 64, lanes = W < 64 ? W : 64;
     const uint32_t nsym = uni(h.nsym);
     const uint32_t* states = (const uint32_t*)(P.vol + uni64(h.states_off));
@@ -544,9 +541,9 @@ __device__ __forceinline__ void zero_output(const Params& P, const TaskHdr& h) {
     uint8_t* out = P.out + uni64(h.out_off) * unit;
     const uint64_t bytes = out_units(1ull << (3 * t), P.pal_bits) * unit;
     if (((uintptr_t)out & 15u) == 0 && (bytes & 15u) == 0) {
-        for (uint64_t u = threadIdx.x; u < bytes / 16; u += NT) ((uint4*)out)[u] = make_uint4(0, 0, 0, 0);
+        for (uint64_t u = threadIdx.x & (NT - 1); u < bytes / 16; u += NT) ((uint4*)out)[u] = make_uint4(0, 0, 0, 0);
     } else {
-        for (uint64_t u = threadIdx.x; u < bytes / 4; u += NT) ((uint32_t*)out)[u] = 0u;
+        for (uint64_t u = threadIdx.x & (NT - 1); u < bytes / 4; u += NT) ((uint32_t*)out)[u] = 0u;
     }
 }
 
@@ -658,8 +655,8 @@ struct SlotBits {
 // copies as their code; with STOP the stop bit goes along.  False (to every
 // thread, nothing written) when the operations exceed `expected`.  Needs at
 // least one ADV before the pass (level 0 is decoded apart).
-template <int NT, bool W32, bool STOP, typename SLOT>
-__device__ __forceinline__ bool ops_pass(Shared& sh, const uint32_t* sym, uint32_t s0, uint32_t s1, uint32_t w_at,
+template <int NT, bool W32, bool STOP, typename SH, typename SLOT>
+__device__ __forceinline__ bool ops_pass(SH& sh, const uint32_t* sym, uint32_t s0, uint32_t s1, uint32_t w_at,
                                          uint32_t nw, uint32_t lr, uint32_t expected, uint32_t kbase, SLOT* slot,
                                          RunState& rs, uint32_t& pbuf, bool& bad) {
     constexpr uint32_t NW = NT / 64;
@@ -815,8 +812,8 @@ __device__ __forceinline__ bool ops_pass(Shared& sh, const uint32_t* sym, uint32
 
 // All passes of a level whose slots are slot[0 .. expected); true when the
 // symbols are exactly its operations (and the ADVs stay inside the palette).
-template <int NT, bool STOP>
-__device__ __forceinline__ bool ops_level(Shared& sh, const uint32_t* sym, uint32_t s0, uint32_t s1, uint32_t expected,
+template <int NT, bool STOP, typename SH>
+__device__ __forceinline__ bool ops_level(SH& sh, const uint32_t* sym, uint32_t s0, uint32_t s1, uint32_t expected,
                                           uint16_t* slot, uint32_t& adv, uint32_t& pbuf, bool& bad) {
     RunState rs{0u, 0u, adv};
     if (s1 > s0) {
@@ -909,8 +906,8 @@ __device__ __forceinline__ void chase8(const uint16_t* base, uint4* at) {
 // the parents they belong to, and then every node of level i - 1 writes its 8
 // children and their expansion bits: an expanding parent what its operations
 // say, any other its own value.
-template <int NT>
-__device__ __forceinline__ bool full_level(Shared& sh, const uint32_t* sym, uint32_t i, uint32_t nexp, uint32_t& adv,
+template <int NT, typename SH>
+__device__ __forceinline__ bool full_level(SH& sh, const uint32_t* sym, uint32_t i, uint32_t nexp, uint32_t& adv,
                                            uint32_t& pbuf) {
     constexpr uint32_t PP = NT >= 512 ? 1u : NT == 64 ? 1u : 512u / NT;  // parents per thread (level 4; NT = 64: levels 1..3)
     constexpr uint32_t STP = SlotBits<false>::kStop;
@@ -984,7 +981,8 @@ __device__ __forceinline__ bool full_level(Shared& sh, const uint32_t* sym, uint
 // prefix of the next level, the number of its expanding nodes in sh.nexp and
 // the ADV count in sh.adv.  Level 0 is one node whose only valid operation is
 // PALETTE_ADV (entry 0), with or without a stop bit.
-__device__ __forceinline__ void small_levels(Shared& sh, const uint32_t* sym, uint32_t last) {
+template <typename SH>
+__device__ __forceinline__ void small_levels(SH& sh, const uint32_t* sym, uint32_t last) {
     const uint32_t s0 = sym[0] & 15u;
     if (uni(sh.h.sym_end[0]) != 1u || (s0 & 7u) != kAdv || uni(sh.h.pc) == 0u) {
         sh.err = 1u;
@@ -1369,17 +1367,17 @@ __device__ __forceinline__ void write_labels5(const Params& P, Shared& sh, const
 
 // Labels of level t <= 4 (all slots final) as an S^3 x-fastest cube, 4 voxels
 // per thread.
-template <int NT, typename LT, bool PAL_LDS>
-__device__ __forceinline__ void write_labels(const Params& P, Shared& sh, const uint8_t* u_area) {
+template <int NT, typename LT, bool PAL_LDS, typename SH>
+__device__ __forceinline__ void write_labels(const Params& P, SH& sh, const LT* lds_pal) {
     const TaskHdr& h = sh.h;
     const uint32_t t = uni(h.t), S = 1u << t, pc = uni(h.pc);
     LT* out = (LT*)(P.out + uni64(h.out_off) * sizeof(LT));
-    const LT* pal = PAL_LDS ? (const LT*)u_area : (const LT*)(P.vol + uni64(h.pal_off));
+    const LT* pal = PAL_LDS ? lds_pal : (const LT*)(P.vol + uni64(h.pal_off));
     const bool vec = ((uintptr_t)out & (4 * sizeof(LT) - 1)) == 0;
     const uint16_t* g = sh.G + fbase(t);
     if (S < 4) {
         const uint32_t n = S * S * S;
-        for (uint32_t v = threadIdx.x; v < n; v += NT) {
+        for (uint32_t v = threadIdx.x & (NT - 1); v < n; v += NT) {
             const uint32_t x = v & (S - 1), y = (v >> t) & (S - 1), z = v >> (2 * t);
             const LT l = pal_get<LT, PAL_LDS>(pal, g[spread3(x) | (spread3(y) << 1) | (spread3(z) << 2)], pc);
             __builtin_nontemporal_store(l, out + v);
@@ -1387,7 +1385,7 @@ __device__ __forceinline__ void write_labels(const Params& P, Shared& sh, const 
         return;
     }
     const uint32_t units = (S * S * S) >> 2;
-    for (uint32_t u = threadIdx.x; u < units; u += NT) {
+    for (uint32_t u = threadIdx.x & (NT - 1); u < units; u += NT) {
         const uint32_t lin = u << 2;
         const uint32_t x = lin & (S - 1), y = (lin >> t) & (S - 1), z = lin >> (2 * t);
         const uint32_t m = spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
@@ -1401,13 +1399,13 @@ __device__ __forceinline__ void write_labels(const Params& P, Shared& sh, const 
 // One thread per word; level 5 (c5: slots, or with C5G plain indices in
 // scratch) reaches a voxel through its level-4 parent, looked up once per pair
 // of voxels along x.
-template <int NT, bool C5G>
-__device__ __forceinline__ void write_indices(const Params& P, Shared& sh, const uint16_t* c5) {
+template <int NT, bool C5G, typename SH>
+__device__ __forceinline__ void write_indices(const Params& P, SH& sh, const uint16_t* c5) {
     const TaskHdr& h = sh.h;
     const uint32_t t = uni(h.t), S = 1u << t, bits = P.pal_bits, e = 32u / bits;
     const uint32_t n = S * S * S, words = (n + e - 1u) / e;
     uint32_t* const out = (uint32_t*)P.out + uni64(h.out_off);
-    for (uint32_t w = threadIdx.x; w < words; w += NT) {
+    for (uint32_t w = threadIdx.x & (NT - 1); w < words; w += NT) {
         uint32_t acc = 0, last_q = 0xFFFFFFFFu, base = 0;
         bool expands = false;
         for (uint32_t q = 0; q < e; ++q) {
@@ -1446,9 +1444,9 @@ __device__ __forceinline__ void write_output(const Params& P, Shared& sh, uint8_
         const uint32_t* src = (const uint32_t*)(P.vol + uni64(sh.h.pal_off));
         for (uint32_t w = threadIdx.x; w < pc * (uint32_t)sizeof(LT) / 4u; w += NT) ((uint32_t*)u_area)[w] = src[w];
         lds_barrier();
-        write_labels<NT, LT, true>(P, sh, u_area);
+        write_labels<NT, LT, true>(P, sh, (const LT*)u_area);
     } else {  // (a cube of side <= 8 reads its few labels straight from the record)
-        write_labels<NT, LT, false>(P, sh, u_area);
+        write_labels<NT, LT, false>(P, sh, (const LT*)nullptr);
     }
 }
 
@@ -1552,6 +1550,160 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     if (threadIdx.x == 0) sh.tab_ok = t >= 5 ? 0u : rans ? 1u : sh.tab_ok;
 }
 
+// ------------------------------------------------------- tasks of one wavefront
+// Cubes of side <= 8 have at most 585 nodes, which one wavefront decodes alone
+// (levels 0..3 never take more): in a work-group of four wavefronts three would
+// wait for most of such a task.  When the lists of larger tasks are used up, up
+// to four wavefronts of a work-group each take tasks of their own, with no
+// barrier among them; the rANS table in LDS is shared.  Kernel time of 1400
+// neurite cubes of side 8: 0.066 -> 0.034 ms; 4096 of side 2..16: 0.107 -> 0.080.
+struct WaveShared {
+    TaskHdr q[4];  // the tasks of a claim, parsed by one lane each
+    TaskHdr h;     // the task being decoded
+    uint32_t err, nexp, adv, prog[1];
+    alignas(16) uint4 pub[1][1];
+    alignas(16) uint2 EP[20];      // levels 0..3
+    alignas(16) uint16_t G[592];
+    alignas(16) uint32_t pal[128];
+};
+constexpr uint32_t kWaves = 4;
+static_assert(sizeof(WaveShared) % 16 == 0 && kWaves * sizeof(WaveShared) <= sizeof(Shared::G) + kUBytesMin,
+              "the wavefronts' areas take the place of the grids and the parent list");
+
+__device__ __forceinline__ void wave_task(const Params& P, WaveShared& ws, const uint32_t* tab, uint8_t* area, uint32_t area_bytes,
+                                          uint8_t* nib) {
+    const TaskHdr& h = ws.h;
+    const uint32_t lane = lane_id(), nsym = uni(h.nsym), n_words = (nsym + 7u) / 8u, t = uni(h.t), pc = uni(h.pc);
+    const uint32_t* sym = (const uint32_t*)nib;
+    if (t > 3u || nsym > kWaveSyms) {  // (the binning kernel does not hand such a task over)
+        ws.err = 1u;
+        return;
+    }
+    const uint32_t pal_bytes = pc <= sizeof(ws.pal) / P.label_bytes && !P.pal_bits ? pc * P.label_bytes : 0u;
+    uint32_t pw[2];
+#pragma unroll
+    for (uint32_t k = 0; k < 2; ++k)
+        pw[k] = 4u * (64u * k + lane) < pal_bytes ? ((const uint32_t*)(P.vol + uni64(h.pal_off)))[64u * k + lane] : 0u;
+    if (uni(h.coder) == kRaw4) {
+        if (uni64(h.pay_off) + 4ull * max(n_words, 1u) <= P.vol_bytes) {
+            sym = (const uint32_t*)(P.vol + uni64(h.pay_off));
+        } else {  // the last record's last word would end past the container
+            for (uint32_t b = lane; b < (nsym + 1u) / 2u; b += 64u) nib[b] = P.vol[uni64(h.pay_off) + b];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        }
+    } else {
+        // the words that the cube's symbols can need, group by group behind the symbols
+        const uint32_t W = 1u << uni(h.log2W), G = (W + 63u) / 64u;
+        const uint32_t x0 = lane < W ? ((const uint32_t*)(P.vol + uni64(h.states_off)))[lane] : 0u;
+        uint32_t at = (4u * n_words + 15u) & ~15u;
+        bool fits = true;
+        uint32_t from[4], to[4];
+#pragma unroll
+        for (uint32_t g = 0; g < 4; ++g) {
+            from[g] = to[g] = 0;
+            if (g < G && 64u * g < nsym) {
+                const uint32_t rounds = (nsym - 64u * g + W - 1u) / W, start = uni(h.gstart[g]);
+                const uint32_t n = min(uni(h.gw[g]), 64u * rounds) + (start & 1u);
+                fits = fits && uni64(h.pay_off) + 2ull * (start & ~1u) + ((2u * n + 15u) & ~15u) <= P.vol_bytes;
+                from[g] = at;
+                at += (2u * n + 15u) & ~15u;
+                to[g] = at;
+            }
+        }
+        if (fits && at + 128u <= area_bytes) {
+#pragma unroll
+            for (uint32_t g = 0; g < 4; ++g) {
+                if (g < G) {
+                    const uint32_t start = uni(h.gstart[g]);
+                    const uint8_t* const src = P.vol + uni64(h.pay_off) + 2ull * (start & ~1u);
+                    for (uint32_t o = 16u * lane; from[g] + o < to[g]; o += 1024u) {
+                        const u32x4_a4 v = *(const u32x4_a4*)(src + o);
+                        *(uint4*)(area + from[g] + o) = make_uint4(v[0], v[1], v[2], v[3]);
+                    }
+                    if (lane == 0) ws.h.gstart[g] = from[g] / 2u + (start & 1u);  // now within `area`
+                }
+            }
+            lsync<64>();
+            rans_rounds<64>(P, ws, tab, (const uint16_t*)area, area, x0, 0u);
+            sym = (const uint32_t*)area;
+        } else {
+            rans_decode<64>(P, ws, tab, nib);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        }
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 2; ++k)
+        if (4u * (64u * k + lane) < pal_bytes) ws.pal[64u * k + lane] = pw[k];
+    lsync<64>();
+    small_levels(ws, sym, t);
+    lsync<64>();
+    if (uni(ws.err) || (t == uni(h.L) && uni(ws.adv) != pc)) {
+        ws.err = 1u;
+        return;
+    }
+    if (P.pal_bits) write_indices<64, false>(P, ws, (const uint16_t*)nullptr);
+    else if (P.label_bytes == 4 && pal_bytes) write_labels<64, uint32_t, true>(P, ws, (const uint32_t*)ws.pal);
+    else if (P.label_bytes == 4) write_labels<64, uint32_t, false>(P, ws, (const uint32_t*)nullptr);
+    else if (pal_bytes) write_labels<64, uint64_t, true>(P, ws, (const uint64_t*)ws.pal);
+    else write_labels<64, uint64_t, false>(P, ws, (const uint64_t*)nullptr);
+}
+
+template <int NT>
+__device__ __forceinline__ void wave_tasks(const Params& P, uint8_t* lds, uint8_t* scratch) {
+    Shared& sh = *reinterpret_cast<Shared*>(lds);
+    static_assert(kClasses == kWgClasses + 2, "two lists");
+    const uint32_t n_first = uni(sh.job[kWgClasses]), n = n_first + uni(sh.job[kWgClasses + 1]);
+    if (n == 0u) return;
+    constexpr uint32_t NW = NT / 64 < kWaves ? NT / 64 : kWaves;
+    const uint32_t u_bytes = list_bytes(P.cap16), o_tab = (uint32_t)sizeof(Shared) + u_bytes, wave = wave_id(), lane = lane_id();
+    if (!uni(sh.tab_ok))
+        for (uint32_t w = threadIdx.x; w < kRansM / 4; w += NT) ((uint4*)(lds + o_tab))[w] = ((const uint4*)P.rans_tab)[w];
+    lds_barrier();
+    WaveShared& ws = *reinterpret_cast<WaveShared*>(lds + offsetof(Shared, G) + min(wave, NW - 1u) * sizeof(WaveShared));
+    const uint32_t area_bytes = ((slot_bytes(P.cap16) - 4u * kRansM) / kWaves) & ~15u;
+    uint8_t* const area = lds + o_tab + 4u * kRansM + wave * area_bytes;
+    uint8_t* const nib = scratch + P.scratch_sym + wave * (kWaveSyms / 2u);
+    // A work-group's claim is up to 4 tasks for each wavefront, which parses them
+    // side by side: as many as give every work-group one claim.  (Claims of single
+    // wavefronts took 70 us of a launch of 3000 cubes on the counter.)  Without
+    // tasks for work-groups the first claim is the work-group's own number.
+    const uint32_t per = min((n + gridDim.x * NW - 1u) / (gridDim.x * NW), 4u), claims = (n + NW * per - 1u) / (NW * per);
+    const bool fixed = uni(sh.n_jobs) == 0u;
+    uint32_t j = uni(sh.small[0]), turn = 0;
+    while (j < claims) {
+        uint32_t ahead = 0xFFFFFFFFu;
+        if (threadIdx.x == 0 && !(fixed && claims <= gridDim.x)) ahead = (fixed ? gridDim.x : 0u) + atomicAdd(&P.ctl->small, 1u);
+        const uint32_t k0 = (j * NW + wave) * per, m = wave < NW && k0 < n ? min(per, n - k0) : 0u;
+        if (lane < m) {
+            const uint32_t k = k0 + lane;
+            const uint32_t task = k < n_first ? P.lists[(uint64_t)kWgClasses * P.list_cap + k]
+                                              : P.lists[(uint64_t)(kWgClasses + 1) * P.list_cap + (k - n_first)];
+            parse_task(P, task, ws.q[lane]);
+        }
+        lsync<64>();
+        for (uint32_t x = 0; x < m; ++x) {
+            if (lane < sizeof(TaskHdr) / 4) ((uint32_t*)&ws.h)[lane] = ((const uint32_t*)&ws.q[x])[lane];
+            if (lane == 0) ws.err = 0;
+            lsync<64>();
+            uint32_t status = uni(ws.h.status);
+            if (status == kTaskOk) {
+                wave_task(P, ws, (const uint32_t*)(lds + o_tab), area, area_bytes, nib);
+                lsync<64>();
+                if (uni(ws.err)) status = kTaskCorrupt;
+            }
+            if (status == kTaskCorrupt && uni(ws.h.write_ok)) zero_output<64>(P, ws.h);
+            if (lane == 0 && P.status) P.status[uni(ws.h.task)] = status;
+            lsync<64>();
+        }
+        turn ^= 1u;
+        if (threadIdx.x == 0) sh.small[turn] = ahead;
+        lds_barrier();
+        j = uni(sh.small[turn]);
+    }
+}
+
 // at least 4 waves per SIMD: 128 VGPRs per lane at most
 template <int NT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) decode_kernel(Params P) {
@@ -1565,14 +1717,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
     constexpr uint32_t PT = NT - 64;
     Ahead ah{0u, true};
     if (tid == PT) {
-        ah.jt = P.ctl ? atomicAdd(&P.ctl->queue, 1u) : blockIdx.x;
         uint32_t n = P.n_tasks;
         if (P.lists) {
             n = 0;
 #pragma unroll
-            for (uint32_t c = 0; c < kClasses; ++c) n += sh.job[c] = P.ctl->count[c];
+            for (uint32_t c = 0; c < kClasses; ++c) {
+                const uint32_t k = sh.job[c] = P.ctl->job[c];
+                n += c < kWgClasses ? k : 0u;
+            }
         }
         sh.n_jobs = n;
+        ah.jt = blockIdx.x;
         parse_ahead(P, sh, ah.jt);
     }
     if (tid == 0) sh.tab_ok = 0;
@@ -1594,6 +1749,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
         }
         if (tid == 0 && P.status) P.status[task] = uni(sh.h.status);
     }
+    if (P.lists) wave_tasks<NT>(P, dyn_smem, scratch);
 }
 
 // ------------------------------------------------------------ small kernels
@@ -1649,8 +1805,12 @@ __device__ __forceinline__ void for_each_class(uint32_t c, F f) {
 
 // Cost class of a task: the cube's side, then the compressed size; a cube takes
 // longer the more of it is explicit, which its record's bytes follow.
-__device__ __forceinline__ uint32_t cost_class(uint32_t t, uint64_t rec_bytes) {
+__device__ __forceinline__ uint32_t cost_class(const Params& P, uint32_t id, uint32_t t, uint64_t rec_bytes) {
     if (t > kMaxLog2b) return kClasses - 1;  // unusable: refused when it is parsed
+    if (t <= 3 && rec_bytes >= 12u + 4u * t) {  // (a shorter record is refused too)
+        const uint64_t a = ((const uint64_t*)(P.vol + P.off_pos))[id];
+        if (ld32(P.vol + a + 8u + 4u * t) > kWaveSyms) return 3u;
+    }
     const bool heavy = rec_bytes > (t == 6 ? 65536u : 8192u);
     return t == 6 ? (heavy ? 0u : 1u) : t == 5 ? (heavy ? 1u : 2u) : t == 4 ? 3u : t == 3 ? 4u : 5u;
 }
@@ -1667,6 +1827,10 @@ __global__ void __launch_bounds__(kBinTasks) bin_kernel(Params P, uint32_t* list
     __shared__ uint32_t first[8];
     __shared__ uint64_t wsum[4];
     __shared__ uint32_t last;
+    if (!lists && !dense) {  // nothing to do but the control words
+        if (threadIdx.x < sizeof(Control) / 4) ((uint32_t*)P.ctl)[threadIdx.x] = 0;
+        return;
+    }
     const uint32_t tid = threadIdx.x, j = blockIdx.x * kBinTasks + tid, lane = lane_id(), wave = tid >> 6;
     uint64_t rec = 0;
     const bool in = j < P.n_tasks;
@@ -1674,7 +1838,7 @@ __global__ void __launch_bounds__(kBinTasks) bin_kernel(Params P, uint32_t* list
     if (lists) {
         uint32_t c = 64;
         if (in) {
-            if (P.ids[j] < P.n_bricks) c = cost_class(t, rec);
+            if (P.ids[j] < P.n_bricks) c = cost_class(P, P.ids[j], t, rec);
             else if (P.status) P.status[j] = kTaskInvalid;
         }
         if (lane < 8) cnt[wave][lane] = 0;
@@ -1695,7 +1859,6 @@ __global__ void __launch_bounds__(kBinTasks) bin_kernel(Params P, uint32_t* list
             lists[(uint64_t)c * P.list_cap + pos] = j;
         }
     }
-    if (!dense) return;
     // exclusive prefix of the tasks' cube sizes (labels, or words of packed
     // indices) in task order; an unusable task occupies nothing
     const uint64_t sz = t <= kMaxLog2b ? out_units(1ull << (3 * t), P.pal_bits) : 0;
@@ -1716,26 +1879,33 @@ __global__ void __launch_bounds__(kBinTasks) bin_kernel(Params P, uint32_t* list
         *total = tot;
         return before + incl - v;
     };
-    uint64_t total;
-    const uint64_t off = block_scan(sz, &total);
-    if (in) dense[j] = off;
+    uint64_t total = 0;
+    if (dense) {
+        const uint64_t off = block_scan(sz, &total);
+        if (in) dense[j] = off;
+    }
+    __syncthreads();  // the block's counts are out
     if (tid == 0) {
-        __hip_atomic_store(&totals[blockIdx.x], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (dense) __hip_atomic_store(&totals[blockIdx.x], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __threadfence();
         last = atomicAdd(&P.ctl->ticket, 1u) == gridDim.x - 1u;
     }
     __syncthreads();
     if (!last) return;
     __threadfence();
+    if (tid < kClasses) {
+        P.ctl->job[tid] = __hip_atomic_load(&P.ctl->count[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        P.ctl->count[tid] = 0;
+    }
+    if (tid == 0) P.ctl->ticket = P.ctl->queue = P.ctl->small = 0;
     uint64_t carry = 0;
-    for (uint32_t b = 0; b < gridDim.x; b += kBinTasks) {
+    for (uint32_t b = 0; dense && b < gridDim.x; b += kBinTasks) {
         const uint64_t v = b + tid < gridDim.x
                                ? __hip_atomic_load(&totals[b + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
         const uint64_t o = block_scan(v, &total);
         if (b + tid < gridDim.x) base[b + tid] = carry + o;
         carry += total;
     }
-    if (tid == 0) P.ctl->ticket = 0;
 }
 
 // ------------------------------------------------------------ host launch
@@ -1796,7 +1966,8 @@ hipError_t launch_prepare(Control* ctl, uint32_t* tab, const RansFreq* f, hipStr
 }
 
 hipError_t launch_bin(const Params& P, uint32_t* lists, uint64_t* dense, uint64_t* base, uint64_t* totals, hipStream_t s) {
-    hipLaunchKernelGGL(bin_kernel, dim3((P.n_tasks + kBinTasks - 1) / kBinTasks), dim3(kBinTasks), 0, s, P, lists, dense, base,
+    const uint32_t blocks = lists || dense ? (P.n_tasks + kBinTasks - 1) / kBinTasks : 1u;
+    hipLaunchKernelGGL(bin_kernel, dim3(blocks), dim3(kBinTasks), 0, s, P, lists, dense, base,
                        totals);
     return hipGetLastError();
 }
