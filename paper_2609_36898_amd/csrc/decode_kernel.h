@@ -39,8 +39,8 @@ constexpr uint32_t kWaveSyms = 4096;
 // record's 4-bit symbols, whose size depends on the largest brick side of the
 // volume (as does the list's: level 6 occurs in 64^3 bricks only).
 constexpr uint64_t kScrComp = 0;                                   // 32768 x u16
-constexpr uint64_t kScrList = kScrComp + 2ull * 32768;             // 4096 or 32768 x u16
-constexpr uint64_t scr_sym(uint32_t max_log2b) { return kScrList + 2ull * (max_log2b > 5 ? 32768 : 4096); }
+constexpr uint64_t kScrList = kScrComp + 2ull * 32768;             // 4096 or 32768 x u32
+constexpr uint64_t scr_sym(uint32_t max_log2b) { return kScrList + 4ull * (max_log2b > 5 ? 32768 : 4096); }
 constexpr uint64_t scratch_per_wg(uint32_t max_log2b) {
     const uint64_t sym = ((4 * total_nodes(max_log2b) + 255) / 256) * 256;
     return scr_sym(max_log2b) + (sym < 4ull * kWaveSyms / 2 ? 4ull * kWaveSyms / 2 : sym);

@@ -378,6 +378,77 @@ __device__ __forceinline__ void rans_decode(const Params& P, SH& sh, const uint3
     }
 }
 
+// The same for streams that do not fit in LDS whole and 64 lanes or more: every
+// wavefront keeps the next words of its lane group in a ring of 512 in LDS,
+// refilled by halves that were loaded one refill ahead, and hands its symbols
+// to scratch by eight rounds, so a round is as long as with everything staged
+// (330 cycles; 800 with a register window, two bpermutes and a byte store to
+// global memory in each).
+constexpr uint32_t kRing = 512, kStreamBytes = 2u * kRing + 256u;  // LDS of a wavefront
+typedef uint32_t u32x2_a4 __attribute__((vector_size(8), aligned(4)));
+template <int NT>
+__device__ __forceinline__ void rans_stream(const Params& P, Shared& sh, const uint32_t* tab, uint8_t* lds, uint8_t* nib) {
+    const TaskHdr& h = sh.h;
+    const uint32_t lane = lane_id(), wave = wave_id();
+    const uint32_t W = 1u << uni(h.log2W), G = W / 64u, nsym = uni(h.nsym);
+    const uint32_t* states = (const uint32_t*)(P.vol + uni64(h.states_off));
+    uint16_t* const ring = (uint16_t*)(lds + wave * kStreamBytes);
+    uint8_t* const buf = (uint8_t*)(ring + kRing);
+    // reads stay inside the container (past the words they only feed what the
+    // word count at the end refuses)
+    const uint64_t pay = min((uint64_t)uni64(h.pay_off), (P.vol_bytes - 8u) & ~3ull), room = P.vol_bytes - pay - 8u;
+    for (uint32_t g = wave; g < G; g += NT / 64) {
+        const uint32_t gcount = uni(h.gw[g]), start = uni(h.gstart[g]), odd = start & 1u;
+        const uint8_t* const src = P.vol + pay;
+        // words 256 k .. 256 k + 255 of the group's stream (from its even start), 4 per lane
+        auto fetch = [&](uint32_t k) -> uint2 {
+            const uint64_t o = 2ull * (start & ~1u) + 512ull * k + 8u * lane;
+            const u32x2_a4 v = *(const u32x2_a4*)(src + (o < room ? o : room & ~3ull));
+            return make_uint2(v[0], v[1]);
+        };
+        uint32_t x = states[64 * g + lane];
+        uint2 a = fetch(0), b = fetch(1), ahead = fetch(2);
+        ((uint2*)ring)[lane] = a;
+        ((uint2*)ring)[64u + lane] = b;
+        uint32_t pos = odd, loaded = 2, r0 = 64u * g, n = 0;
+        lsync<64>();
+        __builtin_amdgcn_s_waitcnt(0);
+        auto flush = [&] {  // the symbols of the last n <= 8 rounds
+            lsync<64>();
+            const uint32_t r = lane >> 3, j = r0 - (n - r) * W + 8u * (lane & 7u);
+            if (r < n && j < nsym) *(uint32_t*)(nib + j / 2u) = ((const uint32_t*)buf)[lane];
+            lsync<64>();
+            n = 0;
+        };
+        for (; r0 < nsym; r0 += W) {
+            if (pos + 64u > 256u * loaded) {
+                ((uint2*)ring)[64u * (loaded & 1u) + lane] = ahead;
+                ++loaded;
+                ahead = fetch(loaded);
+                lsync<64>();
+            }
+            const bool act = r0 + lane < nsym;
+            const uint32_t e = tab[x & (kRansM - 1)];
+            const uint32_t xd = ((e >> 4) & 0x1FFFu) * (x >> kRansBits) + (e >> 17);
+            const bool need = act && xd < kRansL;
+            const uint64_t m = __ballot(need);
+            uint32_t wv = ring[(pos + mbcnt(m)) & (kRing - 1u)];
+            asm volatile("" : "+v"(wv));
+            x = need ? ((xd << 16) | wv) : act ? xd : x;
+            pos += (uint32_t)__popcll(m);
+            const uint32_t s = e & 15u, hi = dpp<0xB1>(0u, s);
+            if (!(lane & 1u)) buf[32u * n + (lane >> 1)] = (uint8_t)(s | (hi << 4));
+            if (++n == 8u) {
+                r0 += W;
+                flush();
+                r0 -= W;
+            }
+        }
+        if (n) flush();
+        if (pos - odd > gcount && lane == 0) atomicOr(&sh.err, 1u);
+    }
+}
+
 // Copy the record's rANS words into LDS at `wl` and, with `tab`, the decoding
 // table (no barrier); returns this thread's state for its wavefront's first
 // lane group.  All loads are issued before the first one is waited for: the
@@ -1072,7 +1143,7 @@ struct ChunkMem {
     uint32_t* buf;   // operation buffer behind it
     uint32_t cap;    // its 32-bit slots
     uint16_t* c5;    // scratch: level-5 palette indices by operation rank
-    uint16_t* list;  // scratch: expanding parents by rank
+    uint32_t* list;  // scratch: expanding parents by rank, node | palette index << 15
     const void* pal; // palette: staged in LDS, or the record's
 };
 
@@ -1099,7 +1170,10 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
     for (uint32_t b = tid; b < nb; b += NT) {
         const uint2 e = ep[b >> 2];
         uint32_t r = ep_rank(e, 8u * b), bits = (e.x >> (8u * (b & 3u))) & 0xFFu;
-        for (; bits; bits &= bits - 1u) cm.list[r++] = (uint16_t)(8u * b + (uint32_t)__builtin_ctz(bits));
+        for (; bits; bits &= bits - 1u) {
+            const uint32_t q = 8u * b + (uint32_t)__builtin_ctz(bits);
+            cm.list[r++] = q | ((i == 5 ? (uint32_t)par4[q] : value5(sh, cm, q)) << 15);
+        }
     }
     if (with_bits)
         for (uint32_t w = tid; w < 1024u; w += NT) cm.ep5[w].x = 0;
@@ -1110,21 +1184,24 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
     uint32_t r_next = 0;
     bool bad = false;
     const uint32_t w_first = s0 >> 3, n_words = s1 > s0 ? ((s1 - 1u) >> 3) - w_first + 1u : 0u;
-    const uint32_t step = min((uint32_t)NT, (cm.cap - 8u) / 8u);  // words of a pass: their operations fit
+    // words of a pass: their operations fit the buffer; two words per thread when
+    // that still fills the work-group (a pass is bound by latency, not by work)
+    const uint32_t room = (cm.cap - 8u) / 8u, lr = room >= NT + NT / 2u ? 1u : 0u, step = min((uint32_t)NT << lr, room);
     for (uint32_t w = 0; w < n_words; w += step) {
         const uint32_t kbase = 8u * r_next;
-        if (!ops_pass<NT, true, true>(sh, sym, s0, s1, w_first + w, min(n_words - w, step), 0u, expected, kbase, cm.buf, rs,
+        if (!ops_pass<NT, true, true>(sh, sym, s0, s1, w_first + w, min(n_words - w, step), lr, expected, kbase, cm.buf, rs,
                                       pbuf, bad))
             return false;
+        // (the results of the pass before, which this one may read, have been
+        // stored by now; the other barriers of a pass exchange LDS only)
         __syncthreads();
         const uint32_t n_par = (rs.k >> 3) - r_next;
         for (uint32_t x = tid; x < n_par; x += NT) {
-            const uint32_t q = cm.list[r_next + x];
-            uint32_t raw[8], v[8], eb[3];
+            const uint32_t qv = cm.list[r_next + x], q = qv & 0x7FFFu, pv = qv >> 15;
+            uint32_t v[8], eb[3];
             bool inv[3], in[3], te[3];
-#pragma unroll
-            for (uint32_t c = 0; c < 8; ++c) raw[c] = cm.buf[8u * x + c];
-            const uint32_t pv = i == 5 ? (uint32_t)par4[q] : value5(sh, cm, q);
+            const uint4 ra = ((const uint4*)cm.buf)[2u * x], rb = ((const uint4*)cm.buf)[2u * x + 1u];
+            const uint32_t raw[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
             const uint32_t vox = (compact3(q >> 2) * 2u * S + compact3(q >> 1) * 2u) * S + compact3(q) * 2u;  // child 0's
 #pragma unroll
             for (uint32_t a = 0; a < 3; ++a) {
@@ -1151,17 +1228,16 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
                 for (uint32_t c = 0; c < 8; ++c) bits |= (raw[c] & STP) ? 0u : 1u << c;
                 ((uint8_t*)&cm.ep5[q >> 2].x)[q & 3u] = (uint8_t)bits;
             }
-#pragma unroll
-            for (uint32_t c = 0; c < 8; ++c) cm.buf[8u * x + c] = v[c];
+            ((uint4*)cm.buf)[2u * x] = make_uint4(v[0], v[1], v[2], v[3]);
+            ((uint4*)cm.buf)[2u * x + 1u] = make_uint4(v[4], v[5], v[6], v[7]);
         }
         // operations of a parent that the next pass completes move to the front
         const uint32_t rest = rs.k & 7u, keep = tid < rest ? cm.buf[8u * n_par + tid] : 0u;
-        __syncthreads();
+        lds_barrier();
         for (uint32_t x = tid; x < n_par; x += NT) {
-            const uint32_t q = cm.list[r_next + x];
-            uint32_t v[8], open;
-#pragma unroll
-            for (uint32_t c = 0; c < 8; ++c) v[c] = cm.buf[8u * x + c];
+            const uint32_t q = cm.list[r_next + x] & 0x7FFFu;
+            const uint4 ra = ((const uint4*)cm.buf)[2u * x], rb = ((const uint4*)cm.buf)[2u * x + 1u];
+            uint32_t v[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w}, open;
             do {
                 open = 0;
 #pragma unroll
@@ -1195,7 +1271,7 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
                 }
             }
         }
-        __syncthreads();
+        lds_barrier();
         if (tid < rest) cm.buf[tid] = keep;
         r_next += n_par;
     }
@@ -1218,11 +1294,17 @@ __device__ __forceinline__ void fill_implied(const Params& P, Shared& sh, const 
         const uint32_t ex = (ep[q >> 5].x >> (q & 31)) & 3u;  // the x neighbour differs in bit 0
         if (ex == 3u) continue;
         LT l[2];
-#pragma unroll
-        for (uint32_t hx = 0; hx < 2; ++hx) {
-            const uint32_t idx = L6 ? value5(sh, cm, q + hx) : (uint32_t)sh.G[fbase(4) + q + hx];
-            l[hx] = pal[min(idx, pc - 1u)];
+        uint32_t idx2;  // the two nodes' palette indices (level 5: they have one parent)
+        if (L6) {
+            const uint2 e4 = sh.EP[ebase(4) + (q >> 8)];
+            const uint32_t p4 = q >> 3;
+            idx2 = ep_bit(e4, p4) ? *(const uint32_t*)(cm.c5 + 8u * ep_rank(e4, p4) + (q & 7u))
+                                  : (uint32_t)sh.G[fbase(4) + p4] * 0x10001u;
+        } else {
+            idx2 = *(const uint32_t*)(sh.G + fbase(4) + q);
         }
+        l[0] = pal[min(idx2 & 0xFFFFu, pc - 1u)];
+        l[1] = pal[min(idx2 >> 16, pc - 1u)];
         LT* const o = out + ((2 * qz) * S + 2 * qy) * S + 4 * px;
 #pragma unroll
         for (uint32_t zy = 0; zy < 4; ++zy) {
@@ -1283,9 +1365,9 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
                 ChunkMem cm;
                 cm.ep5 = (uint2*)slots;
                 cm.buf = (uint32_t*)(cm.ep5 + 1024);
-                cm.cap = P.cap16 / 2u - 2048u;
+                cm.cap = slot_bytes(P.cap16) / 4u - 2048u;
                 cm.c5 = (uint16_t*)(scratch + kScrComp);
-                cm.list = (uint16_t*)(scratch + kScrList);
+                cm.list = (uint32_t*)(scratch + kScrList);
                 cm.pal = P.vol + uni64(sh.h.pal_off);
                 const uint32_t pb = uni(sh.h.pc) * P.label_bytes;
                 if (uni(sh.h.pc) <= kUBytesMin / P.label_bytes && !P.pal_bits) {  // (staged behind the next barrier)
@@ -1509,7 +1591,8 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
         if (fits && (step == 0u || wave < (overlap ? G : 0u))) {
             rans_rounds<NT>(P, sh, tab, (const uint16_t*)(lds + o_words), lds + o_sym, x0, overlap ? max(need, 1u) : 0u);
         } else if (step == 0u) {
-            rans_decode<NT>(P, sh, tab, nib);
+            if (uni(h.log2W) >= 6u && kStreamBytes * (NT / 64) <= o_tab - o_words) rans_stream<NT>(P, sh, tab, lds + o_words, nib);
+            else rans_decode<NT>(P, sh, tab, nib);
             __syncthreads();
         } else if (wave == (overlap ? G : 0u)) {
             // bounded: every group publishes ~0 when its rounds end
