@@ -94,6 +94,7 @@ struct Shared {
     uint32_t n_jobs;                // tasks of the launch for work-groups, and of each of its lists
     uint32_t small[2];              // claims on the lists for single wavefronts, this one and the next
     uint32_t job[kClasses];
+    alignas(16) uint16_t refs[64];  // open slots of levels 0..3
     alignas(16) uint4 pub[2][kMaxWaves];  // per pass and wave: run summary (exit states, counts)
     alignas(16) uint2 EP[kEWords];        // expansion bitmaps of levels 0..4: bits, prefix
     alignas(16) uint16_t G[kFullSlots];   // full grids of levels 0..4
@@ -950,110 +951,160 @@ __device__ __forceinline__ uint32_t node_below(uint32_t q, uint32_t am) {
     return (x ? (x - 1u) & am : 0u) | (q & ~am);
 }
 
-// Replace the references among 8 slots by the values at the ends of their
-// chains.  A reference points to an explicit node of the same level before its
-// source in Morton order, so chains end.
-__device__ __forceinline__ void chase8(const uint16_t* base, uint4* at) {
-    const uint4 w = *at;
-    if (!((w.x | w.y | w.z | w.w) & (kOpen * 0x10001u))) return;
-    int32_t v[8], low;  // sign-extended: open slots are negative
-#pragma unroll
-    for (uint32_t c = 0; c < 8; ++c) v[c] = (int16_t)half_of(w, c);
-    do {
+// The open slots of a row of 16-bit slots (bit c for child c).
+__device__ __forceinline__ uint32_t open_of(const uint4& w) {
+    const uint32_t m = ((w.x >> 15) & 0x10001u) | ((w.y >> 13) & 0x40004u) | ((w.z >> 11) & 0x100010u) | ((w.w >> 9) & 0x400040u);
+    return (m | (m >> 15)) & 0xFFu;
+}
+
+// Replace references by the values at the ends of their chains: the open slots
+// (bits of `open`) of the rows whose first slots are base[at], one row per lane.
+// A reference points to an explicit node of the same level before its source in
+// Morton order, so chains end.  About a fifth of the slots are open and a chain
+// has up to 20 links, so the wavefront first lists its open slots in LDS (`refs`,
+// room for `cap` >= 8, as many rows at a time as fit) and then follows one chain
+// per lane; following the 8 slots of a row side by side in each lane took three
+// times the instructions.
+template <typename V, V OPEN>
+__device__ __forceinline__ void chase_open(V* base, uint32_t at, uint32_t open, uint16_t* refs, uint32_t cap) {
+    const uint32_t lane = lane_id();
+    while (__ballot(open != 0u)) {
+        const uint32_t n = (uint32_t)__popc(open), incl = wave_incl_sum(n);
+        const bool now = incl <= cap;
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63 - __builtin_clzll(__ballot(now)));
+        if (now)
+            for (uint32_t k = incl - n; open; open &= open - 1u) refs[k++] = (uint16_t)(at + (uint32_t)__builtin_ctz(open));
+        lsync<64>();
+        for (uint32_t i = lane; i < total; i += 64u) {
+            const uint32_t me = refs[i];
+            uint32_t v = base[me];
+            while (v & OPEN) v = base[v ^ OPEN];
+            base[me] = (V)v;
+        }
+        lsync<64>();
+    }
+}
+
+// The list of the expanding nodes among the 8 * bytes nodes of a level, by rank:
+// each of NT threads lists those of some bytes of the bitmap.
+template <int NT>
+__device__ __forceinline__ void list_parents(const uint2* ep, uint32_t bytes, uint16_t* list) {
+    for (uint32_t b = threadIdx.x; b < bytes; b += NT) {
+        const uint2 e = ep[b >> 2];
+        uint32_t r = ep_rank(e, 8u * b), bits = (e.x >> (8u * (b & 3u))) & 0xFFu;
 #pragma unroll
         for (uint32_t c = 0; c < 8; ++c)
-            if (v[c] < 0) v[c] = ((const int16_t*)base)[v[c] + (int32_t)kOpen];
-        low = min(min(min(v[0], v[1]), min(v[2], v[3])), min(min(v[4], v[5]), min(v[6], v[7])));
-    } while (low < 0);
-    uint32_t u[8];
-#pragma unroll
-    for (uint32_t c = 0; c < 8; ++c) u[c] = (uint32_t)v[c];
-    *at = pack8(u);
+            if ((bits >> c) & 1u) list[r++] = (uint16_t)(8u * b + c);
+    }
 }
 
 // ------------------------------------------------------------- full levels
-// Level i <= 4 into its full grid: NT threads (64: the calling wavefront alone).
-// The operations are written compactly into the grid's own space, read back by
-// the parents they belong to, and then every node of level i - 1 writes its 8
-// children and their expansion bits: an expanding parent what its operations
-// say, any other its own value.
+// Level i <= 4 into its full grid: the calling wavefront alone (NT = 64, levels
+// 1..3: a lane per parent) or the work-group (level 4: a thread per expanding
+// parent, from a list in `work`).  The operations are written compactly into the
+// grid's own space, read back by the parents they belong to, and then every
+// parent writes its 8 children and their expansion bits: an expanding one what
+// its operations say, any other its own value.  work: LDS for lists of
+// references (and of the parents), work_bytes in all.
 template <int NT, typename SH>
 __device__ __forceinline__ bool full_level(SH& sh, const uint32_t* sym, uint32_t i, uint32_t nexp, uint32_t& adv,
-                                           uint32_t& pbuf) {
-    constexpr uint32_t PP = NT >= 512 ? 1u : NT == 64 ? 1u : 512u / NT;  // parents per thread (level 4; NT = 64: levels 1..3)
+                                           uint32_t& pbuf, uint8_t* work, uint32_t work_bytes) {
+    constexpr uint32_t PP = NT >= 512 ? 1u : NT == 64 ? 1u : 512u / NT;  // parents per thread
     constexpr uint32_t STP = SlotBits<false>::kStop;
     const uint32_t tid = threadIdx.x & (NT - 1);
     uint16_t* const grid = sh.G + fbase(i);
     const uint16_t* const par = sh.G + fbase(i - 1);
     const uint2* const ep = sh.EP + ebase(i - 1);
     const uint32_t np = 1u << (3 * (i - 1));
+    uint16_t* const list = (uint16_t*)work;
+    uint16_t* refs = (uint16_t*)work;
+    uint32_t cap = work_bytes / 2u;
+    if (NT > 64) {
+        constexpr uint32_t NW = NT / 64;
+        list_parents<NT>(ep, 64u, list);
+        cap = (work_bytes - 1024u) / (2u * NW);
+        refs += 512u + wave_id() * cap;
+    }
     bool bad = false;
     if (!ops_level<NT, true>(sh, sym, uni(sh.h.sym_end[i - 1]), uni(sh.h.sym_end[i]), 8u * nexp, grid, adv, pbuf, bad)) return false;
     lsync<NT>();
     uint4 raw[PP];
+    uint32_t qs[PP];
     bool ex[PP];
 #pragma unroll
     for (uint32_t p = 0; p < PP; ++p) {
-        const uint32_t q = tid + p * NT;
-        ex[p] = false;
-        if (q < np) {
-            const uint2 e = ep[q >> 5];
-            ex[p] = ep_bit(e, q);
-            if (ex[p]) raw[p] = *(const uint4*)(grid + 8u * ep_rank(e, q));
+        if (NT == 64) {
+            qs[p] = tid;
+            const uint2 e = ep[tid < np ? tid >> 5 : 0u];
+            ex[p] = tid < np && ep_bit(e, tid);
+            if (ex[p]) raw[p] = *(const uint4*)(grid + 8u * ep_rank(e, tid));
+        } else {
+            const uint32_t r = tid + p * NT;
+            ex[p] = r < nexp;
+            if (ex[p]) {
+                qs[p] = list[r];
+                raw[p] = *(const uint4*)(grid + 8u * r);
+            }
         }
     }
     lsync<NT>();
     const uint32_t mx = 0x09249249u & (np - 1u);
+    uint32_t open[PP];
 #pragma unroll
     for (uint32_t p = 0; p < PP; ++p) {
-        const uint32_t q = tid + p * NT;
-        if (q < np) {
-            const uint32_t pv = par[q];
-            uint32_t v[8], bits = 0;
-            if (ex[p]) {
-                uint32_t eb[3], ea[3];
-                bool inv[3];
+        open[p] = 0;
+        if (ex[p]) {
+            const uint32_t q = qs[p], pv = par[q];
+            uint32_t v[8], eb[3], ea[3];
+            bool inv[3];
 #pragma unroll
-                for (uint32_t a = 0; a < 3; ++a) {
-                    const uint32_t am = mx << a, tq = node_below(q, am);
-                    inv[a] = !(q & am);
-                    const bool te = !inv[a] && ep_bit(ep[tq >> 5], tq);
-                    eb[a] = te ? kOpen | (8u * tq) : par[tq];
-                    ea[a] = te ? 7u : 0u;
-                }
-                const uint4 w = raw[p];
-                const uint32_t keep = ~(STP * 0x10001u);
-                const uint4 ops = flip8(make_uint4(w.x & keep, w.y & keep, w.z & keep, w.w & keep));
-                resolve8<kOpen>(v, [&](uint32_t c) { return half_of(ops, c); }, pv,
-                              [&](uint32_t a, uint32_t c) { return eb[a] | ((c | (1u << a)) & ea[a]); }, inv, bad);
-                // (stop bits: children 0, 2, 4, 6 in the low halves, 1, 3, 5, 7 in the high ones)
-                const uint32_t m = ((w.x >> 14) & 0x10001u) | ((w.y >> 12) & 0x40004u) | ((w.z >> 10) & 0x100010u) |
-                                   ((w.w >> 8) & 0x400040u);
-                bits = ~(m | (m >> 15)) & 0xFFu;
-            } else {
-#pragma unroll
-                for (uint32_t c = 0; c < 8; ++c) v[c] = pv;
+            for (uint32_t a = 0; a < 3; ++a) {
+                const uint32_t am = mx << a, tq = node_below(q, am);
+                inv[a] = !(q & am);
+                const bool te = !inv[a] && ep_bit(ep[tq >> 5], tq);
+                eb[a] = te ? kOpen | (8u * tq) : par[tq];
+                ea[a] = te ? 7u : 0u;
             }
-            ((uint4*)grid)[q] = pack8(v);
+            const uint4 w = raw[p];
+            const uint32_t keep = ~(STP * 0x10001u);
+            const uint4 ops = flip8(make_uint4(w.x & keep, w.y & keep, w.z & keep, w.w & keep));
+            resolve8<kOpen>(v, [&](uint32_t c) { return half_of(ops, c); }, pv,
+                          [&](uint32_t a, uint32_t c) { return eb[a] | ((c | (1u << a)) & ea[a]); }, inv, bad);
+            // (stop bits: children 0, 2, 4, 6 in the low halves, 1, 3, 5, 7 in the high ones)
+            const uint32_t m = ((w.x >> 14) & 0x10001u) | ((w.y >> 12) & 0x40004u) | ((w.z >> 10) & 0x100010u) |
+                               ((w.w >> 8) & 0x400040u);
+            const uint32_t bits = ~(m | (m >> 15)) & 0xFFu;
+            const uint4 row = pack8(v);
+            open[p] = open_of(row);
+            ((uint4*)grid)[q] = row;
             uint2* const eo = sh.EP + ebase(i) + (q >> 2);
             if (i == 1) eo->x = bits;
             else ((uint8_t*)&eo->x)[q & 3u] = (uint8_t)bits;
         }
     }
+    // the other parents
+    for (uint32_t q = tid; q < np; q += NT) {
+        if (!ep_bit(ep[q >> 5], q)) {
+            const uint32_t v2 = par[q] * 0x10001u;
+            ((uint4*)grid)[q] = make_uint4(v2, v2, v2, v2);
+            uint2* const eo = sh.EP + ebase(i) + (q >> 2);
+            if (i == 1) eo->x = 0;
+            else ((uint8_t*)&eo->x)[q & 3u] = 0;
+        }
+    }
     if (bad) sh.err = 1u;
     lsync<NT>();
 #pragma unroll
-    for (uint32_t p = 0; p < PP; ++p)
-        if (ex[p]) chase8(grid, (uint4*)grid + (tid + p * NT));
+    for (uint32_t p = 0; p < PP; ++p) chase_open<uint16_t, kOpen>(grid, 8u * qs[p], open[p], refs, cap);
     return true;
 }
 
 // Levels 0..last (at most 3) by the calling wavefront alone; then the parent
 // prefix of the next level, the number of its expanding nodes in sh.nexp and
-// the ADV count in sh.adv.  Level 0 is one node whose only valid operation is
+// the ADV count in sh.adv; work: LDS for lists of references.  Level 0 is one node whose only valid operation is
 // PALETTE_ADV (entry 0), with or without a stop bit.
 template <typename SH>
-__device__ __forceinline__ void small_levels(SH& sh, const uint32_t* sym, uint32_t last) {
+__device__ __forceinline__ void small_levels(SH& sh, const uint32_t* sym, uint32_t last, uint8_t* work, uint32_t work_bytes) {
     const uint32_t s0 = sym[0] & 15u;
     if (uni(sh.h.sym_end[0]) != 1u || (s0 & 7u) != kAdv || uni(sh.h.pc) == 0u) {
         sh.err = 1u;
@@ -1066,7 +1117,7 @@ __device__ __forceinline__ void small_levels(SH& sh, const uint32_t* sym, uint32
     lsync<64>();
     uint32_t adv = 1, pbuf = 0, nexp = s0 & 8u ? 0u : 1u;
     for (uint32_t i = 1; i <= last; ++i) {
-        if (!full_level<64>(sh, sym, i, nexp, adv, pbuf)) {
+        if (!full_level<64>(sh, sym, i, nexp, adv, pbuf, work, work_bytes)) {
             sh.err = 1u;
             return;
         }
@@ -1084,19 +1135,12 @@ __device__ __forceinline__ void small_levels(SH& sh, const uint32_t* sym, uint32
 // Level 5 of a 32^3 cube at full resolution: its explicit nodes by operation
 // rank in the slot area (child c of the r-th expanding parent at 8r + c).
 template <int NT>
-__device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t* c5, uint8_t* u_area, uint32_t nexp,
+__device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t* c5, uint8_t* u_area, uint32_t u_bytes, uint32_t nexp,
                                        uint32_t pal_words, const uint32_t* pal, uint32_t& adv, uint32_t& pbuf) {
     const uint2* const ep = sh.EP + ebase(4);
     const uint16_t* const par = sh.G + fbase(4);
     uint16_t* const list = (uint16_t*)u_area;
-    // the expanding parents by rank: each thread lists those of some bytes of the bitmap
-    for (uint32_t b = threadIdx.x; b < 512u; b += NT) {
-        const uint2 e = ep[b >> 2];
-        uint32_t r = ep_rank(e, 8u * b), bits = (e.x >> (8u * (b & 3u))) & 0xFFu;
-#pragma unroll
-        for (uint32_t c = 0; c < 8; ++c)
-            if ((bits >> c) & 1u) list[r++] = (uint16_t)(8u * b + c);
-    }
+    list_parents<NT>(ep, 512u, list);
     bool bad = false;
     if (!ops_level<NT, false>(sh, sym, uni(sh.h.sym_end[4]), uni(sh.h.sym_end[5]), 8u * nexp, c5, adv, pbuf, bad)) return false;
     lds_barrier();
@@ -1120,9 +1164,15 @@ __device__ __forceinline__ bool level5(Shared& sh, const uint32_t* sym, uint16_t
     }
     if (bad) sh.err = 1u;
     lds_barrier();
-    // the palette, over the parent list (which has been read), for the output pass
+    // the parent list has been read: its area takes the palette, for the output
+    // pass, and the lists of references
     for (uint32_t w = threadIdx.x; w < pal_words; w += NT) ((uint32_t*)u_area)[w] = pal[w];
-    for (uint32_t r = threadIdx.x; r < nexp; r += NT) chase8(c5, (uint4*)c5 + r);
+    const uint32_t cap = (u_bytes - 4u * pal_words) / (2u * (NT / 64));
+    uint16_t* const refs = (uint16_t*)(u_area + 4u * pal_words) + wave_id() * cap;
+    for (uint32_t r0 = 64u * wave_id(); r0 < nexp; r0 += NT) {
+        const uint32_t r = r0 + lane_id();
+        chase_open<uint16_t, kOpen>(c5, 8u * r, r < nexp ? open_of(((const uint4*)c5)[r]) : 0u, refs, cap);
+    }
     return true;
 }
 
@@ -1145,6 +1195,8 @@ struct ChunkMem {
     uint16_t* c5;    // scratch: level-5 palette indices by operation rank
     uint32_t* list;  // scratch: expanding parents by rank, node | palette index << 15
     const void* pal; // palette: staged in LDS, or the record's
+    uint8_t* work;   // LDS for lists of references
+    uint32_t work_bytes;
 };
 
 // palette index of a level-5 node (64^3 cubes; levels 4 and 5 final)
@@ -1165,6 +1217,8 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
     const bool with_bits = i == 5 && uni(sh.h.t) == 6;
     LT* const out = (LT*)(P.out + uni64(sh.h.out_off) * sizeof(LT));
     const bool vec = ((uintptr_t)out & (2 * sizeof(LT) - 1)) == 0;
+    const uint32_t cap = cm.work_bytes / (2u * (NT / 64));
+    uint16_t* const refs = (uint16_t*)cm.work + wave_id() * cap;
     // expanding parents by rank
     const uint32_t nb = 1u << (3 * (i - 1) - 3);
     for (uint32_t b = tid; b < nb; b += NT) {
@@ -1234,18 +1288,20 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
         // operations of a parent that the next pass completes move to the front
         const uint32_t rest = rs.k & 7u, keep = tid < rest ? cm.buf[8u * n_par + tid] : 0u;
         lds_barrier();
-        for (uint32_t x = tid; x < n_par; x += NT) {
+        for (uint32_t x0 = 64u * wave_id(); x0 < n_par; x0 += NT) {
+            const uint32_t x = x0 + lane_id();
+            uint32_t open = 0;
+            if (x < n_par) {
+                const uint4 ra = ((const uint4*)cm.buf)[2u * x], rb = ((const uint4*)cm.buf)[2u * x + 1u];
+                const uint32_t o[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c) open |= (o[c] & OPEN) ? 1u << c : 0u;
+            }
+            chase_open<uint32_t, OPEN>(cm.buf, 8u * x, open, refs, cap);
+            if (x >= n_par) continue;
             const uint32_t q = cm.list[r_next + x] & 0x7FFFu;
             const uint4 ra = ((const uint4*)cm.buf)[2u * x], rb = ((const uint4*)cm.buf)[2u * x + 1u];
-            uint32_t v[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w}, open;
-            do {
-                open = 0;
-#pragma unroll
-                for (uint32_t c = 0; c < 8; ++c) {
-                    if (v[c] & OPEN) v[c] = cm.buf[v[c] ^ OPEN];
-                    open |= v[c];
-                }
-            } while (open & OPEN);
+            uint32_t v[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
             // (both candidates are loaded, at clamped places: no branch around the loads)
             if (!LABELS) {
 #pragma unroll
@@ -1337,7 +1393,7 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
     bool ok = true;
     labels = true;
     if (t >= 4) {
-        ok = full_level<NT>(sh, sym, 4, uni(sh.nexp), adv, pbuf);
+        ok = full_level<NT>(sh, sym, 4, uni(sh.nexp), adv, pbuf, u_area, list_bytes(P.cap16));
         if (ok && t >= 5) {
             if (wave == 0) {
                 const uint32_t n = level_prefix(sh.EP + ebase(4), ewords(4));
@@ -1357,9 +1413,9 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
                 __syncthreads();
             }
             if (in_lds) {
-                pal_lds = !P.pal_bits && uni(sh.h.pc) <= list_bytes(P.cap16) / P.label_bytes;
+                pal_lds = !P.pal_bits && uni(sh.h.pc) <= list_bytes(P.cap16) / 2u / P.label_bytes;
                 rows = (uint16_t*)(u_area + o_rows);
-                ok = level5<NT>(sh, sym, rows, u_area, nexp, pal_lds ? uni(sh.h.pc) * P.label_bytes / 4u : 0u,
+                ok = level5<NT>(sh, sym, rows, u_area, o_rows, nexp, pal_lds ? uni(sh.h.pc) * P.label_bytes / 4u : 0u,
                                 (const uint32_t*)(P.vol + uni64(sh.h.pal_off)), adv, pbuf);
             } else {
                 ChunkMem cm;
@@ -1370,9 +1426,13 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
                 cm.list = (uint32_t*)(scratch + kScrList);
                 cm.pal = P.vol + uni64(sh.h.pal_off);
                 const uint32_t pb = uni(sh.h.pc) * P.label_bytes;
-                if (uni(sh.h.pc) <= kUBytesMin / P.label_bytes && !P.pal_bits) {  // (staged behind the next barrier)
+                cm.work = u_area;
+                cm.work_bytes = list_bytes(P.cap16);
+                if (uni(sh.h.pc) <= kUBytesMin / 2u / P.label_bytes && !P.pal_bits) {  // (staged behind the next barrier)
                     for (uint32_t w = threadIdx.x; w < pb / 4u; w += NT) ((uint32_t*)u_area)[w] = ((const uint32_t*)cm.pal)[w];
                     cm.pal = u_area;
+                    cm.work += pb;
+                    cm.work_bytes -= pb;
                 }
                 c5g = cm.c5;
                 if (t == 6 || P.pal_bits) {
@@ -1600,7 +1660,7 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
                 for (uint32_t g = 0; g < G; ++g)
                     while (__hip_atomic_load(&sh.prog[g], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < need)
                         __builtin_amdgcn_s_sleep(1);
-            small_levels(sh, sym, small);
+            small_levels(sh, sym, small, (uint8_t*)sh.refs, (uint32_t)sizeof(sh.refs));
         } else if (threadIdx.x == NT - 64 && !ah.done) {
             parse_ahead(P, sh, ah.jt);
             ah.done = true;
@@ -1720,7 +1780,8 @@ __device__ __forceinline__ void wave_task(const Params& P, WaveShared& ws, const
     for (uint32_t k = 0; k < 2; ++k)
         if (4u * (64u * k + lane) < pal_bytes) ws.pal[64u * k + lane] = pw[k];
     lsync<64>();
-    small_levels(ws, sym, t);
+    const uint32_t used = sym == (const uint32_t*)area ? (4u * n_words + 15u) & ~15u : 0u;
+    small_levels(ws, sym, t, area + used, area_bytes - used);
     lsync<64>();
     if (uni(ws.err) || (t == uni(h.L) && uni(ws.adv) != pc)) {
         ws.err = 1u;
