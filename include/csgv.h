@@ -103,7 +103,10 @@ typedef struct {
     uint32_t max_palette;  /* largest palette count of any record (|P|max of cache paletting) */
 } csgv_volume_info;
 
-/* Launch shape.  Zero (or -1 for sort_tasks) selects the default. */
+/* Launch shape.  Zero (or -1 for sort_tasks) selects the default.  While wg_size,
+   lds_slots and wgs_per_cu are all left at their defaults, a launch of at most
+   two tasks per compute unit runs work-groups of 512 threads with a larger LDS
+   split. */
 typedef struct {
     int mode;            /* CSGV_MODE_* (plans are always PERSISTENT)                      */
     int wg_size;         /* work-group size 128, 256, 512 or 1024; default 256              */

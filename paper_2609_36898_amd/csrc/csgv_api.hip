@@ -79,6 +79,20 @@ int resident_per_cu(int wg, uint32_t cap16) {
     return std::max(1, std::min(by_lds, max_resident_per_cu(wg, std::max<uint32_t>(cap16, kMinCap16))));
 }
 
+// The shape of a launch whose work-group size and LDS split the caller left to
+// the default.  With at most two tasks per CU a task's latency is the launch's,
+// and 512 threads shorten it (64 bricks of 32^3: 58 -> 50 us, 512: 63 -> 55; 64
+// bricks of 64^3 0.63 -> 0.47 ms; 1024 threads 55 and 89 us and 0.41 ms); such
+// work-groups leave LDS for 24,576 slots, which hold level 5 of most 64^3 bricks
+// at LOD 1 (512 cubes: 0.18 -> 0.14 ms).  From three tasks per CU on,
+// work-groups of 256 threads keep more bricks in flight.
+void auto_shape(uint32_t n, int* wg, uint32_t* cap16) {
+    if (n <= 2u * (uint32_t)device_cus()) {
+        *wg = 512;
+        *cap16 = 24576;
+    }
+}
+
 RansFreq pack_freq(const csgv_volume_info* vol, bool* ok) {
     RansFreq f;
     uint32_t sum = 0;
@@ -287,6 +301,7 @@ csgv_status prepare_call(const csgv_volume_info* vol, const void* d_container, c
     if (opts && opts->lds_slots > 0) P->cap16 = std::max<uint32_t>((uint32_t)opts->lds_slots, kMinCap16) & ~7u;
     if (opts && opts->palette_bits > 0) P->pal_bits = (uint32_t)opts->palette_bits;
     *wg = opts && opts->wg_size ? opts->wg_size : 256;
+    if (!(opts && (opts->wg_size || opts->lds_slots || opts->wgs_per_cu > 0))) auto_shape(n, wg, &P->cap16);
     *per_cu = opts && opts->wgs_per_cu > 0 ? opts->wgs_per_cu : resident_per_cu(*wg, P->cap16);
     return CSGV_OK;
 }
@@ -335,6 +350,7 @@ struct csgv_plan {
     csgv_volume_info vol;
     uint32_t max_tasks = 0;
     csgv_decode_opts opts;
+    bool auto_shape = false;  // the caller never chose a shape
     uint32_t grid = 0;
     uint64_t scratch_bytes = 0;
     uint8_t* mem = nullptr;
@@ -354,7 +370,9 @@ csgv_status plan_enqueue(csgv_plan* p, hipStream_t s, const Params& P0, bool wit
     Params P = P0;
     P.cap16 = std::max<uint32_t>((uint32_t)p->opts.lds_slots, kMinCap16) & ~7u;
     P.pal_bits = p->opts.palette_bits > 0 ? (uint32_t)p->opts.palette_bits : 0u;
-    hipError_t e = enqueue(P, p->b, &p->vol, p->opts.wg_size, plan_grid(p, P.n_tasks), true, p->opts.sort_tasks != 0, s,
+    int wg = p->opts.wg_size;
+    if (p->auto_shape) auto_shape(P.n_tasks, &wg, &P.cap16);
+    hipError_t e = enqueue(P, p->b, &p->vol, wg, plan_grid(p, P.n_tasks), true, p->opts.sort_tasks != 0, s,
                            with_events ? p->ev0 : nullptr, with_events ? p->ev1 : nullptr);
     if (e != hipSuccess) return fail(CSGV_EHIP, "plan launch: %s", hipGetErrorString(e));
     return CSGV_OK;
@@ -404,6 +422,7 @@ csgv_status csgv_plan_create(const csgv_volume_info* vol, uint32_t max_tasks, co
     if (st != CSGV_OK) return st;
     HIP_TRY(ensure_attrs());
     csgv_plan* p = new csgv_plan();
+    p->auto_shape = !(opts && (opts->wg_size || opts->lds_slots || opts->wgs_per_cu > 0));
     p->vol = *vol;
     p->max_tasks = max_tasks;
     p->opts.mode = CSGV_MODE_PERSISTENT;
@@ -449,6 +468,7 @@ csgv_status csgv_plan_set_opts(csgv_plan* p, const csgv_decode_opts* o) {
     if (o->palette_bits >= 0) n.palette_bits = o->palette_bits;
     const csgv_decode_opts old = p->opts;
     p->opts = n;
+    if (o->wg_size || o->lds_slots > 0 || o->wgs_per_cu > 0) p->auto_shape = false;
     if ((st = plan_alloc(p)) != CSGV_OK) {
         p->opts = old;
         return st;
