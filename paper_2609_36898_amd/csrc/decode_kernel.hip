@@ -106,6 +106,15 @@ static_assert(offsetof(Shared, G) + sizeof(Shared::G) == sizeof(Shared),
 
 // ------------------------------------------------------ wave/block helpers
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
+// The launch's parameters, read again from the kernel arguments: held in scalar
+// registers over the whole kernel they push loop masks and counters out of them
+// (spills to vector lanes).  Every phase takes its own.
+__device__ __forceinline__ const Params& params() {
+    auto p = (const __attribute__((address_space(4))) Params*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const Params*)p;
+}
+
 // a value that is the same in every lane of the wavefront, in a scalar register
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 __device__ __forceinline__ uint64_t uni64(uint64_t v) { return ((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v); }
@@ -299,7 +308,7 @@ __device__ __forceinline__ void parse_ahead(const Params& P, Shared& sh, uint32_
         for (; c < kClasses - 1u && jt >= sh.job[c]; ++c) jt -= sh.job[c];
         task = P.lists[(uint64_t)c * P.list_cap + jt];
     }
-    parse_task(P, task, hn);
+    parse_task(params(), task, hn);
 }
 
 // The next claim of a work-group after jt; its first task is its own number.
@@ -1194,7 +1203,8 @@ struct ChunkMem {
     uint32_t cap;    // its 32-bit slots
     uint16_t* c5;    // scratch: level-5 palette indices by operation rank
     uint32_t* list;  // scratch: expanding parents by rank, node | palette index << 15
-    const void* pal; // palette: staged in LDS, or the record's
+    const void* pal;         // palette of the record
+    const uint8_t* pal_lds;  // the same in LDS, or null
     uint8_t* work;   // LDS for lists of references
     uint32_t work_bytes;
 };
@@ -1224,10 +1234,14 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
     for (uint32_t b = tid; b < nb; b += NT) {
         const uint2 e = ep[b >> 2];
         uint32_t r = ep_rank(e, 8u * b), bits = (e.x >> (8u * (b & 3u))) & 0xFFu;
-        for (; bits; bits &= bits - 1u) {
-            const uint32_t q = 8u * b + (uint32_t)__builtin_ctz(bits);
-            cm.list[r++] = q | ((i == 5 ? (uint32_t)par4[q] : value5(sh, cm, q)) << 15);
-        }
+        if (!bits) continue;
+        // the values of 8 nodes at once: a row of the grid, or of c5 (level-5 nodes
+        // 8b .. 8b + 7 are the children of level-4 node b, which expands)
+        const uint4 row = i == 5 ? ((const uint4*)par4)[b]
+                                 : ((const uint4*)cm.c5)[ep_rank(sh.EP[ebase(4) + (b >> 5)], b)];
+#pragma unroll
+        for (uint32_t c = 0; c < 8; ++c)
+            if ((bits >> c) & 1u) cm.list[r++] = (8u * b + c) | (half_of(row, c) << 15);
     }
     if (with_bits)
         for (uint32_t w = tid; w < 1024u; w += NT) cm.ep5[w].x = 0;
@@ -1290,8 +1304,9 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
         lds_barrier();
         for (uint32_t x0 = 64u * wave_id(); x0 < n_par; x0 += NT) {
             const uint32_t x = x0 + lane_id();
-            uint32_t open = 0;
+            uint32_t open = 0, q = 0;
             if (x < n_par) {
+                q = cm.list[r_next + x] & 0x7FFFu;  // (needed after the chains)
                 const uint4 ra = ((const uint4*)cm.buf)[2u * x], rb = ((const uint4*)cm.buf)[2u * x + 1u];
                 const uint32_t o[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
 #pragma unroll
@@ -1299,31 +1314,40 @@ __device__ __forceinline__ bool chunk_level(const Params& P, Shared& sh, const C
             }
             chase_open<uint32_t, OPEN>(cm.buf, 8u * x, open, refs, cap);
             if (x >= n_par) continue;
-            const uint32_t q = cm.list[r_next + x] & 0x7FFFu;
             const uint4 ra = ((const uint4*)cm.buf)[2u * x], rb = ((const uint4*)cm.buf)[2u * x + 1u];
             uint32_t v[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
-            // (both candidates are loaded, at clamped places: no branch around the loads)
+            // (loads at clamped places instead of branches around them, and none of
+            // earlier results when no lane needs one)
+            const bool any = __ballot(((v[0] | v[1] | v[2] | v[3] | v[4] | v[5] | v[6] | v[7]) & kChunkDone) != 0u);
             if (!LABELS) {
+                uint32_t got[8];
+                if (any)
 #pragma unroll
-                for (uint32_t c = 0; c < 8; ++c) {
-                    const bool done = v[c] & kChunkDone;
-                    const uint32_t at = v[c] & (kChunkDone - 1u), got = cm.c5[done ? at : 0u];
-                    v[c] = done ? got : at & 0xFFFFu;
-                }
+                    for (uint32_t c = 0; c < 8; ++c) got[c] = cm.c5[(v[c] & kChunkDone) ? v[c] & (kChunkDone - 1u) : 0u];
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c) v[c] = (v[c] & kChunkDone) ? got[c] : v[c] & 0xFFFFu;
                 ((uint4*)cm.c5)[r_next + x] = pack8(v);
             } else {
-                LT l[8];
-#pragma unroll
-                for (uint32_t c = 0; c < 8; ++c) {
-                    const bool done = v[c] & kChunkDone;
-                    const uint32_t at = v[c] & (kChunkDone - 1u);
-                    const LT got = out[done ? at : 0u], own = pal[min(done ? 0u : at, pc - 1u)];
-                    l[c] = done ? got : own;
-                }
                 LT* const o = out + (compact3(q >> 2) * 2u * S + compact3(q >> 1) * 2u) * S + compact3(q) * 2u;
 #pragma unroll
-                for (uint32_t zy = 0; zy < 4; ++zy) {
-                    store2<LT>(o + ((zy >> 1) * S + (zy & 1u)) * S, l[2 * zy], l[2 * zy + 1], vec);
+                for (uint32_t z = 0; z < 2; ++z) {  // (4 children at a time: registers)
+                    LT l[4], got[4];
+                    const uint32_t* const vz = v + 4u * z;
+                    if (any)
+#pragma unroll
+                        for (uint32_t c = 0; c < 4; ++c) got[c] = out[(vz[c] & kChunkDone) ? vz[c] & (kChunkDone - 1u) : 0u];
+                    if (cm.pal_lds) {
+                        const LT* const lp = (const LT*)cm.pal_lds;
+#pragma unroll
+                        for (uint32_t c = 0; c < 4; ++c) l[c] = lp[(vz[c] & kChunkDone) ? 0u : min(vz[c], pc - 1u)];
+                    } else {
+#pragma unroll
+                        for (uint32_t c = 0; c < 4; ++c) l[c] = pal[(vz[c] & kChunkDone) ? 0u : min(vz[c], pc - 1u)];
+                    }
+#pragma unroll
+                    for (uint32_t c = 0; c < 4; ++c) l[c] = (vz[c] & kChunkDone) ? got[c] : l[c];
+                    store2<LT>(o + z * S * S, l[0], l[1], vec);
+                    store2<LT>(o + z * S * S + S, l[2], l[3], vec);
                 }
             }
         }
@@ -1359,8 +1383,14 @@ __device__ __forceinline__ void fill_implied(const Params& P, Shared& sh, const 
         } else {
             idx2 = *(const uint32_t*)(sh.G + fbase(4) + q);
         }
-        l[0] = pal[min(idx2 & 0xFFFFu, pc - 1u)];
-        l[1] = pal[min(idx2 >> 16, pc - 1u)];
+        const uint32_t i0 = min(idx2 & 0xFFFFu, pc - 1u), i1 = min(idx2 >> 16, pc - 1u);
+        if (cm.pal_lds) {
+            l[0] = ((const LT*)cm.pal_lds)[i0];
+            l[1] = ((const LT*)cm.pal_lds)[i1];
+        } else {
+            l[0] = pal[i0];
+            l[1] = pal[i1];
+        }
         LT* const o = out + ((2 * qz) * S + 2 * qy) * S + 4 * px;
 #pragma unroll
         for (uint32_t zy = 0; zy < 4; ++zy) {
@@ -1425,18 +1455,19 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
                 cm.c5 = (uint16_t*)(scratch + kScrComp);
                 cm.list = (uint32_t*)(scratch + kScrList);
                 cm.pal = P.vol + uni64(sh.h.pal_off);
+                cm.pal_lds = nullptr;
                 const uint32_t pb = uni(sh.h.pc) * P.label_bytes;
                 cm.work = u_area;
                 cm.work_bytes = list_bytes(P.cap16);
                 if (uni(sh.h.pc) <= kUBytesMin / 2u / P.label_bytes && !P.pal_bits) {  // (staged behind the next barrier)
                     for (uint32_t w = threadIdx.x; w < pb / 4u; w += NT) ((uint32_t*)u_area)[w] = ((const uint32_t*)cm.pal)[w];
-                    cm.pal = u_area;
+                    cm.pal_lds = u_area;
                     cm.work += pb;
                     cm.work_bytes -= pb;
                 }
                 c5g = cm.c5;
                 if (t == 6 || P.pal_bits) {
-                    ok = chunk_level<NT, false, uint32_t>(P, sh, cm, sym, 5, nexp, adv, pbuf);
+                    ok = chunk_level<NT, false, uint32_t>(params(), sh, cm, sym, 5, nexp, adv, pbuf);
                     if (ok && t == 6) {
                         if (wave == 0) {
                             const uint32_t n = level_prefix(cm.ep5, 1024u);
@@ -1447,8 +1478,8 @@ __device__ __forceinline__ bool decode_levels(const Params& P, Shared& sh, uint8
                 __syncthreads();
                 if (ok && !P.pal_bits) {
                     labels = false;
-                    ok = P.label_bytes == 4 ? chunk_labels<NT, uint32_t>(P, sh, cm, sym, adv, pbuf)
-                                            : chunk_labels<NT, uint64_t>(P, sh, cm, sym, adv, pbuf);
+                    ok = P.label_bytes == 4 ? chunk_labels<NT, uint32_t>(params(), sh, cm, sym, adv, pbuf)
+                                            : chunk_labels<NT, uint64_t>(params(), sh, cm, sym, adv, pbuf);
                 }
             }
         }
@@ -1598,7 +1629,7 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     Shared& sh = *reinterpret_cast<Shared*>(lds);
     const TaskHdr& h = sh.h;
     if (uni(h.status) != kTaskOk) {
-        if (uni(h.status) == kTaskCorrupt && uni(h.write_ok)) zero_output<NT>(P, h);
+        if (uni(h.status) == kTaskCorrupt && uni(h.write_ok)) zero_output<NT>(params(), h);
         return;
     }
     const uint32_t u_bytes = list_bytes(P.cap16);
@@ -1640,7 +1671,7 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
         }
     } else {
         if (threadIdx.x < 4) sh.prog[threadIdx.x] = 0;
-        x0 = rans_stage<NT>(P, h, (uint16_t*)(lds + o_words), words_bytes, uni(sh.tab_ok) ? nullptr : (uint4*)(lds + o_tab));
+        x0 = rans_stage<NT>(params(), h, (uint16_t*)(lds + o_words), words_bytes, uni(sh.tab_ok) ? nullptr : (uint4*)(lds + o_tab));
         lds_barrier();
     }
     // step 0 decodes the symbols; step 1 levels 0..3, on one wavefront, while lane
@@ -1649,10 +1680,10 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     for (uint32_t step = rans && !overlap ? 0u : 1u; step < 2u; ++step) {
         const uint32_t* const tab = (const uint32_t*)(lds + o_tab);
         if (fits && (step == 0u || wave < (overlap ? G : 0u))) {
-            rans_rounds<NT>(P, sh, tab, (const uint16_t*)(lds + o_words), lds + o_sym, x0, overlap ? max(need, 1u) : 0u);
+            rans_rounds<NT>(params(), sh, tab, (const uint16_t*)(lds + o_words), lds + o_sym, x0, overlap ? max(need, 1u) : 0u);
         } else if (step == 0u) {
-            if (uni(h.log2W) >= 6u && kStreamBytes * (NT / 64) <= o_tab - o_words) rans_stream<NT>(P, sh, tab, lds + o_words, nib);
-            else rans_decode<NT>(P, sh, tab, nib);
+            if (uni(h.log2W) >= 6u && kStreamBytes * (NT / 64) <= o_tab - o_words) rans_stream<NT>(params(), sh, tab, lds + o_words, nib);
+            else rans_decode<NT>(params(), sh, tab, nib);
             __syncthreads();
         } else if (wave == (overlap ? G : 0u)) {
             // bounded: every group publishes ~0 when its rounds end
@@ -1662,7 +1693,7 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
                         __builtin_amdgcn_s_sleep(1);
             small_levels(sh, sym, small, (uint8_t*)sh.refs, (uint32_t)sizeof(sh.refs));
         } else if (threadIdx.x == NT - 64 && !ah.done) {
-            parse_ahead(P, sh, ah.jt);
+            parse_ahead(params(), sh, ah.jt);
             ah.done = true;
         }
         lds_barrier();
@@ -1672,22 +1703,22 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     if (ok) {
         uint16_t *rows = slots, *c5g = nullptr;
         bool labels, pal_lds = false;
-        ok = decode_levels<NT>(P, sh, u_area, slots, scratch, sym, fits ? o_sym - o_tab : 0u, rows, c5g, labels, pal_lds);
+        ok = decode_levels<NT>(params(), sh, u_area, slots, scratch, sym, fits ? o_sym - o_tab : 0u, rows, c5g, labels, pal_lds);
         if (ok && labels) {
             if (P.pal_bits) {
-                if (c5g) write_indices<NT, true>(P, sh, c5g);
-                else write_indices<NT, false>(P, sh, rows);
+                if (c5g) write_indices<NT, true>(params(), sh, c5g);
+                else write_indices<NT, false>(params(), sh, rows);
             } else if (P.label_bytes == 4) {
-                write_output<NT, uint32_t>(P, sh, u_area, rows, pal_lds);
+                write_output<NT, uint32_t>(params(), sh, u_area, rows, pal_lds);
             } else {
-                write_output<NT, uint64_t>(P, sh, u_area, rows, pal_lds);
+                write_output<NT, uint64_t>(params(), sh, u_area, rows, pal_lds);
             }
         }
     }
     if (!ok) {
         __syncthreads();  // the zeros come after what the work-group has written
         if (threadIdx.x == 0) sh.h.status = kTaskCorrupt;
-        zero_output<NT>(P, h);
+        zero_output<NT>(params(), h);
     }
     // (read again only after the task loop's next barriers)
     if (threadIdx.x == 0) sh.tab_ok = t >= 5 ? 0u : rans ? 1u : sh.tab_ok;
@@ -1768,10 +1799,10 @@ __device__ __forceinline__ void wave_task(const Params& P, WaveShared& ws, const
                 }
             }
             lsync<64>();
-            rans_rounds<64>(P, ws, tab, (const uint16_t*)area, area, x0, 0u);
+            rans_rounds<64>(params(), ws, tab, (const uint16_t*)area, area, x0, 0u);
             sym = (const uint32_t*)area;
         } else {
-            rans_decode<64>(P, ws, tab, nib);
+            rans_decode<64>(params(), ws, tab, nib);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         }
@@ -1787,11 +1818,11 @@ __device__ __forceinline__ void wave_task(const Params& P, WaveShared& ws, const
         ws.err = 1u;
         return;
     }
-    if (P.pal_bits) write_indices<64, false>(P, ws, (const uint16_t*)nullptr);
-    else if (P.label_bytes == 4 && pal_bytes) write_labels<64, uint32_t, true>(P, ws, (const uint32_t*)ws.pal);
-    else if (P.label_bytes == 4) write_labels<64, uint32_t, false>(P, ws, (const uint32_t*)nullptr);
-    else if (pal_bytes) write_labels<64, uint64_t, true>(P, ws, (const uint64_t*)ws.pal);
-    else write_labels<64, uint64_t, false>(P, ws, (const uint64_t*)nullptr);
+    if (P.pal_bits) write_indices<64, false>(params(), ws, (const uint16_t*)nullptr);
+    else if (P.label_bytes == 4 && pal_bytes) write_labels<64, uint32_t, true>(params(), ws, (const uint32_t*)ws.pal);
+    else if (P.label_bytes == 4) write_labels<64, uint32_t, false>(params(), ws, (const uint32_t*)nullptr);
+    else if (pal_bytes) write_labels<64, uint64_t, true>(params(), ws, (const uint64_t*)ws.pal);
+    else write_labels<64, uint64_t, false>(params(), ws, (const uint64_t*)nullptr);
 }
 
 template <int NT>
@@ -1824,7 +1855,7 @@ __device__ __forceinline__ void wave_tasks(const Params& P, uint8_t* lds, uint8_
             const uint32_t k = k0 + lane;
             const uint32_t task = k < n_first ? P.lists[(uint64_t)kWgClasses * P.list_cap + k]
                                               : P.lists[(uint64_t)(kWgClasses + 1) * P.list_cap + (k - n_first)];
-            parse_task(P, task, ws.q[lane]);
+            parse_task(params(), task, ws.q[lane]);
         }
         lsync<64>();
         for (uint32_t x = 0; x < m; ++x) {
@@ -1833,11 +1864,11 @@ __device__ __forceinline__ void wave_tasks(const Params& P, uint8_t* lds, uint8_
             lsync<64>();
             uint32_t status = uni(ws.h.status);
             if (status == kTaskOk) {
-                wave_task(P, ws, (const uint32_t*)(lds + o_tab), area, area_bytes, nib);
+                wave_task(params(), ws, (const uint32_t*)(lds + o_tab), area, area_bytes, nib);
                 lsync<64>();
                 if (uni(ws.err)) status = kTaskCorrupt;
             }
-            if (status == kTaskCorrupt && uni(ws.h.write_ok)) zero_output<64>(P, ws.h);
+            if (status == kTaskCorrupt && uni(ws.h.write_ok)) zero_output<64>(params(), ws.h);
             if (lane == 0 && P.status) P.status[uni(ws.h.task)] = status;
             lsync<64>();
         }
@@ -1872,7 +1903,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
         }
         sh.n_jobs = n;
         ah.jt = blockIdx.x;
-        parse_ahead(P, sh, ah.jt);
+        parse_ahead(params(), sh, ah.jt);
     }
     if (tid == 0) sh.tab_ok = 0;
     for (;;) {
@@ -1883,17 +1914,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
         const uint32_t task = uni(sh.h.task);
         if (task == 0xFFFFFFFFu) break;
         if (tid == PT) {
-            ah.jt = claim(P, sh, ah.jt);
+            ah.jt = claim(params(), sh, ah.jt);
             ah.done = false;
         }
-        decode_task<NT>(P, dyn_smem, scratch, ah);
+        decode_task<NT>(params(), dyn_smem, scratch, ah);
         if (tid == PT && !ah.done) {
-            parse_ahead(P, sh, ah.jt);
+            parse_ahead(params(), sh, ah.jt);
             ah.done = true;
         }
         if (tid == 0 && P.status) P.status[task] = uni(sh.h.status);
     }
-    if (P.lists) wave_tasks<NT>(P, dyn_smem, scratch);
+    if (P.lists) wave_tasks<NT>(params(), dyn_smem, scratch);
 }
 
 // ------------------------------------------------------------ small kernels
