@@ -446,8 +446,8 @@ __device__ __forceinline__ void rans_stream(const Params& P, Shared& sh, const u
             asm volatile("" : "+v"(wv));
             x = need ? ((xd << 16) | wv) : act ? xd : x;
             pos += (uint32_t)__popcll(m);
-            const uint32_t s = e & 15u, hi = dpp<0xB1>(0u, s);
-            if (!(lane & 1u)) buf[32u * n + (lane >> 1)] = (uint8_t)(s | (hi << 4));
+            const uint32_t s = e & 15u;
+            buf[32u * n + (lane >> 1)] = (uint8_t)(dpp<0xA0>(0u, s) | (dpp<0xF5>(0u, s) << 4));
             if (++n == 8u) {
                 r0 += W;
                 flush();
@@ -502,7 +502,7 @@ __device__ __forceinline__ uint32_t rans_stage(const Params& P, const TaskHdr& h
 // order, that group g's symbols below index `mark` are out as soon as they are
 // (its next round would start at or past `mark`), and ~0 when the group is done.
 // A round is a serial chain (table, multiply, ballot, word, next state), so what
-// counts is its length: a full round of 64 lanes has no lane checks, and a
+// counts is its length: a round of all lanes has no lane checks, and a
 // group that consumes more words than it has is found out at its end (the word
 // index is held inside the staged words plus one round).
 template <int NT, typename SH>
@@ -517,31 +517,32 @@ __device__ __forceinline__ void rans_rounds(const Params& P, SH& sh, const uint3
         const uint32_t gcount = uni(h.gw[g]), gbase = uni(h.gstart[g]);
         uint32_t x = g == wave ? x0 : lane < lanes ? states[64 * g + lane] : 0u;
         uint32_t gpos = 0, pend = 0, r0 = 64 * g;
-        bool marked = mark == 0;
-        auto publish = [&] {
-            if (!marked && r0 + W >= mark) {
-                marked = true;
-                if (lane == 0) __hip_atomic_store(&sh.prog[g], mark, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        };
         __builtin_amdgcn_s_waitcnt(0);
-        if (W >= 64) {
-            for (; r0 + 64u <= nsym; r0 += W) {
-                const uint32_t e = tab[x & (kRansM - 1)];
-                const uint32_t xd = ((e >> 4) & 0x1FFFu) * (x >> kRansBits) + (e >> 17);
-                const bool need = xd < kRansL;
-                const uint64_t m = __ballot(need);
-                uint32_t wv = wl[gbase + min(gpos, gcount) + mbcnt(m)];
-                asm volatile("" : "+v"(wv));  // (read by every lane: a branch around the read costs more)
-                x = need ? ((xd << 16) | wv) : xd;
-                gpos += (uint32_t)__popcll(m);
-                // two consecutive symbols per byte
-                const uint32_t s = e & 15u, hi = dpp<0xB1>(0u, s);  // quad_perm [1,0,3,2]: the pair partner
-                if (!(lane & 1u)) nl[(r0 >> 1) + (lane >> 1)] = (uint8_t)(s | (hi << 4));
-                publish();
+        // full rounds, first those below `mark`
+        if (W >= 2u && lane < lanes) {
+#pragma nounroll
+            for (uint32_t part = mark ? 0u : 1u; part < 2u; ++part) {
+                const uint32_t last = nsym >= lanes ? nsym - lanes + 1u : 0u, end = uni(part ? last : min(mark, last));
+                // (uni: the compiler takes the position for a lane's own otherwise)
+                for (r0 = uni(r0); r0 < end; r0 += W) {
+                    const uint32_t e = tab[x & (kRansM - 1)];
+                    const uint32_t xd = ((e >> 4) & 0x1FFFu) * (x >> kRansBits) + (e >> 17);
+                    const bool need = xd < kRansL;
+                    const uint64_t m = __ballot(need);
+                    uint32_t wv = wl[gbase + min(gpos, gcount) + mbcnt(m)];
+                    asm volatile("" : "+v"(wv));  // (read by every lane: a branch around the read costs more)
+                    x = need ? ((xd << 16) | wv) : xd;
+                    gpos += (uint32_t)__popcll(m);
+                    // two consecutive symbols per byte
+                    const uint32_t s = e & 15u;  // quad_perm [0,0,2,2], [1,1,3,3]: both lanes write the pair's byte
+                    nl[(r0 >> 1) + (lane >> 1)] = (uint8_t)(dpp<0xA0>(0u, s) | (dpp<0xF5>(0u, s) << 4));
+                }
+                if (part == 0u && r0 >= mark && lane == 0)
+                    __hip_atomic_store(&sh.prog[g], mark, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
-        for (; r0 < nsym; r0 += W) {
+        gpos = uni(gpos);
+        for (r0 = uni(r0); r0 < nsym; r0 += W) {  // the last round (all rounds of one lane)
             const uint32_t j = r0 + lane;
             const bool act = lane < lanes && j < nsym;
             const uint32_t e = tab[x & (kRansM - 1)];
@@ -563,7 +564,6 @@ __device__ __forceinline__ void rans_rounds(const Params& P, SH& sh, const uint3
                     nl[j >> 1] = (uint8_t)(pend | (s << 4));
                 }
             }
-            publish();
         }
         if (gpos > gcount && lane == 0) atomicOr(&sh.err, 1u);
         if (mark && lane == 0) __hip_atomic_store(&sh.prog[g], 0xFFFFFFFFu, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
