@@ -404,17 +404,23 @@ __device__ __forceinline__ void rans_stream(const Params& P, Shared& sh, const u
     const uint32_t* states = (const uint32_t*)(P.vol + uni64(h.states_off));
     uint16_t* const ring = (uint16_t*)(lds + wave * kStreamBytes);
     uint8_t* const buf = (uint8_t*)(ring + kRing);
-    // reads stay inside the container (past the words they only feed what the
-    // word count at the end refuses)
-    const uint64_t pay = min((uint64_t)uni64(h.pay_off), (P.vol_bytes - 8u) & ~3ull), room = P.vol_bytes - pay - 8u;
+    // reads stay inside the container; what lies past it only feeds what the word
+    // count at the end refuses
+    const uint64_t pay = uni64(h.pay_off), avail = P.vol_bytes - pay;
     for (uint32_t g = wave; g < G; g += NT / 64) {
         const uint32_t gcount = uni(h.gw[g]), start = uni(h.gstart[g]), odd = start & 1u;
         const uint8_t* const src = P.vol + pay;
         // words 256 k .. 256 k + 255 of the group's stream (from its even start), 4 per lane
         auto fetch = [&](uint32_t k) -> uint2 {
             const uint64_t o = 2ull * (start & ~1u) + 512ull * k + 8u * lane;
-            const u32x2_a4 v = *(const u32x2_a4*)(src + (o < room ? o : room & ~3ull));
-            return make_uint2(v[0], v[1]);
+            if (o + 8u <= avail) {
+                const u32x2_a4 v = *(const u32x2_a4*)(src + o);
+                return make_uint2(v[0], v[1]);
+            }
+            uint32_t q[4];  // the container's last words
+#pragma unroll
+            for (uint32_t c = 0; c < 4; ++c) q[c] = o + 2u * c + 2u <= avail ? *(const uint16_t*)(src + o + 2u * c) : 0u;
+            return make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
         };
         uint32_t x = states[64 * g + lane];
         uint2 a = fetch(0), b = fetch(1), ahead = fetch(2);
