@@ -7,7 +7,12 @@ import numpy as np
 import pytest
 
 import oracle
-import paper_2609_36898_amd as P
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2609_36898_amd  # (not at collection: GPU tests import torch first)
+    return paper_2609_36898_amd
 
 
 def _bricks(rng, lb, l2):
@@ -27,7 +32,7 @@ def _bricks(rng, lb, l2):
 
 @pytest.mark.parametrize("lb", [4, 8])
 @pytest.mark.parametrize("op_mask,nmode", [(63, 0), (63, 1), (0, 0), (1, 0), (14, 1), (30, 0), (48, 0), (62, 1), (59, 0), (55, 1)])
-def test_blocks_match_the_oracle(lb, op_mask, nmode):
+def test_blocks_match_the_oracle(P, lb, op_mask, nmode):
     rng = np.random.default_rng(op_mask + 2 * nmode)
     l2 = [1, 2, 3, 4, 5, 5, 5, 4, 3, 2]
     vox = _bricks(rng, lb, l2)
@@ -39,7 +44,7 @@ def test_blocks_match_the_oracle(lb, op_mask, nmode):
 
 @pytest.mark.parametrize("lane_syms", [1, 16, 63, 300, 5000, 1 << 20])
 @pytest.mark.parametrize("n_threads", [1, 3, 64])
-def test_lane_counts_match_the_oracle(lane_syms, n_threads):
+def test_lane_counts_match_the_oracle(P, lane_syms, n_threads):
     rng = np.random.default_rng(lane_syms)
     l2 = [5, 6, 2, 1, 4, 5]
     vox = _bricks(rng, 4, l2)
