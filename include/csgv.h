@@ -184,7 +184,7 @@ csgv_status csgv_decode_bricks(hipStream_t stream, const csgv_volume_info* vol, 
  * until the process ends (its device address is looked up on the first call
  * on each device).  Limits: at most CSGV_NOALLOC_MAX_TASKS tasks per call
  * (else CSGV_EINVAL), and the persistent grid holds only as many work-groups
- * as the array's scratch share fits (about 250 for 32^3 bricks, 75 for 64^3),
+ * as the array's scratch share fits (about 520 for 32^3 bricks, 85 for 64^3),
  * so large batches run slower than with csgv_decode_bricks.  Every call on a
  * GPU uses that GPU's one array: calls that overlap on one GPU (other streams,
  * other threads) race and must be serialised by the caller.  The array keeps

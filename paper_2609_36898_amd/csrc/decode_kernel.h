@@ -73,7 +73,7 @@ struct Params {
     uint32_t label_bytes;
     uint32_t freq_ok;          // the volume's frequency table sums to 4096
     uint32_t max_log2b;        // records with a larger brick side are rejected (scratch bound)
-    const uint32_t* rans_tab;  // decoding table built by rans_table_kernel (4096 entries)
+    const uint32_t* rans_tab;  // decoding table built by prepare_kernel (4096 entries)
     const uint32_t* ids;
     const uint8_t* lods;
     const uint64_t* out_offs;    // caller's element offsets, or null

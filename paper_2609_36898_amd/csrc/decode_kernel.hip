@@ -8,49 +8,48 @@
 // with stop bits for all-constant children; Methods > "GPU rendering
 // pipeline" for the decode stage; Methods > "Memory management" for LODs).
 //
-// Storage of the levels of a task (node order within a level is Morton):
-//   levels 0..4   full grids (4681 nodes).  When a level starts, the children
-//                 of every parent that does not expand take the parent's
-//                 value, and the children of expanding parents are marked
-//                 "not yet decoded";
-//   level 5       explicit nodes only, indexed by operation rank k (the k-th
-//                 operation of a level is the k-th explicit node in Morton
-//                 order); an implied node is its level-4 parent's value, an
-//                 explicit one is found through the rank of its parent:
-//                 prefix popcount of the level-4 expansion bitmap;
-//   level 6       (64^3 bricks at full resolution) explicit nodes are kept at
-//                 their voxel position in the task's own output range, which
-//                 the output pass then overwrites in place with labels.
-// A slot holds either a final palette index (top bit set) or a reference to
-// a same-level slot whose value it copies (a neighbour operation whose target
-// is decoded in the same pass).  Fast path: 16-bit slots, levels 0..5 in LDS;
-// a 32^3 cube at full resolution with more level-5 nodes than the LDS share
-// holds keeps its 16-bit level-5 slots in the work-group's scratch instead.
-// Big path (palettes above 2^15 entries, or a 64^3 cube whose level 5 does not
-// fit): 32-bit slots in a per-work-group global scratch area.
+// The kernel is bound by instruction issue and by the serial chain of a task's
+// phases, not by memory (a 32^3 brick is about 3 KB read and 128 KB written): 4096
+// Voronoi bricks run at 56 % VALU busy, and the output is written at about 2.6 TB/s.
+// A 32^3 cube at full resolution takes 100k cycles with four work-groups of 256
+// threads on a CU: 9k staging, 25k rANS rounds and levels 0..3, 18k level 4, 34k
+// level 5, 10k output.  That is why the levels are decoded by expanding parents,
+// with no work for nodes that are implied.
 //
-// A level's symbol segment is consumed in passes of one symbol per thread.
-// Per wavefront, ballots classify each symbol as an operation or a 4-bit
-// delta entry for both possible entry states of the 2-state automaton
-// (inside a delta chain or not), count operations and PALETTE_ADV operations
-// (Methods > "Compressed segmentation volumes" for the delta chains); one
-// barrier later every wave folds the earlier waves' summaries and knows its
-// entry state, its first operation rank and its palette (ADV) rank, and every
-// lane then ranks itself with mbcnt.  Neighbour targets decoded in an earlier
-// pass are already final; references within a pass are resolved right after
-// it by chasing, which terminates because every target precedes its source
-// in Morton order.
+// Storage of the levels of a task (node order within a level is Morton; the k-th
+// operation of a level is its k-th explicit node):
+//   levels 0..4   full grids in LDS (4681 nodes), and bitmaps of the nodes that
+//                 expand, with a popcount prefix;
+//   level 5       explicit nodes only, by operation rank: 8 slots, a row, for
+//                 every expanding parent, found through the rank of the parent
+//                 in the level-4 bitmap.  In LDS when the rows fit there (32^3
+//                 cubes), else palette indices in the work-group's scratch;
+//   level 6       (64^3 bricks at full resolution) nowhere: labels go straight to
+//                 the task's output, from which later nodes copy.
+// A level is decoded in two steps.  ops_pass ranks the level's symbols: a thread
+// takes up to four words of eight 4-bit symbols, summarises them for both entry
+// states of the automaton (inside a chain of delta entries or not), and one scan
+// and one barrier give it its state, its first operation rank and its palette
+// (ADV) rank; it writes each operation's slot, a palette index or a copy's code.
+// Then a thread per expanding parent turns the 8 slots of its children into
+// values or references to slots of the same level (resolve8), and the references
+// are followed (chase_open), which ends because every target precedes its source
+// in Morton order.  Levels 1 and 2 take a lane per symbol and per node instead.
+//   Levels whose rows do not fit in LDS, and level 6, do the same in chunks of a
+// 32-bit buffer in LDS, parent by parent as their operations are complete
+// (chunk_level).
 //
-// rANS-coded records are first decoded into 4-bit symbols (in LDS for a cube
-// of side <= 16 when they fit, else in the work-group's scratch): every 64-lane
-// group of the interleaved coder is one wavefront, and the lanes that
-// renormalise in a round find their word offsets with a ballot and a masked
-// bit count.  The decoding table stays in LDS across tasks until a level-5
-// decode reuses its space.
+// rANS-coded records are first decoded into 4-bit symbols: every 64-lane group of
+// the interleaved coder is one wavefront, and the lanes that renormalise in a
+// round find their word offsets with a ballot and a masked bit count.  Words,
+// decoding table and symbols are all in LDS where they fit, as those of nearly
+// every 32^3 record do; longer streams go through a ring (rans_stream).
 //
-// Levels 0..2 (at most 73 nodes) are decoded by wavefront 0 alone, with wave
-// barriers; meanwhile lane 0 of the last wavefront parses the work-group's
-// next task (claimed when the current one started) into a second header.
+// Levels 0..3 (at most 585 nodes) are decoded by one wavefront, while the others
+// still decode symbols if there is one to spare; meanwhile lane 0 of the last
+// wavefront parses the work-group's next task (claimed when the current one
+// started) into a second header.  Cubes of side <= 8 are decoded by single
+// wavefronts throughout (wave_tasks).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -94,7 +93,7 @@ struct Shared {
     uint32_t n_jobs;                // tasks of the launch for work-groups, and of each of its lists
     uint32_t small[2];              // claims on the lists for single wavefronts, this one and the next
     uint32_t job[kClasses];
-    alignas(16) uint16_t refs[64];  // open slots of levels 0..3
+    alignas(16) uint16_t refs[64];  // open slots of level 3
     alignas(16) uint4 pub[2][kMaxWaves];  // per pass and wave: run summary (exit states, counts)
     alignas(16) uint2 EP[kEWords];        // expansion bitmaps of levels 0..4: bits, prefix
     alignas(16) uint16_t G[kFullSlots];   // full grids of levels 0..4
@@ -285,8 +284,8 @@ __device__ __forceinline__ void parse_task(const Params& P, uint32_t task, TaskH
 
 // The work-group's next task: claimed by lane 0 of its last wavefront (jt, in
 // that lane's register) when a task starts, and parsed into sh.hn by the same
-// lane while that wavefront has nothing else to do (levels 0..2 are decoded by
-// wavefront 0 alone), else at the end of the task.
+// lane while that wavefront has nothing else to do (levels 0..3 are decoded by
+// one wavefront alone), else at the end of the task.
 struct Ahead {
     uint32_t jt;
     bool done;
@@ -1029,8 +1028,8 @@ __device__ __forceinline__ void list_parents(const uint2* ep, uint32_t bytes, ui
 }
 
 // ------------------------------------------------------------- full levels
-// Level i <= 4 into its full grid: the calling wavefront alone (NT = 64, levels
-// 1..3: a lane per parent) or the work-group (level 4: a thread per expanding
+// Level 3 or 4 into its full grid: the calling wavefront alone (NT = 64, level 3:
+// a lane per parent) or the work-group (level 4: a thread per expanding
 // parent, from a list in `work`).  The operations are written compactly into the
 // grid's own space, read back by the parents they belong to, and then every
 // parent writes its 8 children and their expansion bits: an expanding one what
@@ -1108,8 +1107,7 @@ __device__ __forceinline__ bool full_level(SH& sh, const uint32_t* sym, uint32_t
             open[p] = open_of(row);
             ((uint4*)grid)[q] = row;
             uint2* const eo = sh.EP + ebase(i) + (q >> 2);
-            if (i == 1) eo->x = bits;
-            else ((uint8_t*)&eo->x)[q & 3u] = (uint8_t)bits;
+            ((uint8_t*)&eo->x)[q & 3u] = (uint8_t)bits;
         }
     }
     // the other parents
@@ -1118,8 +1116,7 @@ __device__ __forceinline__ bool full_level(SH& sh, const uint32_t* sym, uint32_t
             const uint32_t v2 = par[q] * 0x10001u;
             ((uint4*)grid)[q] = make_uint4(v2, v2, v2, v2);
             uint2* const eo = sh.EP + ebase(i) + (q >> 2);
-            if (i == 1) eo->x = 0;
-            else ((uint8_t*)&eo->x)[q & 3u] = 0;
+            ((uint8_t*)&eo->x)[q & 3u] = 0;
         }
     }
     if (bad) sh.err = 1u;
@@ -1901,12 +1898,13 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
 }
 
 // ------------------------------------------------------- tasks of one wavefront
-// Cubes of side <= 8 have at most 585 nodes, which one wavefront decodes alone
-// (levels 0..3 never take more): in a work-group of four wavefronts three would
+// Cubes of side <= 8 have at most 585 nodes, which one wavefront decodes alone, as
+// it does levels 0..3 of any cube: in a work-group of four wavefronts three would
 // wait for most of such a task.  When the lists of larger tasks are used up, up
 // to four wavefronts of a work-group each take tasks of their own, with no
 // barrier among them; the rANS table in LDS is shared.  Kernel time of 1400
-// neurite cubes of side 8: 0.066 -> 0.034 ms; 4096 of side 2..16: 0.107 -> 0.080.
+// neurite cubes of side 8: 0.066 -> 0.034 ms (0.025 with lane_level); 4096 of side
+// 2..16: 0.107 -> 0.080 (0.063).
 struct WaveShared {
     TaskHdr q[4];  // the tasks of a claim, parsed by one lane each
     TaskHdr h;     // the task being decoded
