@@ -128,7 +128,7 @@ def build_workload(name: str) -> Workload:
         n = 4096
         wl = Workload(name, c, np.arange(n), np.zeros(n), 4, P.bricks_of_volume(vol, 5),
                       {"workload": "voronoi512_voids_u32_b32_lod0", "volume": [512] * 3, "bricks": n,
-                       "seeds": 20000, "void_fraction_min": 0.10, "form": "persistent+graph"})
+                       "seeds": 20000, "void_fraction_min": 0.10, "form": "persistent"})
     elif name == "neurite1024":
         vol = W.neurite1024()
         c = P.encode_volume(vol, 5)
@@ -136,7 +136,7 @@ def build_workload(name: str) -> Workload:
         n = 32768
         wl = Workload(name, c, np.arange(n), W.neurite1024_lods(n), 4, None,
                       {"workload": "neurite1024_u32_b32_lod0-3", "volume": [1024] * 3, "bricks": n,
-                       "tubes": 100000, "lod": "uniform 0..3 per brick", "form": "autotuned persistent+graph"})
+                       "tubes": 100000, "lod": "uniform 0..3 per brick", "form": "autotuned persistent"})
     elif name == "uneven1024":
         flat, l2, origins, kinds = W.uneven1024()
         c = P.csgv_encode_bricks(flat, l2, 8, dims=(1024, 1024, 1024), origins=origins)
@@ -146,7 +146,7 @@ def build_workload(name: str) -> Workload:
                        "bricks_64": int((l2 == 6).sum()), "bricks_32": int((l2 == 5).sum()),
                        "kinds": {"constant": int((kinds == 0).sum()), "voronoi": int((kinds == 1).sum()),
                                  "noise": int((kinds == 2).sum())},
-                       "form": "persistent+graph vs plain"}, plain=True)
+                       "form": "persistent vs plain"}, plain=True)
     elif name == "neurite2048":
         # generated and encoded slab by slab (32 planes = one layer of bricks)
         n = SERVE_SIDE
@@ -262,7 +262,7 @@ def measure(wl: Workload, args, dev):
         torch.cuda.synchronize()
         plain_ms = p0.elapsed_time(p1) / args.plain_steps
         res["plain"] = {"value": round(voxels / (plain_ms * 1e-3) / 1e9, 3), "unit": "GVoxel/s",
-                        "ms_per_step": round(plain_ms, 3), "launches_per_step": n,
+                        "ms_per_step": round(plain_ms, 3), "launches_per_step": 1,
                         "bit_exact": bool(torch.equal(plain_out, out))}
         del plain_out
 
@@ -569,7 +569,6 @@ def device_staged(P, dv, cache, cache_elems, container, ids, lods, starts, n_war
     stream = torch.cuda.current_stream(dev)
     dc = P.csgv.csgv_dcache(dv.info, dv.tensor, cache_elems, stream=stream)
     plan = P.csgv_plan(dv.info, max(int(np.diff(pb).max()), 1))
-    plan.set_graph(False)  # every chunk has its own arrays and count: a captured graph would be rebuilt each time
     ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
     t0 = time.time()
@@ -847,7 +846,7 @@ def main():
     ap.add_argument("--workload", nargs="*", default=None,
                     help="workloads to run (first = headline); default: %s %s" % (HEADLINE, " ".join(SECONDARY)))
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle baseline")
-    ap.add_argument("--no-plain", action="store_true", help="skip the plain one-launch-per-brick legs")
+    ap.add_argument("--no-plain", action="store_true", help="skip the plain legs (one launch, tasks in the order given)")
     ap.add_argument("--no-tune", action="store_true", help="default launch shape instead of the autotuner")
     ap.add_argument("--shape", default=None, metavar="WG,SLOTS,WGS_PER_CU",
                     help="fixed launch shape of the batched legs instead of the autotuner (profiling runs)")
