@@ -198,10 +198,14 @@ hipError_t enqueue(Params P, const Bufs& b, const csgv_volume_info* vol, int wg,
     queue = queue && P.n_tasks > grid;
     sort = sort && queue;
     hipError_t e;
+    // a call without a plan builds its rANS table and sets its control words: in
+    // the binning kernel if there is one, of one block, else in a kernel before it
+    const bool bin = queue || !P.out_offs, solo = bin && (P.n_tasks <= kBinTasks || (!sort && P.out_offs));
+    bool table = false;
+    RansFreq f{};
     if (!b.prepared) {
-        bool ok;
-        const RansFreq f = pack_freq(vol, &ok);
-        if ((e = launch_prepare(b.ctl, ok ? b.rans_tab : nullptr, &f, s)) != hipSuccess) return e;
+        f = pack_freq(vol, &table);
+        if (!solo && (e = launch_prepare(b.ctl, table ? b.rans_tab : nullptr, &f, s)) != hipSuccess) return e;
     }
     P.ctl = b.ctl;
     P.list_cap = b.list_cap;
@@ -209,10 +213,9 @@ hipError_t enqueue(Params P, const Bufs& b, const csgv_volume_info* vol, int wg,
         P.dense_offs = b.dense;
         P.dense_base = b.base;
     }
-    if (queue || !P.out_offs) {
-        if ((e = launch_bin(P, sort ? b.lists : nullptr, P.out_offs ? nullptr : b.dense, b.base, b.totals, s)) != hipSuccess)
-            return e;
-    }
+    if (bin && (e = launch_bin(P, sort ? b.lists : nullptr, P.out_offs ? nullptr : b.dense, b.base, b.totals,
+                               solo && table ? b.rans_tab : nullptr, &f, s)) != hipSuccess)
+        return e;
     if (sort) P.lists = b.lists;
     if (!queue) P.ctl = nullptr;
     if (ev0 && (e = hipEventRecord(ev0, s)) != hipSuccess) return e;

@@ -105,6 +105,7 @@ int max_resident_per_cu(int wg_size, uint32_t cap16);  // occupancy of the decod
 hipError_t set_kernel_attrs();
 hipError_t launch_decode(const Params& P, int wg_size, uint32_t grid, hipStream_t s);
 hipError_t launch_prepare(Control* ctl, uint32_t* tab, const RansFreq* f, hipStream_t s);
-hipError_t launch_bin(const Params& P, uint32_t* lists, uint64_t* dense, uint64_t* base, uint64_t* totals, hipStream_t s);
+hipError_t launch_bin(const Params& P, uint32_t* lists, uint64_t* dense, uint64_t* base, uint64_t* totals, uint32_t* tab,
+                      const RansFreq* f, hipStream_t s);
 
 }  // namespace csgv

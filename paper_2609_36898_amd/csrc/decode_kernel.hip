@@ -2104,10 +2104,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) de
 // ------------------------------------------------------------ small kernels
 // The control words of a one-shot call and the volume's rANS decoding table:
 // slot -> symbol | freq << 4 | (slot - cum) << 17
-__global__ void prepare_kernel(Control* ctl, uint32_t* tab, RansFreq f) {
-    const uint32_t slot = blockIdx.x * blockDim.x + threadIdx.x;
-    if (ctl && slot < sizeof(Control) / 4) ((uint32_t*)ctl)[slot] = 0;
-    if (!tab || slot >= kRansM) return;
+__device__ __forceinline__ void table_slot(uint32_t* tab, const RansFreq& f, uint32_t slot) {
     uint32_t cum = 0, s = 0, fs = 0;
     for (uint32_t k = 0; k < 16; ++k) {
         const uint32_t fk = (f.w[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
@@ -2119,6 +2116,12 @@ __global__ void prepare_kernel(Control* ctl, uint32_t* tab, RansFreq f) {
         cum += fk;
     }
     tab[slot] = s | (fs << 4) | ((slot - cum) << 17);
+}
+
+__global__ void prepare_kernel(Control* ctl, uint32_t* tab, RansFreq f) {
+    const uint32_t slot = blockIdx.x * blockDim.x + threadIdx.x;
+    if (ctl && slot < sizeof(Control) / 4) ((uint32_t*)ctl)[slot] = 0;
+    if (tab && slot < kRansM) table_slot(tab, f, slot);
 }
 
 // brick side exponent of a task's record (0 when the task or record is unusable)
@@ -2169,13 +2172,20 @@ __device__ __forceinline__ uint32_t cost_class(const Params& P, uint32_t id, uin
 // within the block; the block that finishes last turns the blocks' totals into
 // the blocks' own offsets.  A task that names no brick is refused here and goes
 // to no list.  (One launch; a histogram, a scan and a scatter took four, 4.7 us
-// each.)
+// each.)  The blocks from `bins` on build the rANS table, for a one-shot call whose
+// tasks are one block's: that block needs no control words set before it, so the
+// call has no other kernel before the decode (64 bricks, packed: 47.6 -> 43.1 us).
 __global__ void __launch_bounds__(kBinTasks) bin_kernel(Params P, uint32_t* lists, uint64_t* dense, uint64_t* base,
-                                                        uint64_t* totals) {
+                                                        uint64_t* totals, uint32_t bins, uint32_t* tab, RansFreq f) {
     __shared__ uint32_t cnt[4][8];
     __shared__ uint32_t first[8];
     __shared__ uint64_t wsum[4];
     __shared__ uint32_t last;
+    if (blockIdx.x >= bins) {
+        const uint32_t slot = (blockIdx.x - bins) * kBinTasks + threadIdx.x;
+        if (slot < kRansM) table_slot(tab, f, slot);
+        return;
+    }
     if (!lists && !dense) {  // nothing to do but the control words
         if (threadIdx.x < sizeof(Control) / 4) ((uint32_t*)P.ctl)[threadIdx.x] = 0;
         return;
@@ -2199,7 +2209,7 @@ __global__ void __launch_bounds__(kBinTasks) bin_kernel(Params P, uint32_t* list
         __syncthreads();
         if (tid < kClasses) {
             const uint32_t tot = cnt[0][tid] + cnt[1][tid] + cnt[2][tid] + cnt[3][tid];
-            first[tid] = tot ? atomicAdd(&P.ctl->count[tid], tot) : 0u;
+            first[tid] = bins == 1u ? 0u : tot ? atomicAdd(&P.ctl->count[tid], tot) : 0u;
         }
         __syncthreads();
         if (c < kClasses) {
@@ -2236,23 +2246,25 @@ __global__ void __launch_bounds__(kBinTasks) bin_kernel(Params P, uint32_t* list
     __syncthreads();  // the block's counts are out
     if (tid == 0) {
         if (dense) __hip_atomic_store(&totals[blockIdx.x], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __threadfence();
-        last = atomicAdd(&P.ctl->ticket, 1u) == gridDim.x - 1u;
+        if (bins > 1u) __threadfence();
+        last = bins == 1u || atomicAdd(&P.ctl->ticket, 1u) == bins - 1u;
     }
     __syncthreads();
     if (!last) return;
     __threadfence();
     if (tid < kClasses) {
-        P.ctl->job[tid] = __hip_atomic_load(&P.ctl->count[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        P.ctl->job[tid] = bins > 1u ? __hip_atomic_load(&P.ctl->count[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                          : lists   ? cnt[0][tid] + cnt[1][tid] + cnt[2][tid] + cnt[3][tid]
+                                    : 0u;
         P.ctl->count[tid] = 0;
     }
     if (tid == 0) P.ctl->ticket = P.ctl->queue = P.ctl->small = 0;
     uint64_t carry = 0;
-    for (uint32_t b = 0; dense && b < gridDim.x; b += kBinTasks) {
-        const uint64_t v = b + tid < gridDim.x
+    for (uint32_t b = 0; dense && b < bins; b += kBinTasks) {
+        const uint64_t v = b + tid < bins
                                ? __hip_atomic_load(&totals[b + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
         const uint64_t o = block_scan(v, &total);
-        if (b + tid < gridDim.x) base[b + tid] = carry + o;
+        if (b + tid < bins) base[b + tid] = carry + o;
         carry += total;
     }
 }
@@ -2314,10 +2326,11 @@ hipError_t launch_prepare(Control* ctl, uint32_t* tab, const RansFreq* f, hipStr
     return hipGetLastError();
 }
 
-hipError_t launch_bin(const Params& P, uint32_t* lists, uint64_t* dense, uint64_t* base, uint64_t* totals, hipStream_t s) {
-    const uint32_t blocks = lists || dense ? (P.n_tasks + kBinTasks - 1) / kBinTasks : 1u;
-    hipLaunchKernelGGL(bin_kernel, dim3(blocks), dim3(kBinTasks), 0, s, P, lists, dense, base,
-                       totals);
+hipError_t launch_bin(const Params& P, uint32_t* lists, uint64_t* dense, uint64_t* base, uint64_t* totals, uint32_t* tab,
+                      const RansFreq* f, hipStream_t s) {
+    const uint32_t bins = lists || dense ? (P.n_tasks + kBinTasks - 1) / kBinTasks : 1u;
+    hipLaunchKernelGGL(bin_kernel, dim3(bins + (tab ? kRansM / kBinTasks : 0u)), dim3(kBinTasks), 0, s, P, lists, dense, base,
+                       totals, bins, tab, f ? *f : RansFreq{});
     return hipGetLastError();
 }
 

@@ -194,3 +194,27 @@ def test_long_streams_at_the_end_of_the_container(P, lane_syms, lb):
         c = P.csgv_encode_bricks(b.reshape(-1), [5], lb, origins=np.zeros((1, 3), np.uint32), coder_policy=2, lane_syms=lane_syms)
         want, st = _compare(P, c, [0], [0], modes=(0, 2))
         assert st[0] == 0
+
+
+@pytest.mark.parametrize("sort", [0, 1])
+@pytest.mark.parametrize("dense", [True, False])
+def test_queue_of_one_block_without_a_plan(P, sort, dense):
+    # more tasks than the fixed scratch has work-groups for 64^3 bricks, few enough for one block of
+    # the binning kernel, which then also sets the control words and the table; and larger calls between
+    import torch
+    b = np.concatenate([synth.voronoi_u32(64, 20 + 9 * k, seed=k).reshape(-1) for k in range(4)])
+    c = P.csgv_encode_bricks(b, [6] * 4, 4, origins=np.zeros((4, 3), np.uint32))
+    dv = P.DeviceVolume(c)
+    rng = np.random.default_rng(5)
+    for n in (130, 256, 600, 91, 256, 3):
+        ids, lods = rng.integers(0, 4, n).astype(np.uint32), rng.integers(1, 7, n).astype(np.uint8)
+        lods[: n // 50] = 0
+        d_ids, d_lods, d_offs, offs, total = dv.tasks(ids, lods)
+        out = torch.zeros(total, dtype=torch.int32, device="cuda")
+        st = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+        P.csgv.csgv_decode_bricks_noalloc(None, dv.info, dv.tensor, d_ids, d_lods, None if dense else d_offs, n, out, total, st,
+                                          mode=P.MODE_PERSISTENT, sort_tasks=sort)
+        torch.cuda.synchronize()
+        want, wst = oracle.decode_tasks(c, ids, lods, offs, total, 4, nthreads=8)
+        assert np.array_equal(st.cpu().numpy().view(np.uint32), wst), n
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want), n
