@@ -30,6 +30,11 @@ __host__ __device__ constexpr uint32_t slot_bytes(uint32_t cap16) {
 }
 static_assert(list_bytes(kMinCap16) >= kUBytesMin, "palette area");
 
+// Room of n 4-bit symbols, in whole words.  The first symbol is looked at whatever
+// n is (a damaged record may have none), so there is a word of it always.
+__host__ __device__ constexpr uint32_t symbol_bytes(uint32_t n) { return 4u * (n ? (n + 7u) / 8u : 1u); }
+static_assert(symbol_bytes(0) == 4u && symbol_bytes(8) == 4u && symbol_bytes(9) == 8u, "the first symbol has a place");
+
 // cubes of side <= 8 with at most this many symbols are decoded by one wavefront
 // each, up to four in a work-group
 constexpr uint32_t kWaveSyms = 4096;

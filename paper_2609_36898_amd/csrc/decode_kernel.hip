@@ -1823,7 +1823,7 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     const uint32_t o_tab = (uint32_t)sizeof(Shared) + u_bytes, o_end = o_tab + slot_bytes(P.cap16);
     const uint32_t G = rans ? ((1u << uni(h.log2W)) + 63u) / 64u : 0u;
     const uint64_t words = rans ? (uint64_t)uni(h.gstart[G - 1]) + uni(h.gw[G - 1]) : 0u;
-    const uint32_t sym_bytes = 4u * n_words;
+    const uint32_t sym_bytes = symbol_bytes(nsym);
     // (a round may read up to 63 words past a group's end)
     const bool fits = rans && o_words + 2u * words + 16u + 128u <= o_tab && o_tab + 4u * kRansM + sym_bytes + 16u <= o_end;
     const uint32_t words_bytes = fits ? (2u * (uint32_t)words + 15u) & ~15u : 0u, o_sym = fits ? (o_end - sym_bytes) & ~15u : 0u;
