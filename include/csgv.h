@@ -447,7 +447,8 @@ void csgv_dcache_destroy(csgv_dcache* cache);
  *   neighbor_mode  0: neighbour copies at any position; 1: only across sibling groups.
  *   coder_policy   0: per brick the smaller of plain 4-bit and rANS; 1: plain; 2: rANS.
  *   lane_syms      target symbols per rANS lane (sets the lane count W <= 256).
- *   n_threads      worker threads (0 = all hardware threads).
+ *   n_threads      most threads to use, the calling one among them (0 = all hardware
+ *                  threads); fewer are started when the bricks hold less work.
  * On success *h_out is a malloc'd container of *out_bytes bytes; free it with
  * csgv_free_host.
  */

@@ -440,13 +440,42 @@ void build_record(BrickCode& bc, uint32_t lb, uint32_t policy, uint32_t lane_sym
     }
 }
 
-// fn(item, thread) for every item; the calling thread takes part, and no thread is
-// started that would not find a few items to do (a thread costs as much as
-// encoding one or two 32^3 bricks).
-constexpr uint32_t kItemsPerThread = 4;
+// Threads worth starting for n items of `ns` nanoseconds of work in all, the calling
+// one included: one per 200 us, twice what starting and joining it costs (40 us of
+// the starting thread and a wake-up; 7 threads and no work: 0.35 ms).
+constexpr double kThreadNs = 2e5;
+int threads_for(int threads, uint32_t n, double ns) {
+    return (int)std::max(1.0, std::min({(double)threads, (double)n, ns / kThreadNs}));
+}
+
+// About the nanoseconds that a brick's operations take: 4 a voxel, and 30 more for one that
+// can copy from no neighbour, judged by how often voxels of four of the brick's rows differ
+// from the one before them, for two axes (smooth labels 3 to 5 ns a voxel, 16 labels at
+// random 29, noise 32 to 42 and at side 64, where its label table leaves the caches, 105).
+// The number of bricks says little: 4 of 64^3 with 16 random labels take 37 ms with one
+// thread and 16 with four, 4 smooth ones of 16^3 take 0.12 with one and 1.4 with eight.
+template <typename LT>
+double brick_ns(const uint8_t* vox, uint32_t L) {
+    const uint32_t b = 1u << L;
+    uint32_t seen = 0, differ = 0;
+    for (uint32_t r = 0; r < 4; ++r) {
+        const uint32_t y = (2u * r + 1u) * b / 8u, z = (2u * (r ^ 1u) + 1u) * b / 8u;
+        const uint8_t* const row = vox + sizeof(LT) * (((size_t)z * b + y) * b);
+        LT last, v;
+        memcpy(&last, row, sizeof(LT));
+        for (uint32_t x = 1; x < b; ++x, last = v) {
+            memcpy(&v, row + sizeof(LT) * x, sizeof(LT));
+            ++seen;
+            differ += v != last;
+        }
+    }
+    const double f = (double)differ / seen;
+    return (double)(size_t(1) << (3 * L)) * (4.0 + 30.0 * f * f);
+}
+
+// fn(item, thread) for every item on `threads` threads, the calling one among them
 template <class F>
 void parallel_for(uint32_t n, int threads, F&& fn) {
-    threads = (int)std::min<uint64_t>((uint64_t)std::max(threads, 1), (n + kItemsPerThread - 1) / kItemsPerThread);
     std::atomic<uint32_t> next{0};
     const auto work = [&](int t) {
         for (;;) {
@@ -512,10 +541,16 @@ csgv_status csgv_encoder_add(csgv_encoder* e, const void* h_voxels, const uint8_
     }
     const size_t base = e->bc.size();
     e->bc.resize(base + n_bricks);
-    std::vector<Worker> workers(e->threads);
     const uint8_t* vox = (const uint8_t*)h_voxels;
     const uint32_t lb = e->label_bytes;
-    parallel_for(n_bricks, e->threads, [&](uint32_t k, int t) {
+    double ns = 0;
+    for (uint32_t k = 0; k < n_bricks && ns < kThreadNs * e->threads; ++k) {
+        const uint8_t* const v = vox + vox_off[k] * lb;
+        ns += lb == 4 ? brick_ns<uint32_t>(v, h_log2b[k]) : brick_ns<uint64_t>(v, h_log2b[k]);
+    }
+    const int threads = threads_for(e->threads, n_bricks, ns);
+    std::vector<Worker> workers(threads);
+    parallel_for(n_bricks, threads, [&](uint32_t k, int t) {
         const uint8_t* const v = vox + vox_off[k] * lb;
         if (lb == 4) encode_brick<uint32_t>(v, h_log2b[k], e->op_mask, e->neighbor_mode, workers[t], e->bc[base + k]);
         else encode_brick<uint64_t>(v, h_log2b[k], e->op_mask, e->neighbor_mode, workers[t], e->bc[base + k]);
@@ -540,8 +575,12 @@ csgv_status csgv_encoder_finish(csgv_encoder* e, void** h_out, uint64_t* out_byt
     for (int s = 0; s < 16; ++s) cum[s + 1] = cum[s] + freq[s];
     RansStep steps[16];
     rans_steps(freq, cum, steps);
-    std::vector<std::vector<uint16_t>> words(e->threads);
-    parallel_for(n_bricks, e->threads, [&](uint32_t k, int t) {
+    // (2 to 5 ns a symbol with its palette entry)
+    double ns = 0;
+    for (auto& c : bc) ns += 2.0 * (double)(c.sym.size() + c.pal.size());
+    const int threads = threads_for(e->threads, n_bricks, ns);
+    std::vector<std::vector<uint16_t>> words(threads);
+    parallel_for(n_bricks, threads, [&](uint32_t k, int t) {
         build_record(bc[k], label_bytes, coder_policy, lane_syms, steps, words[t]);
         std::vector<uint8_t>().swap(bc[k].sym);
         std::vector<uint64_t>().swap(bc[k].pal);
@@ -582,8 +621,8 @@ csgv_status csgv_encoder_finish(csgv_encoder* e, void** h_out, uint64_t* out_byt
         pos += bc[k].rec.size();
     }
     w64(off_pos + 8ull * n_bricks, pos);
-    // (threads for the copies from 32 MiB on: less is done before they have started)
-    parallel_for(n_bricks, total >> 25 ? e->threads : 1, [&](uint32_t k, int) {
+    // (0.25 ns a byte, most of it the fresh pages')
+    parallel_for(n_bricks, threads_for(e->threads, n_bricks, 0.25 * (double)total), [&](uint32_t k, int) {
         uint64_t at;
         memcpy(&at, buf + off_pos + 8ull * k, 8);
         memcpy(buf + at, bc[k].rec.data(), bc[k].rec.size());
