@@ -371,7 +371,7 @@ void build_record(BrickCode& bc, uint32_t lb, uint32_t policy, uint32_t lane_sym
         }
         G = (W + 63) / 64;
         // every lane group's words, backwards from the end of its share: a symbol emits one at most
-        for (uint32_t g = 0; g < G; ++g) begin[g + 1] = begin[g] + 64u * (nsym / W + 1);
+        for (uint32_t g = 0; g < G; ++g) begin[g + 1] = begin[g] + std::min(W, 64u) * (nsym / W + 1);
         if (words.size() < begin[G]) words.resize(begin[G]);
         for (uint32_t g = 0; g < G; ++g) at[g] = begin[g + 1];
         for (uint32_t l = 0; l < W; ++l) state[l] = kRansL;

@@ -58,3 +58,20 @@ def test_few_hard_bricks_use_the_threads_asked_for(P, side, n, streamed):
 def test_little_work_starts_no_thread(P):
     v = np.broadcast_to((np.arange(16) // 5).astype(np.uint64), (4, 16, 16, 16)).reshape(4, -1)
     assert max(_most_threads(lambda: [_encode(P, v, 4, 8, False) for _ in range(200)]) for _ in range(3)) == 0
+
+
+def test_record_buffer_follows_the_lanes():
+    # one 64^3 brick of few labels at random, half a million symbols and more: encoded with one lane it
+    # takes no more memory than with 256 (a buffer of 64 lanes' room would take 64 bytes a symbol more)
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = ("import numpy as np, resource, paper_2609_36898_amd as P\n"
+            "v = np.random.default_rng(0).integers(1, 17, 64 ** 3).astype(np.uint32)\n"
+            "go = lambda s: P.csgv_encode_bricks(v, [6], 4, coder_policy=2, lane_syms=s, n_threads=1)\n"
+            "go(64)\n"
+            "a = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss\n"
+            "go(1 << 20)\n"
+            "print(resource.getrusage(resource.RUSAGE_SELF).ru_maxrss - a)")
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, check=True)
+    assert int(r.stdout.split()[-1]) < 8192, "KiB more"
