@@ -232,7 +232,8 @@ csgv_status csgv_plan_set_timing(csgv_plan* plan, int enable);
 
 /* Change the launch shape (fields left 0, or -1 for sort_tasks and
    wgs_per_cu, keep their value); scratch is re-sized when needed, which
-   synchronises the device. */
+   synchronises the device.  A change that fails (CSGV_ENOMEM when the scratch
+   does not fit) leaves the plan as it was. */
 csgv_status csgv_plan_set_opts(csgv_plan* plan, const csgv_decode_opts* opts);
 
 /* The shape the plan launches with (wgs_per_cu resolved to the grid / CUs). */

@@ -381,7 +381,33 @@ csgv_status plan_enqueue(csgv_plan* p, hipStream_t s, const Params& P0, bool wit
     return CSGV_OK;
 }
 
-// (re)size the plan's grid and scratch for its current shape
+// Device memory of a plan for `grid` work-groups: their scratch, and behind it the
+// control words, lists, offsets and the volume's rANS table, which is built here
+// once for every launch of the plan.
+csgv_status plan_take(csgv_plan* p, uint32_t grid, uint64_t sb) {
+    hipError_t e = hipMalloc(&p->mem, sb + aux_bytes(p->max_tasks));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();  // (the next launch asks for it)
+        p->mem = nullptr;
+        return fail(CSGV_ENOMEM, "plan scratch (%llu bytes): %s", (unsigned long long)sb, hipGetErrorString(e));
+    }
+    carve(p->mem, sb, p->max_tasks, &p->b);
+    p->grid = grid;
+    p->scratch_bytes = sb;
+    bool ok;
+    const RansFreq f = pack_freq(&p->vol, &ok);
+    if ((e = launch_prepare(p->b.ctl, ok ? p->b.rans_tab : nullptr, &f, nullptr)) != hipSuccess ||
+        (e = hipDeviceSynchronize()) != hipSuccess) {
+        (void)hipFree(p->mem);
+        p->mem = nullptr;
+        return fail(CSGV_EHIP, "rANS table: %s", hipGetErrorString(e));
+    }
+    p->b.prepared = true;
+    return CSGV_OK;
+}
+
+// (re)size the plan's grid and scratch for its current shape; when that fails the
+// plan takes back the memory it had
 csgv_status plan_alloc(csgv_plan* p) {
     const int per_cu = p->opts.wgs_per_cu > 0 ? p->opts.wgs_per_cu : resident_per_cu(p->opts.wg_size, p->opts.lds_slots);
     const uint32_t grid = (uint32_t)std::min<uint64_t>((uint64_t)device_cus() * per_cu, p->max_tasks);
@@ -391,26 +417,20 @@ csgv_status plan_alloc(csgv_plan* p) {
         p->grid = grid;
         return CSGV_OK;
     }
+    const uint32_t had = p->mem ? p->grid : 0;
+    const uint64_t had_bytes = p->scratch_bytes;
     if (p->mem) {
         (void)hipDeviceSynchronize();
         (void)hipFree(p->mem);
         p->mem = nullptr;
     }
-    hipError_t e = hipMalloc(&p->mem, sb + aux_bytes(p->max_tasks));
-    if (e != hipSuccess) return fail(CSGV_ENOMEM, "plan scratch (%llu bytes): %s", (unsigned long long)sb,
-                                     hipGetErrorString(e));
-    carve(p->mem, sb, p->max_tasks, &p->b);
-    p->grid = grid;
-    p->scratch_bytes = sb;
-    // the volume's rANS table, built once for every launch of the plan, and the
-    // control words, which every launch leaves zero
-    bool ok;
-    const RansFreq f = pack_freq(&p->vol, &ok);
-    if ((e = launch_prepare(p->b.ctl, ok ? p->b.rans_tab : nullptr, &f, nullptr)) != hipSuccess ||
-        (e = hipDeviceSynchronize()) != hipSuccess)
-        return fail(CSGV_EHIP, "rANS table: %s", hipGetErrorString(e));
-    p->b.prepared = true;
-    return CSGV_OK;
+    const csgv_status st = plan_take(p, grid, sb);
+    if (st != CSGV_OK && had) {
+        const std::string why = g_last_error;
+        (void)plan_take(p, had, had_bytes);
+        g_last_error = why;
+    }
+    return st;
 }
 
 }  // namespace
@@ -436,7 +456,7 @@ csgv_status csgv_plan_create(const csgv_volume_info* vol, uint32_t max_tasks, co
     p->opts.lds_slots = opts && opts->lds_slots > 0 ? opts->lds_slots : (int)kDefaultCap16;
     p->opts.palette_bits = opts && opts->palette_bits > 0 ? opts->palette_bits : 0;
     if ((st = plan_alloc(p)) != CSGV_OK) {
-        delete p;
+        csgv_plan_destroy(p);
         return st;
     }
     if (hipEventCreate(&p->ev0) != hipSuccess || hipEventCreate(&p->ev1) != hipSuccess) {
@@ -487,6 +507,7 @@ csgv_status csgv_plan_launch(csgv_plan* p, hipStream_t stream, const void* d_con
     if (st != CSGV_OK) return st;
     if (n == 0) return CSGV_OK;
     if (n > p->max_tasks) return fail(CSGV_EINVAL, "n = %u exceeds the plan's max_tasks = %u", n, p->max_tasks);
+    if (!p->mem) return fail(CSGV_ENOMEM, "the plan lost its scratch to a change of shape that did not fit");
     Params P = make_params(&p->vol, d_container, d_brick_ids, d_lods, d_out_offsets, n, d_out, out_capacity, d_status);
     st = plan_enqueue(p, stream, P, p->timing);
     p->ev_valid = st == CSGV_OK && p->timing;
