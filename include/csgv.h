@@ -236,7 +236,10 @@ csgv_status csgv_plan_set_timing(csgv_plan* plan, int enable);
    does not fit) leaves the plan as it was. */
 csgv_status csgv_plan_set_opts(csgv_plan* plan, const csgv_decode_opts* opts);
 
-/* The shape the plan launches with (wgs_per_cu resolved to the grid / CUs). */
+/* The shape of a launch of max_tasks tasks (wgs_per_cu resolved to the grid /
+   CUs); smaller launches run another one while the shape is left to default (see
+   csgv_decode_opts).  Handing all of it back to csgv_plan_set_opts does not fix
+   the shape; setting any field of it to something else does, for every n. */
 csgv_status csgv_plan_get_opts(const csgv_plan* plan, csgv_decode_opts* out);
 
 /* Duration of the most recent decode kernel launched by the plan, in milliseconds
@@ -252,10 +255,11 @@ void csgv_plan_destroy(csgv_plan* plan);
  * work-group size {128, 256, 512} x LDS split {8192, 10240, 16384, 24576}
  * slots, as many resident groups per CU as fit -- with HIP events on
  * `stream` (first launch of each shape discarded, best of three kept), and
- * leaves the plan on the fastest.  cache_path (or NULL): a text file of
- * "key<TAB>wg lds wgs_per_cu" lines; the key is the GPU architecture, CU
- * count, volume (label width, brick side, bricks, bytes) and task list (count,
- * LOD histogram).  A key already in the file is applied without timing.
+ * leaves the plan on the fastest, whatever the n of later launches.
+ * cache_path (or NULL): a text file of "key<TAB>wg lds wgs_per_cu" lines; the
+ * key is the GPU architecture, CU count, volume (label width, brick side,
+ * bricks, bytes) and task list (count, LOD histogram).  A key already in the
+ * file is applied without timing.
  * Writes d_out/d_status like a launch; synchronises `stream`.
  */
 typedef struct {

@@ -369,12 +369,18 @@ uint32_t plan_grid(const csgv_plan* p, uint32_t n) {
     return std::min<uint32_t>(p->grid, std::max<uint32_t>(n, 1));
 }
 
+// the shape that a launch of n tasks runs
+void plan_shape(const csgv_plan* p, uint32_t n, int* wg, uint32_t* cap16) {
+    *wg = p->opts.wg_size;
+    *cap16 = std::max<uint32_t>((uint32_t)p->opts.lds_slots, kMinCap16) & ~7u;
+    if (p->auto_shape) auto_shape(n, wg, cap16);
+}
+
 csgv_status plan_enqueue(csgv_plan* p, hipStream_t s, const Params& P0, bool with_events) {
     Params P = P0;
-    P.cap16 = std::max<uint32_t>((uint32_t)p->opts.lds_slots, kMinCap16) & ~7u;
     P.pal_bits = p->opts.palette_bits > 0 ? (uint32_t)p->opts.palette_bits : 0u;
-    int wg = p->opts.wg_size;
-    if (p->auto_shape) auto_shape(P.n_tasks, &wg, &P.cap16);
+    int wg;
+    plan_shape(p, P.n_tasks, &wg, &P.cap16);
     hipError_t e = enqueue(P, p->b, &p->vol, wg, plan_grid(p, P.n_tasks), true, p->opts.sort_tasks != 0, s,
                            with_events ? p->ev0 : nullptr, with_events ? p->ev1 : nullptr);
     if (e != hipSuccess) return fail(CSGV_EHIP, "plan launch: %s", hipGetErrorString(e));
@@ -433,6 +439,24 @@ csgv_status plan_alloc(csgv_plan* p) {
     return st;
 }
 
+// Change a plan's options; a work-group size, LDS split or number of work-groups
+// that is given ends the choice of the shape by the number of tasks.
+csgv_status plan_set(csgv_plan* p, const csgv_decode_opts& o) {
+    csgv_status st = check_opts(&o);
+    if (st != CSGV_OK) return st;
+    const csgv_decode_opts old = p->opts;
+    csgv_decode_opts& n = p->opts;
+    if (o.wg_size) n.wg_size = o.wg_size;
+    if (o.wgs_per_cu >= 0) n.wgs_per_cu = o.wgs_per_cu;
+    if (o.sort_tasks >= 0) n.sort_tasks = o.sort_tasks ? 1 : 0;
+    if (o.bricks_per_wave > 0) n.bricks_per_wave = o.bricks_per_wave;
+    if (o.lds_slots > 0) n.lds_slots = o.lds_slots;
+    if (o.palette_bits >= 0) n.palette_bits = o.palette_bits;
+    if (o.wg_size || o.lds_slots > 0 || o.wgs_per_cu > 0) p->auto_shape = false;
+    if ((st = plan_alloc(p)) != CSGV_OK) p->opts = old;
+    return st;
+}
+
 }  // namespace
 
 extern "C" {
@@ -480,23 +504,14 @@ csgv_status csgv_plan_set_timing(csgv_plan* p, int enable) {
 
 csgv_status csgv_plan_set_opts(csgv_plan* p, const csgv_decode_opts* o) {
     if (!p || !o) return fail(CSGV_EINVAL, "NULL argument");
-    csgv_status st = check_opts(o);
-    if (st != CSGV_OK) return st;
-    csgv_decode_opts n = p->opts;
-    if (o->wg_size) n.wg_size = o->wg_size;
-    if (o->wgs_per_cu >= 0) n.wgs_per_cu = o->wgs_per_cu;
-    if (o->sort_tasks >= 0) n.sort_tasks = o->sort_tasks ? 1 : 0;
-    if (o->bricks_per_wave > 0) n.bricks_per_wave = o->bricks_per_wave;
-    if (o->lds_slots > 0) n.lds_slots = o->lds_slots;
-    if (o->palette_bits >= 0) n.palette_bits = o->palette_bits;
-    const csgv_decode_opts old = p->opts;
-    p->opts = n;
-    if (o->wg_size || o->lds_slots > 0 || o->wgs_per_cu > 0) p->auto_shape = false;
-    if ((st = plan_alloc(p)) != CSGV_OK) {
-        p->opts = old;
-        return st;
+    // the shape that the plan reports, handed back, is no choice of a shape
+    csgv_decode_opts now, n = *o;
+    (void)csgv_plan_get_opts(p, &now);
+    if (o->wg_size == now.wg_size && o->lds_slots == now.lds_slots && o->wgs_per_cu == now.wgs_per_cu) {
+        n.wg_size = n.lds_slots = 0;
+        n.wgs_per_cu = -1;
     }
-    return CSGV_OK;
+    return plan_set(p, n);
 }
 
 csgv_status csgv_plan_launch(csgv_plan* p, hipStream_t stream, const void* d_container, const uint32_t* d_brick_ids,
@@ -517,6 +532,11 @@ csgv_status csgv_plan_launch(csgv_plan* p, hipStream_t stream, const void* d_con
 csgv_status csgv_plan_get_opts(const csgv_plan* p, csgv_decode_opts* out) {
     if (!p || !out) return fail(CSGV_EINVAL, "NULL argument");
     *out = p->opts;
+    if (p->auto_shape) {
+        uint32_t cap16;
+        plan_shape(p, p->max_tasks, &out->wg_size, &cap16);
+        out->lds_slots = (int)cap16;
+    }
     if (out->wgs_per_cu == 0) out->wgs_per_cu = (int)(p->grid / std::max(1, device_cus()));
     return CSGV_OK;
 }
@@ -612,7 +632,7 @@ extern "C" csgv_status csgv_plan_autotune(csgv_plan* p, hipStream_t stream, cons
     memset(&rep, 0, sizeof(rep));
     csgv_decode_opts cached = p->opts;
     if (tune_lookup(cache_path, key, &cached)) {
-        if ((st = csgv_plan_set_opts(p, &cached)) != CSGV_OK) return st;
+        if ((st = plan_set(p, cached)) != CSGV_OK) return st;
         rep.from_cache = 1;
         rep.chosen = p->opts;
         if (report) *report = rep;
@@ -622,7 +642,7 @@ extern "C" csgv_status csgv_plan_autotune(csgv_plan* p, hipStream_t stream, cons
     p->timing = true;
     const csgv_decode_opts start = p->opts;
     auto time_shape = [&](const csgv_decode_opts& o, float* best) -> csgv_status {
-        csgv_status s2 = csgv_plan_set_opts(p, &o);
+        csgv_status s2 = plan_set(p, o);
         if (s2 != CSGV_OK) return s2;
         *best = 1e30f;
         for (int rep_i = 0; rep_i < 4; ++rep_i) {
@@ -660,7 +680,7 @@ extern "C" csgv_status csgv_plan_autotune(csgv_plan* p, hipStream_t stream, cons
             }
         }
     p->timing = had_timing;
-    if ((st = csgv_plan_set_opts(p, &best)) != CSGV_OK) return st;
+    if ((st = plan_set(p, best)) != CSGV_OK) return st;
     tune_store(cache_path, key, best);
     rep.tried = tried;
     rep.best_ms = best_ms;
