@@ -452,8 +452,8 @@ csgv_status plan_set(csgv_plan* p, const csgv_decode_opts& o) {
     if (o.bricks_per_wave > 0) n.bricks_per_wave = o.bricks_per_wave;
     if (o.lds_slots > 0) n.lds_slots = o.lds_slots;
     if (o.palette_bits >= 0) n.palette_bits = o.palette_bits;
-    if (o.wg_size || o.lds_slots > 0 || o.wgs_per_cu > 0) p->auto_shape = false;
     if ((st = plan_alloc(p)) != CSGV_OK) p->opts = old;
+    else if (o.wg_size || o.lds_slots > 0 || o.wgs_per_cu > 0) p->auto_shape = false;
     return st;
 }
 

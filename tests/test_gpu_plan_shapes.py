@@ -104,14 +104,14 @@ def test_a_shape_that_does_not_fit_leaves_the_plan_as_it_was(P):
     dv = P.DeviceVolume(c)
     rng = np.random.default_rng(0)
     plan = P.csgv_plan(dv.info, 1 << 22)
-    before = plan.get_opts().as_dict()
+    before, few = plan.get_opts().as_dict(), _launched(dv, plan, 40)
     for n in (40, 1500):
         ids, lods = rng.integers(0, 3, n).astype(np.uint32), rng.integers(0, 7, n).astype(np.uint8)
         _decode(P, plan, dv, c, ids, lods)
         with pytest.raises(P.CsgvError) as e:
             plan.set_opts(wgs_per_cu=1 << 14)
         assert e.value.code == P.csgv.CSGV_ENOMEM
-        assert plan.get_opts().as_dict() == before
+        assert plan.get_opts().as_dict() == before and _launched(dv, plan, 40) == few
         _decode(P, plan, dv, c, ids, lods)
     plan.destroy()
     with pytest.raises(P.CsgvError) as e:  # and no plan at all where none fits
