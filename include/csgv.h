@@ -266,7 +266,7 @@ typedef struct {
     int from_cache;            /* 1: shape taken from cache_path */
     int tried;                 /* shapes timed */
     float best_ms;             /* decode-kernel time of the chosen shape */
-    float default_ms;          /* decode-kernel time of the default shape (256 threads, 10240 slots) */
+    float default_ms;          /* decode-kernel time of the default shape of n tasks */
     csgv_decode_opts chosen;   /* the plan's shape afterwards */
 } csgv_tune_report;
 

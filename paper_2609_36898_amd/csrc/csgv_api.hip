@@ -657,6 +657,9 @@ extern "C" csgv_status csgv_plan_autotune(csgv_plan* p, hipStream_t stream, cons
     };
     static const int kWg[] = {128, 256, 512};
     static const int kLds[] = {8192, 10240, 16384, 24576};
+    int wg0 = 256;  // the default shape of n tasks, one of those tried
+    uint32_t lds0 = kDefaultCap16;
+    auto_shape(n, &wg0, &lds0);
     float best_ms = 1e30f;
     csgv_decode_opts best = start;
     int tried = 0;
@@ -673,7 +676,7 @@ extern "C" csgv_status csgv_plan_autotune(csgv_plan* p, hipStream_t stream, cons
                 return st;
             }
             ++tried;
-            if (wg == 256 && lds == (int)kDefaultCap16) rep.default_ms = ms;
+            if (wg == wg0 && lds == (int)lds0) rep.default_ms = ms;
             if (ms < best_ms) {
                 best_ms = ms;
                 best = o;

@@ -98,6 +98,31 @@ def test_the_reported_shape_is_launched_and_may_be_handed_back(P, max_tasks, kw)
     assert _launched(dv, plan, max_tasks)[0] == _launched(dv, plan, 5)[0] == plan.get_opts().wg_size == 256
 
 
+def test_the_tuner_reports_the_default_shape_of_its_tasks(P):
+    # at two tasks per CU and fewer the default is 512 threads with 24,576 slots, which is also the fastest
+    # shape where level 5 fits in no smaller split; the time reported for it is then the best one
+    import torch
+    v = np.concatenate([synth.voronoi_u32(64, 900, seed=k).reshape(-1) for k in range(3)])
+    c = P.csgv_encode_bricks(v, [6] * 3, 4, origins=np.zeros((3, 3), np.uint32))
+    dv = P.DeviceVolume(c)
+    n = 100
+    ids, lods = (np.arange(n) % 3).astype(np.uint32), np.ones(n, np.uint8)
+    d_ids, d_lods, d_offs, _, total = dv.tasks(ids, lods)
+    out = torch.zeros(total, dtype=torch.int32, device="cuda")
+    plan = P.csgv_plan(dv.info, n)
+    default = plan.get_opts()
+    chosen = 0
+    for _ in range(5):
+        rep = plan.autotune(None, dv.tensor, d_ids, d_lods, d_offs, n, out, total)
+        assert 0 < rep.best_ms <= rep.default_ms and rep.tried == 12
+        if (rep.chosen.wg_size, rep.chosen.lds_slots) == (default.wg_size, default.lds_slots):
+            chosen += 1
+            assert rep.default_ms == rep.best_ms
+    assert chosen
+    assert _launched(dv, plan, n)[0] == rep.chosen.wg_size == plan.get_opts().wg_size
+    _decode(P, plan, dv, c, ids, lods)
+
+
 def test_a_shape_that_does_not_fit_leaves_the_plan_as_it_was(P):
     # 4 million work-groups' scratch is refused by the allocator (5.8 TB)
     c = _volume64(P)
