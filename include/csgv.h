@@ -167,8 +167,12 @@ csgv_status csgv_volume_parse(const void* h_container, uint64_t bytes, csgv_volu
  *   d_status       n task status words (CSGV_TASK_*), or NULL.
  *   opts           NULL for defaults (plain form).
  * Output ranges of different tasks must not overlap.  Device scratch is
- * allocated and freed stream-ordered inside the call.  Returns CSGV_OK,
- * CSGV_EINVAL, CSGV_ENOMEM or CSGV_EHIP.
+ * allocated and freed stream-ordered inside the call: per work-group 226 KiB for
+ * volumes of bricks up to 32^3 and 1.33 MiB for 64^3, for as many as there are
+ * tasks or as the GPU holds (at most 4 per compute unit by default, so up to
+ * 0.24 and 1.43 GB on 256), and 8 bytes a task, 32 in the persistent form.
+ * Where that is refused the plain form takes fewer work-groups, down to one.
+ * Returns CSGV_OK, CSGV_EINVAL, CSGV_ENOMEM or CSGV_EHIP.
  */
 csgv_status csgv_decode_bricks(hipStream_t stream, const csgv_volume_info* vol, const void* d_container,
                                const uint32_t* d_brick_ids, const uint8_t* d_lods, const uint64_t* d_out_offsets,
