@@ -188,7 +188,7 @@ csgv_status csgv_decode_bricks(hipStream_t stream, const csgv_volume_info* vol, 
  * until the process ends (its device address is looked up on the first call
  * on each device).  Limits: at most CSGV_NOALLOC_MAX_TASKS tasks per call
  * (else CSGV_EINVAL), and the persistent grid holds only as many work-groups
- * as the array's scratch share fits (about 520 for 32^3 bricks, 85 for 64^3),
+ * as the array's scratch share fits (542 for 32^3 bricks, 90 for 64^3),
  * so large batches run slower than with csgv_decode_bricks.  Every call on a
  * GPU uses that GPU's one array: calls that overlap on one GPU (other streams,
  * other threads) race and must be serialised by the caller.  The array keeps
@@ -213,8 +213,9 @@ csgv_status csgv_check_status(const uint32_t* d_status, uint32_t n, hipStream_t 
  * queue, optionally in decreasing estimated cost -- after one kernel that
  * sorts the tasks into cost classes and computes dense offsets (when either is
  * needed).  The plan owns its device scratch (sized by vol->max_log2b and the
- * grid) and the volume's rANS table.  A plan serves one stream at a time; distinct plans may be used from different threads.
- * max_tasks bounds n of every launch.
+ * grid) and the volume's rANS table.  A plan serves one stream at a time;
+ * distinct plans may be used from different threads.  max_tasks bounds n of
+ * every launch.
  */
 typedef struct csgv_plan csgv_plan;
 
@@ -231,7 +232,8 @@ csgv_status csgv_plan_launch(csgv_plan* plan, hipStream_t stream, const void* d_
    which are enqueued directly (a graph of them would start later). */
 csgv_status csgv_plan_set_graph(csgv_plan* plan, int enable);
 
-/* When enabled, launches bracket the decode kernel with HIP events on the launch stream (read with csgv_plan_last_kernel_ms). */
+/* When enabled, launches bracket the decode kernel with HIP events on the launch
+   stream (read with csgv_plan_last_kernel_ms). */
 csgv_status csgv_plan_set_timing(csgv_plan* plan, int enable);
 
 /* Change the launch shape (fields left 0, or -1 for sort_tasks and

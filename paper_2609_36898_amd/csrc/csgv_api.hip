@@ -84,8 +84,10 @@ int resident_per_cu(int wg, uint32_t cap16) {
 // and 512 threads shorten it (64 bricks of 32^3: 58 -> 50 us, 512: 63 -> 55; 64
 // bricks of 64^3 0.63 -> 0.47 ms; 1024 threads 55 and 89 us and 0.41 ms); such
 // work-groups leave LDS for 24,576 slots, which hold level 5 of most 64^3 bricks
-// at LOD 1 (512 cubes: 0.18 -> 0.14 ms).  From three tasks per CU on,
-// work-groups of 256 threads keep more bricks in flight.
+// at LOD 1 (512 cubes: 0.18 -> 0.14 ms).  1024 threads are the faster ones for 64^3
+// cubes alone; a volume of 64^3 bricks decodes 32^3 cubes too, at LOD 1, and the
+// LODs are in device memory, so the number of tasks is what the rule goes by.
+// From three tasks per CU on, work-groups of 256 threads keep more bricks in flight.
 void auto_shape(uint32_t n, int* wg, uint32_t* cap16) {
     if (n <= 2u * (uint32_t)device_cus()) {
         *wg = 512;
@@ -163,7 +165,7 @@ struct Bufs {
     uint64_t* dense = nullptr;   // max_tasks
     uint64_t* base = nullptr;    // one per block of kBinTasks
     uint64_t* totals = nullptr;  // one per block of kBinTasks
-    bool prepared = false;       // the table is built and the control words are zero
+    bool prepared = false;       // the table is built and the binning kernel's counts are zero
 };
 
 uint64_t bin_blocks(uint64_t max_tasks) { return (max_tasks + kBinTasks - 1) / kBinTasks; }

@@ -57,6 +57,8 @@ constexpr uint64_t scratch_per_wg(uint32_t max_log2b) {
 constexpr uint32_t kClasses = 6, kWgClasses = 4;
 // Control words of a launch.  The binning kernel's last block leaves them ready
 // for the decode that follows: the classes' sizes in job, everything else zero.
+// That decode leaves queue, small and job as it used them, so every decode with
+// ctl set comes behind a binning kernel; ticket and count are zero in between.
 struct Control {
     uint32_t ticket;            // blocks of the binning kernel done
     uint32_t count[kClasses];   // tasks per class while they are binned

@@ -168,11 +168,8 @@ __device__ __forceinline__ uint32_t dpp(uint32_t old, uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xF, false);
 }
 constexpr int kDppRowShr = 0x110;   // + n: lane l takes lane l - n of its row of 16
-constexpr int kDppWaveShl1 = 0x130;  // lane l takes lane l + 1
-constexpr int kDppWaveShr1 = 0x138;  // lane l takes lane l - 1
 constexpr int kDppBcast15 = 0x142;   // rows 1, 3 take lane 15 of the row before
 constexpr int kDppBcast31 = 0x143;   // rows 2, 3 take lane 31
-constexpr uint32_t kFnId = 2u;       // transfer function that keeps the state
 
 // inclusive sum over the wavefront (lane 0 first)
 __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t x) {
@@ -1810,8 +1807,9 @@ __device__ __forceinline__ void decode_task(const Params& P, uint8_t* lds, uint8
     uint8_t* const u_area = lds + sizeof(Shared);
     uint16_t* const slots = (uint16_t*)(u_area + u_bytes);
     // The symbols, 4 bits each, are read by the level passes as aligned 32-bit
-    // words: plain payloads from the record itself, rANS symbols from LDS for a
-    // cube of side <= 16, else from the work-group's scratch.
+    // words: plain payloads from the record itself, rANS symbols from LDS when they
+    // fit there together with the record's words and the decoding table (`fits`, as
+    // nearly all of a 32^3 brick do), else from the work-group's scratch.
     const uint32_t wave = wave_id(), t = uni(h.t), nsym = uni(h.nsym), n_words = (nsym + 7u) / 8u;
     const bool rans = uni(h.coder) == kRans;
     // While the symbols are decoded: the words between the level 0..3 grids and
@@ -2124,7 +2122,7 @@ __global__ void prepare_kernel(Control* ctl, uint32_t* tab, RansFreq f) {
     if (tab && slot < kRansM) table_slot(tab, f, slot);
 }
 
-// brick side exponent of a task's record (0 when the task or record is unusable)
+// side exponent of a task's cube (0xFF when the task or record is unusable)
 __device__ __forceinline__ uint32_t task_t(const Params& P, uint32_t j, uint64_t* rec_bytes) {
     const uint32_t id = P.ids[j];
     *rec_bytes = 0;
@@ -2141,8 +2139,8 @@ __device__ __forceinline__ uint32_t task_t(const Params& P, uint32_t j, uint64_t
 
 // Lanes of one wavefront grouped by class: for every distinct class c among
 // the lanes with c < 64, f(c, mask of the lanes holding it) runs once, with
-// the lowest such lane as the leader.  One atomic per (wavefront, class)
-// instead of one per task keeps the cost sort free of same-address contention.
+// the lowest such lane as the leader: a lane's rank among its class and the
+// wavefront's count of it, from which the block takes one atomic per class.
 template <typename F>
 __device__ __forceinline__ void for_each_class(uint32_t c, F f) {
     uint64_t left = __ballot(c < 64u);

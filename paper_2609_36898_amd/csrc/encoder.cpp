@@ -334,7 +334,8 @@ inline void put32(std::vector<uint8_t>& v, size_t at, uint32_t x) { memcpy(&v[at
 // multiplication: q = x * rcp >> 64 is x / f for x < 2^32 and f <= 4096 (Granlund
 // and Montgomery, "Division by invariant integers using multiplication", 1994),
 // and the step is x + bias + q * (4096 - f).  f = 1 has no 64-bit reciprocal:
-// its q is x - 1, which its bias makes good.
+// its q is x - 1, which its bias makes good.  (The four quantities per symbol and
+// the way out for f = 1 are those of Giesen's public-domain rANS coder, 2014.)
 struct RansStep {
     uint64_t rcp, limit;
     uint32_t bias, rest;

@@ -192,7 +192,6 @@ csgv_status csgv_server_create(const csgv_volume_info* vol, const void* d_contai
                 destroy_server(s);
                 return serve_fail(st, msg.c_str());
             }
-            (void)csgv_plan_set_graph(l.plan, 0);  // batches differ in size: direct launches
             (void)csgv_plan_set_timing(l.plan, 1);
         }
         bes.push_back(&be);
