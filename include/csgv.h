@@ -117,7 +117,8 @@ typedef struct {
     int bricks_per_wave; /* tasks a wavefront takes at a time; only 1 is implemented        */
     int lds_slots;       /* LDS split: 16-bit slots per work-group for the explicit nodes of
                             level 5 (bricks needing more use global scratch); the area also
-                            holds the rANS table, so 8192..32760; default 10240             */
+                            holds the rANS table, so 8192..32760; default 10240, with
+                            work-groups of 1024 threads (one per compute unit) 32760        */
     int palette_bits;    /* 0: labels (default).  I in 1..31: cache-paletted output, see
                             CSGV_PALETTED_WORDS                                             */
 } csgv_decode_opts;

@@ -79,6 +79,14 @@ int resident_per_cu(int wg, uint32_t cap16) {
     return std::max(1, std::min(by_lds, max_resident_per_cu(wg, std::max<uint32_t>(cap16, kMinCap16))));
 }
 
+// The LDS split of a work-group size whose split the caller left to the default.  A
+// CU holds one work-group of 1024 threads, whatever its LDS (16 wavefronts of 128
+// VGPRs), so it takes the largest split: with that of four work-groups of 256 its
+// passes over a level in chunks are as short as theirs, and behind more barriers
+// (2000 cubes of 32^3 noise, rANS: 0.87 ms with 10,240 slots, 0.56 with 32,760;
+// three labels at random 1.05 and 0.48).
+uint32_t default_slots(int wg) { return wg == 1024 ? kMaxCap16 : kDefaultCap16; }
+
 // The shape of a launch whose work-group size and LDS split the caller left to
 // the default.  With at most two tasks per CU a task's latency is the launch's,
 // and 512 threads shorten it (64 bricks of 32^3: 58 -> 50 us, 512: 63 -> 55; 64
@@ -304,9 +312,9 @@ csgv_status prepare_call(const csgv_volume_info* vol, const void* d_container, c
     *mode = opts ? opts->mode : CSGV_MODE_PLAIN;
     if (*mode != CSGV_MODE_PLAIN && *mode != CSGV_MODE_PERSISTENT) return fail(CSGV_EINVAL, "unknown mode %d", *mode);
     *P = make_params(vol, d_container, d_brick_ids, d_lods, d_out_offsets, n, d_out, out_capacity, d_status);
-    if (opts && opts->lds_slots > 0) P->cap16 = std::max<uint32_t>((uint32_t)opts->lds_slots, kMinCap16) & ~7u;
     if (opts && opts->palette_bits > 0) P->pal_bits = (uint32_t)opts->palette_bits;
     *wg = opts && opts->wg_size ? opts->wg_size : 256;
+    P->cap16 = std::max<uint32_t>(opts && opts->lds_slots > 0 ? (uint32_t)opts->lds_slots : default_slots(*wg), kMinCap16) & ~7u;
     if (!(opts && (opts->wg_size || opts->lds_slots || opts->wgs_per_cu > 0))) auto_shape(n, wg, &P->cap16);
     *per_cu = opts && opts->wgs_per_cu > 0 ? opts->wgs_per_cu : resident_per_cu(*wg, P->cap16);
     // (in task order more work-groups than the GPU holds only take scratch)
@@ -384,10 +392,14 @@ uint32_t plan_grid(const csgv_plan* p, uint32_t n) {
     return std::min<uint32_t>(p->grid, std::max<uint32_t>(n, 1));
 }
 
+uint32_t plan_slots(const csgv_plan* p) {
+    return p->opts.lds_slots > 0 ? (uint32_t)p->opts.lds_slots : default_slots(p->opts.wg_size);
+}
+
 // the shape that a launch of n tasks runs
 void plan_shape(const csgv_plan* p, uint32_t n, int* wg, uint32_t* cap16) {
     *wg = p->opts.wg_size;
-    *cap16 = std::max<uint32_t>((uint32_t)p->opts.lds_slots, kMinCap16) & ~7u;
+    *cap16 = std::max<uint32_t>(plan_slots(p), kMinCap16) & ~7u;
     if (p->auto_shape) auto_shape(n, wg, cap16);
 }
 
@@ -430,7 +442,7 @@ csgv_status plan_take(csgv_plan* p, uint32_t grid, uint64_t sb) {
 // (re)size the plan's grid and scratch for its current shape; when that fails the
 // plan takes back the memory it had
 csgv_status plan_alloc(csgv_plan* p) {
-    const int per_cu = p->opts.wgs_per_cu > 0 ? p->opts.wgs_per_cu : resident_per_cu(p->opts.wg_size, p->opts.lds_slots);
+    const int per_cu = p->opts.wgs_per_cu > 0 ? p->opts.wgs_per_cu : resident_per_cu(p->opts.wg_size, plan_slots(p));
     const uint32_t grid = (uint32_t)std::min<uint64_t>((uint64_t)device_cus() * per_cu, p->max_tasks);
     const uint32_t lmax = p->vol.max_log2b ? std::min<uint32_t>(p->vol.max_log2b, kMaxLog2b) : kMaxLog2b;
     const uint64_t sb = scratch_per_wg(lmax) * grid;
@@ -492,7 +504,7 @@ csgv_status csgv_plan_create(const csgv_volume_info* vol, uint32_t max_tasks, co
     p->opts.wgs_per_cu = opts && opts->wgs_per_cu > 0 ? opts->wgs_per_cu : 0;
     p->opts.sort_tasks = opts && opts->sort_tasks >= 0 ? opts->sort_tasks : 1;
     p->opts.bricks_per_wave = opts && opts->bricks_per_wave > 0 ? opts->bricks_per_wave : 1;
-    p->opts.lds_slots = opts && opts->lds_slots > 0 ? opts->lds_slots : (int)kDefaultCap16;
+    p->opts.lds_slots = opts && opts->lds_slots > 0 ? opts->lds_slots : 0;
     p->opts.palette_bits = opts && opts->palette_bits > 0 ? opts->palette_bits : 0;
     if ((st = plan_alloc(p)) != CSGV_OK) {
         csgv_plan_destroy(p);
@@ -547,11 +559,9 @@ csgv_status csgv_plan_launch(csgv_plan* p, hipStream_t stream, const void* d_con
 csgv_status csgv_plan_get_opts(const csgv_plan* p, csgv_decode_opts* out) {
     if (!p || !out) return fail(CSGV_EINVAL, "NULL argument");
     *out = p->opts;
-    if (p->auto_shape) {
-        uint32_t cap16;
-        plan_shape(p, p->max_tasks, &out->wg_size, &cap16);
-        out->lds_slots = (int)cap16;
-    }
+    uint32_t cap16;
+    plan_shape(p, p->max_tasks, &out->wg_size, &cap16);
+    if (p->opts.lds_slots == 0) out->lds_slots = (int)cap16;
     if (out->wgs_per_cu == 0) out->wgs_per_cu = (int)(p->grid / std::max(1, device_cus()));
     return CSGV_OK;
 }

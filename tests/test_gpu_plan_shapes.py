@@ -75,7 +75,7 @@ def _launched(dv, plan, n):
 
 
 @pytest.mark.parametrize("max_tasks", [5, 300, 512, 513, 600, 3000])
-@pytest.mark.parametrize("kw", [{}, dict(wg_size=128), dict(lds_slots=8203), dict(wg_size=1024, lds_slots=16384, wgs_per_cu=1)])
+@pytest.mark.parametrize("kw", [{}, dict(wg_size=1024), dict(wg_size=128), dict(lds_slots=8203), dict(wg_size=1024, lds_slots=16384, wgs_per_cu=1)])
 def test_the_reported_shape_is_launched_and_may_be_handed_back(P, max_tasks, kw):
     import torch
     dv = P.DeviceVolume(P.encode_volume(synth.voronoi_u32(64, 40, seed=1), 5))
@@ -89,6 +89,8 @@ def test_the_reported_shape_is_launched_and_may_be_handed_back(P, max_tasks, kw)
         assert all(getattr(o, k) == v for k, v in kw.items())
     else:
         assert (o.wg_size, o.lds_slots) == ((512, 24576) if max_tasks <= two else (256, 10240))
+    if "lds_slots" not in kw and "wg_size" in kw:  # a CU's one work-group of 1024 threads has its LDS to itself
+        assert o.lds_slots == (32760 if kw["wg_size"] == 1024 else 10240)
     few = _launched(dv, plan, 5)
     o.sort_tasks = 0  # one change, everything else handed back
     plan.set_opts(**{k: v for k, v in o.as_dict().items() if k != "mode"})
